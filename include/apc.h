@@ -487,9 +487,9 @@ typedef struct apc_counters {
   int64_t table_samples;    /* samples (m >= 6) whose moment bound needed roots, found by Newton from a
                                start: their pixel's gap table (kept pieces) or the ray's previous sample
                                (re-walk) */
-  int64_t table_fallback;   /* of those, samples that took the closed-form roots: a start that did not
-                               converge (~1e-4 with tables), and in the re-walk every first sample of a ray
-                               in a new gap of the bound (a few percent) */
+  int64_t table_fallback;   /* of those, samples without a carried start: with tables the ones that took the
+                               closed-form roots (~1e-4: a start that did not converge), in the re-walk every
+                               first sample of a ray in a new gap of the bound (a few percent) */
   int64_t segments;         /* maximal ray intervals inside one subdomain with at least one piece, every walk */
 } apc_counters;
 

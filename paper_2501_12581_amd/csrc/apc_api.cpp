@@ -358,8 +358,23 @@ apc_status make_frame(const apc_mesh_s* m, const apc_view* v, const apc_tf* tf, 
   f.step = v->step;
   f.inv_step = 1.0 / v->step;
   double lg0 = std::log2(tn), lg1 = std::log2(tfar);
-  f.lg_near = float(lg0);
-  f.warp_scale = float(2.0 / (lg1 - lg0));
+  const double mean = std::sqrt(tn) * std::sqrt(tfar);
+  f.w_scale = 0.5 / mean;
+  f.w_off = tmid / mean;
+  f.z_scale = 2.0 / (lg1 - lg0);
+  f.lg_half = float(0.5 * (lg1 - lg0));
+  // cutting a chord adds `step` to depths up to `deepest`: it must change them
+  double deepest = 0.0;
+  for (int c = 0; c < 8; ++c) {
+    double d2 = 0.0;
+    for (int k = 0; k < 3; ++k) {
+      const double d = ((c >> k) & 1 ? m->hi[k] : m->lo[k]) - v->eye[k];
+      d2 += d * d;
+    }
+    deepest = std::max(deepest, std::sqrt(d2) + tmid + std::fabs(f.t_near));
+  }
+  f.max_chord = f.step > deepest * 1e-15 ? f.step * double(1 << 22) : -1.0;
+  f.long_chords = 2.0 * deepest > f.max_chord;
   f.s_min = tf->s_min;
   f.tf_scale = float(double(tf->n_entries - 1) / (double(tf->s_max) - double(tf->s_min)));
   f.kappa = tf->kappa;
@@ -871,8 +886,14 @@ apc_status apc_load_mesh(apc_ctx ctx, const apc_mesh_desc* d, apc_mesh* out, voi
       hipSuccess)
     return dev_fail(e, "upload");
   if ((e = hipMalloc(&m->wrec, sizeof(int4) * 8 * T)) != hipSuccess) return dev_fail(e, "alloc");
-  if ((e = apc::launch_walk_records(m->tet, m->vert, T, m->wrec, s)) != hipSuccess) return dev_fail(e, "records");
+  if ((e = d_off.ensure(sizeof(int) * m->sub_begin.size())) != hipSuccess) return dev_fail(e, "alloc");
+  if ((e = hipMemcpyAsync(d_off.p, m->sub_begin.data(), sizeof(int) * m->sub_begin.size(), hipMemcpyHostToDevice,
+                          s)) != hipSuccess)
+    return dev_fail(e, "upload");
+  if ((e = apc::launch_walk_records(m->tet, m->vert, T, d_off.as<int>(), S, m->wrec, s)) != hipSuccess)
+    return dev_fail(e, "records");
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return dev_fail(e, "upload");
+  cleanup();
   m->device_bytes = int64_t(sizeof(float4) * V + sizeof(int4) * 10 * T + sizeof(int) * bface.size());
   *out = m;
   return APC_OK;

@@ -14,8 +14,8 @@ namespace apc {
 struct MeshDev {
   const float4* vert;  // [V]: x, y, z, scalar
   const int4* tet;     // [2T]
-  // [8T]: the walk's record of tet t, one 128-byte line: vertex ids, neighbour
-  // codes, then the four vertices (x, y, z, scalar) in vertex-id order
+  // [8T]: the walk's records of tet t, one 128-byte line: for each face the
+  // tet may be entered through, 32 bytes (k_walk_records)
   const int4* wrec;
   int64_t n_vertices;
   int64_t n_tets;
@@ -48,7 +48,13 @@ struct FrameDev {
   // t_mid = (t_near + t_far) / 2.  t_near below is the lattice origin in
   // those shifted units (t_near - t_mid).
   double t_mid, t_near, step, inv_step;
-  float lg_near, warp_scale;  // log2(t_near), 2 / (log2 t_far - log2 t_near), absolute units
+  double max_chord;           // a longer chord is not cut (2^22 steps, or none where a step is below rounding)
+  int long_chords;            // the mesh may hold longer ones
+  // the warped depth of a point at depth t from the eye is log2(t / sqrt(near far)) * z_scale, the logarithm
+  // clamped to +-lg_half (half that of far / near); the ratio of a piece that ends at u and v (shifted units)
+  // is (u + v) * w_scale + w_off
+  double w_scale, w_off, z_scale;
+  float lg_half;
   float s_min, tf_scale;      // table coordinate = (s - s_min) * tf_scale
   float kappa, amax;
   int max_steps;
@@ -129,8 +135,10 @@ hipError_t launch_sum_moments(const float* in, int n_slots, const int* order, in
                               hipStream_t s);
 hipError_t launch_sum_images(const float* in, int n_slots, const int* order, int64_t pixels, const float* b0,
                              const BoundParams& bp, float* out, hipStream_t s);
-// 128-byte walk records from the tet records and the vertices
-hipError_t launch_walk_records(const int4* tet, const float4* vert, int64_t n_tets, int4* wrec, hipStream_t s);
+// 128 bytes of walk records per tet from the tet records, the vertices and the subdomains' tet ranges
+// (sub_begin: device [n_sub + 1])
+hipError_t launch_walk_records(const int4* tet, const float4* vert, int64_t n_tets, const int* sub_begin, int n_sub,
+                               int4* wrec, hipStream_t s);
 // exclusive scan of n int32 values; tmp must hold scan_tmp_elems(n) ints
 int64_t scan_tmp_elems(int64_t n);
 hipError_t launch_exclusive_scan(const int* in, int* out, int64_t n, int* tmp, hipStream_t s);

@@ -6,17 +6,17 @@
 //   k_moments    one 64-lane wavefront per 8x8 pixel tile: per subdomain,
 //                collect the boundary faces where each pixel ray enters the
 //                subdomain, walk the ray tet by tet from each entry to where
-//                it leaves the subdomain, cut every chord at the global
-//                sampling lattice and add a*z^j per piece (paper Alg. 2)
+//                it leaves the subdomain, queue the chords, cut them at the
+//                global sampling lattice and add a*z^j per piece (Alg. 2)
 //                (with every subdomain on one GPU it also sums them: the
 //                global image; else per-subdomain images, dense or as tiles
 //                of the (tile, subdomain) pairs that have boundary faces)
 //   k_sum_moments / k_sum_tiles  canonical-order FP64 sum of per-subdomain
 //                images or tiles (the paper's moment Allreduce, Section 4.1)
 //   k_resolve    stage two, plain form: per tile a walker wavefront walks the
-//                rays again and hands each piece (depth, length, scalar)
-//                through LDS to an evaluator wavefront, which forms the piece's
-//                optical and warped depths as stage one did, evaluates the
+//                rays again and hands each chord's end (depth, scalar) through
+//                LDS to an evaluator wavefront, which cuts it into the pieces
+//                stage one had, forms their optical and warped depths, evaluates the
 //                moment bound of its pixel (Alg. 3) and weights the piece's
 //                colour by T = exp(-b0 F) (Alg. 1 second loop, Section 4.2)
 //   k_eval       the same evaluation over pieces stage one kept (variant)
@@ -29,9 +29,8 @@
 // higher; the entry test of one subdomain and the exit test of the walk in
 // its neighbour therefore see identical signs for the face they share, so
 // every ray crosses each subdomain interface exactly once (no gaps, no double
-// counting).  The barycentric coordinates of the
-// crossing point are the three edge products of the face, which give the
-// depth t and the scalar at the crossing.  Functions whose results must agree
+// counting).  The barycentric coordinates of the crossing point are the three
+// edge products of the face, which give the depth t and the scalar there.  Functions whose results must agree
 // bit for bit between the two passes or between the entry test and the walk
 // are compiled without floating-point contraction.
 #include <float.h>
@@ -43,20 +42,19 @@ namespace apc {
 namespace {
 
 constexpr int WAVE = 64;
-constexpr int E_MAX = 16;    // entries per ray held at once (more are handled in further rounds)
-constexpr int CHUNK = 64;    // boundary faces staged in LDS at a time
+constexpr int E_MAX = 8;     // entries per ray held at once (more are handled in further rounds)
+constexpr int CHUNK = 32;    // boundary faces staged in LDS at a time
 
-// outward vertex order of the face opposite vertex f of a positively oriented tet
-__device__ __constant__ int kFaceOut[4][3] = {{1, 2, 3}, {0, 3, 2}, {0, 1, 3}, {0, 2, 1}};
+// Outward vertex order of the face opposite vertex f of a positively oriented tet: the local vertices f ^ 1,
+// f ^ 2, f ^ 3 in this order; inward: f ^ 1, f ^ 3, f ^ 2.
 
 __device__ __forceinline__ int sel4(const int4& v, int i) {
   return i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w));
 }
-// The same as an OR of masked components: every component is read (the four
-// come from one load), and no branch or indexed access is left.
-__device__ __forceinline__ int sel4m(const int4& v, int i) {
-  return (v.x & -int(i == 0)) | (v.y & -int(i == 1)) | (v.z & -int(i == 2)) | (v.w & -int(i == 3));
-}
+// b where m is all ones, a where it is 0 (v_bfi_b32: no compare, and nothing for the compiler to branch on)
+__device__ __forceinline__ int bit_select(int m, int a, int b) { return (m & b) | (~m & a); }
+__device__ __forceinline__ unsigned long long ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ bool lane_of(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 // Blocks are dispatched round-robin over the 8 XCDs (block b runs on XCD
 // b % 8).  The tiles are handed out in runs of XCD_RUN consecutive tiles, so
@@ -104,30 +102,30 @@ __device__ __forceinline__ int queue_take(int* q, int nb) {
   return -1;
 }
 
-// A pixel ray in FP64: origin o (moved forward by t_mid), unit direction d,
-// and unit vectors a, b = d x a perpendicular to d, so that (a, b, d) is a
-// right-handed orthonormal frame.
+// A pixel ray in FP64, as what the walk needs of it: with o the origin (moved forward by t_mid), d the unit
+// direction and (a, b, d) a right-handed orthonormal frame, the vectors d, a, b and the offsets -d.o, -a.o, -b.o
+// (a point's coordinates in the frame are then three fused multiply-adds each; the offsets round to ~1e-16 of
+// the distance to the origin, far below the FP32 rounding of the vertex positions themselves).
 struct Ray {
-  double ox, oy, oz, dx, dy, dz;
-  double ax, ay, az, bx, by, bz;
+  double dx, dy, dz, ax, ay, az, bx, by, bz, od, oa, ob;
 };
 
 __device__ __forceinline__ Ray pixel_ray(const FrameDev& f, int i, int j) {
 #pragma clang fp contract(off)
   const double a = double(j) + 0.5, b = double(i) + 0.5;
   Ray r;
-  double dx, dy, dz;
+  double dx, dy, dz, ox, oy, oz;
   if (f.proj == 0) {
-    r.ox = f.ceye[0] + a * f.cright[0] + b * f.cdown[0];
-    r.oy = f.ceye[1] + a * f.cright[1] + b * f.cdown[1];
-    r.oz = f.ceye[2] + a * f.cright[2] + b * f.cdown[2];
+    ox = f.ceye[0] + a * f.cright[0] + b * f.cdown[0];
+    oy = f.ceye[1] + a * f.cright[1] + b * f.cdown[1];
+    oz = f.ceye[2] + a * f.cright[2] + b * f.cdown[2];
     dx = f.cdir[0];
     dy = f.cdir[1];
     dz = f.cdir[2];
   } else {
-    r.ox = f.ceye[0];
-    r.oy = f.ceye[1];
-    r.oz = f.ceye[2];
+    ox = f.ceye[0];
+    oy = f.ceye[1];
+    oz = f.ceye[2];
     const double aa = a - 0.5 * double(f.W), bb = b - 0.5 * double(f.H);
     dx = f.cdir[0] + aa * f.cright[0] + bb * f.cdown[0];
     dy = f.cdir[1] + aa * f.cright[1] + bb * f.cdown[1];
@@ -151,32 +149,32 @@ __device__ __forceinline__ Ray pixel_ray(const FrameDev& f, int i, int j) {
     r.bz = r.dx * r.ay - r.dy * r.ax;
   }
   // depth 0 at the middle of the depth range
-  r.ox = r.ox + f.t_mid * r.dx;
-  r.oy = r.oy + f.t_mid * r.dy;
-  r.oz = r.oz + f.t_mid * r.dz;
+  ox = ox + f.t_mid * r.dx;
+  oy = oy + f.t_mid * r.dy;
+  oz = oz + f.t_mid * r.dz;
+  r.od = -(r.dx * ox + r.dy * oy + r.dz * oz);
+  r.oa = -(r.ax * ox + r.ay * oy + r.az * oz);
+  r.ob = -(r.bx * ox + r.by * oy + r.bz * oz);
   return r;
 }
 
-// A vertex as seen from one ray: id, scalar, depth t = d.(P-o) (FP64) and its
+// A vertex as seen from one ray: scalar, depth t = d.(P-o) (FP64) and its
 // coordinates u = a.(P-o), v = b.(P-o) in the plane perpendicular to the ray,
 // computed in FP64 and rounded to FP32 (near the ray |u|, |v| are about a
 // cell's size, so the rounding is ~1e-7 of a cell, not of the distance to
 // the eye).
 struct VS {
-  int id;
   float s, u, v;
   double t;
 };
 
-__device__ __forceinline__ VS vstate(const Ray& r, int id, float4 p) {
-#pragma clang fp contract(off)
+__device__ __forceinline__ VS vstate(const Ray& r, float4 p) {
+  const double x = p.x, y = p.y, z = p.z;
   VS v;
-  v.id = id;
   v.s = p.w;
-  const double px = double(p.x) - r.ox, py = double(p.y) - r.oy, pz = double(p.z) - r.oz;
-  v.t = r.dx * px + r.dy * py + r.dz * pz;
-  v.u = float(r.ax * px + r.ay * py + r.az * pz);
-  v.v = float(r.bx * px + r.by * py + r.bz * pz);
+  v.t = fma(r.dx, x, fma(r.dy, y, fma(r.dz, z, r.od)));
+  v.u = float(fma(r.ax, x, fma(r.ay, y, fma(r.az, z, r.oa))));
+  v.v = float(fma(r.bx, x, fma(r.by, y, fma(r.bz, z, r.ob))));
   return v;
 }
 
@@ -186,60 +184,44 @@ __device__ __forceinline__ VS vstate(const Ray& r, int id, float4 p) {
 // of an edge give exactly opposite values (the products are the same two
 // roundings in either order), so every test that meets the edge sees one
 // value up to sign; an exact zero counts as positive in the orientation from
-// the lower vertex id to the higher.
+// the lower vertex id to the higher (the callers' part: zeros are rare).
 __device__ __forceinline__ float side(const VS& a, const VS& b) {
 #pragma clang fp contract(off)
-  const float p = a.u * b.v - a.v * b.u;
-  return p == 0.0f ? (a.id < b.id ? FLT_MIN : -FLT_MIN) : p;
+  return a.u * b.v - a.v * b.u;
 }
+__device__ __forceinline__ float zero_side(bool low_to_high) { return low_to_high ? FLT_MIN : -FLT_MIN; }
 
 // Crossing point of the ray with the face (A, B, C) whose oriented products
 // pAB, pBC, pCA are all positive: barycentric weights (pBC, pCA, pAB).  The
-// sums start at the vertex with the smallest id, so a walk that leaves its
-// subdomain (or the mesh) through a face and the entry test of the tet behind
-// it (which list the face's vertices in different rotations) get the same
-// depth bit for bit.
-// The depth is that vertex's FP64 depth plus the weighted depth differences
-// across the face (at most a cell's extent, so FP32 keeps them to ~1e-7 of a
-// cell, the precision of the weights themselves).
+// depth is A's FP64 depth plus the weighted depth differences across the face
+// (at most a cell's extent, so FP32 keeps them to ~1e-7 of a cell, the
+// precision of the weights themselves); the scalar likewise.
 __device__ __forceinline__ void face_point(const VS& A, const VS& B, const VS& C, float pAB, float pBC, float pCA,
                                            double& t, float& s) {
-#pragma clang fp contract(off)
-  float uA = fmaxf(pBC, 0.0f), uB = fmaxf(pCA, 0.0f), uC = fmaxf(pAB, 0.0f);
-  const bool bmin = B.id < A.id && B.id < C.id, cmin = C.id < A.id && C.id < B.id;
-  const float u0 = bmin ? uB : (cmin ? uC : uA), u1 = bmin ? uC : (cmin ? uA : uB), u2 = bmin ? uA : (cmin ? uB : uC);
-  const double t0 = bmin ? B.t : (cmin ? C.t : A.t), t1 = bmin ? C.t : (cmin ? A.t : B.t),
-               t2 = bmin ? A.t : (cmin ? B.t : C.t);
-  const float s0 = bmin ? B.s : (cmin ? C.s : A.s), s1 = bmin ? C.s : (cmin ? A.s : B.s),
-              s2 = bmin ? A.s : (cmin ? B.s : C.s);
-  float sum = u0 + u1 + u2;
-  if (!(sum > 0.0f)) {
-    t = t0;
-    s = s0;
-    return;
-  }
-  float inv = __builtin_amdgcn_rcpf(sum);  // 1 ulp; both passes alike
-  t = t0 + double((u1 * float(t1 - t0) + u2 * float(t2 - t0)) * inv);
-  s = (u0 * s0 + u1 * s1 + u2 * s2) * inv;
+  const float inv = __builtin_amdgcn_rcpf(fmaxf(pBC + pCA + pAB, FLT_MIN));  // 1 ulp; both passes alike
+  t = A.t + double(fmaf(pCA, float(B.t - A.t), pAB * float(C.t - A.t)) * inv);
+  s = fmaf(fmaf(pCA, B.s - A.s, pAB * (C.s - A.s)), inv, A.s);
 }
 
-// The same crossing with A as the base vertex: the depth and scalar a walk
-// hands from one tet to the next inside a subdomain, where only this walk
-// meets the face.  Where the walk leaves the subdomain (the neighbouring
-// subdomain's entry test meets the face too) face_point's ordering is used.
-__device__ __forceinline__ void face_point_a(const VS& A, const VS& B, const VS& C, float pAB, float pBC, float pCA,
-                                             double& t, float& s) {
-#pragma clang fp contract(off)
-  const float uA = fmaxf(pBC, 0.0f), uB = fmaxf(pCA, 0.0f), uC = fmaxf(pAB, 0.0f);
-  const float sum = uA + uB + uC;
-  if (!(sum > 0.0f)) {
-    t = A.t;
-    s = A.s;
-    return;
-  }
-  const float inv = __builtin_amdgcn_rcpf(sum);
-  t = A.t + double((uB * float(B.t - A.t) + uC * float(C.t - A.t)) * inv);
-  s = (uA * A.s + uB * B.s + uC * C.s) * inv;
+// a or b, field by field (value selects: no store through a selected address)
+__device__ __forceinline__ VS pick(bool c, const VS& a, const VS& b) {
+  VS r;
+  r.s = c ? a.s : b.s;
+  r.u = c ? a.u : b.u;
+  r.v = c ? a.v : b.v;
+  r.t = c ? a.t : b.t;
+  return r;
+}
+
+// face_point with the vertex `base` (0 A, 1 B, 2 C) first: the one with the
+// smallest id, so a walk that leaves its subdomain (or the mesh) through a
+// face and the entry test of the tet behind it (which list the face's vertices
+// in different rotations) get the same depth bit for bit.
+__device__ __forceinline__ void face_point_from(int base, const VS& A, const VS& B, const VS& C, float pAB, float pBC,
+                                                float pCA, double& t, float& s) {
+  const bool b1 = base == 1, b2 = base == 2;
+  face_point(pick(b1, B, pick(b2, C, A)), pick(b1, C, pick(b2, A, B)), pick(b1, A, pick(b2, B, C)),
+             b1 ? pBC : (b2 ? pCA : pAB), b1 ? pCA : (b2 ? pAB : pBC), b1 ? pAB : (b2 ? pBC : pCA), t, s);
 }
 
 // A boundary face staged in LDS, vertices in outward order of its tet.
@@ -249,28 +231,25 @@ struct FaceL {
   float4 p0, p1, p2;
 };
 
-// Does the ray enter the face's tet through it?  On success returns the
-// entry state: the face in inward order (A, B, C) with its positive
-// products, and the entry depth/scalar.
-struct Entry {
-  VS A, B, C;
-  float pAB, pBC, pCA, s;
-  double t;
-};
+// Which of the face's vertices 0, 1, 2 (outward order) in the slots A, B, C =
+// vertices 0, 2, 1 (inward order) has the smallest id.
+__device__ __forceinline__ int first_slot(int id0, int id1, int id2) {
+  return id0 < id1 && id0 < id2 ? 0 : (id2 < id1 ? 1 : 2);
+}
 
-__device__ __forceinline__ bool enter_face(const Ray& r, int id0, int id1, int id2, float4 p0, float4 p1,
-                                           float4 p2, Entry& e) {
-  VS a = vstate(r, id0, p0), b = vstate(r, id1, p1), c = vstate(r, id2, p2);
+// Does the ray enter the face's tet through it (vertices in outward order)?
+// On success also the entry depth.
+__device__ __forceinline__ bool enters(const Ray& r, int id0, int id1, int id2, float4 p0, float4 p1, float4 p2,
+                                       double& t) {
+  const VS a = vstate(r, p0), b = vstate(r, p1), c = vstate(r, p2);
   float sab = side(a, b), sbc = side(b, c), sca = side(c, a);
+  if (sab == 0.0f) sab = zero_side(id0 < id1);
+  if (sbc == 0.0f) sbc = zero_side(id1 < id2);
+  if (sca == 0.0f) sca = zero_side(id2 < id0);
   if (!(sab < 0.0f && sbc < 0.0f && sca < 0.0f)) return false;
   // inward order (a, c, b): pi(a->c) = -sca, pi(c->b) = -sbc, pi(b->a) = -sab
-  e.A = a;
-  e.B = c;
-  e.C = b;
-  e.pAB = -sca;
-  e.pBC = -sbc;
-  e.pCA = -sab;
-  face_point(e.A, e.B, e.C, e.pAB, e.pBC, e.pCA, e.t, e.s);
+  float s;
+  face_point_from(first_slot(id0, id1, id2), a, c, b, -sca, -sbc, -sab, t, s);
   return true;
 }
 
@@ -278,63 +257,71 @@ __device__ __forceinline__ bool enter_face(const Ray& r, int id0, int id1, int i
 // (a walk cut off by its step limit, an exit face chosen by the tie fallback, an entry list or buffer that
 // overflowed) go straight to the device counters instead, so they hold no register in the walk.
 struct LaneCount {
-  unsigned pieces, steps, entries, nonpd, tabled, tab_fallback, segments;
+  unsigned pieces, entries, nonpd, segments;
+  unsigned w_pieces, w_steps, w_tabled, w_fallback;  // counted for the whole wavefront at once
   unsigned long long* ctr;
   __device__ void rare(int which, unsigned n = 1u) {
     if (n) atomicAdd(ctr + which, (unsigned long long)n);
   }
 };
 
-// Cut the chord [t0, t1] (scalar s0 -> s1) at the lattice t_near + k*step and
-// hand each piece (mid depth, length, scalar at the mid point) to fn.  The cut
+// Cuts the chords of one ray at the sampling lattice t_near + k*step.  The
+// chords of a segment meet end to start, so only a chord's end is handed over
+// (to) and the next lattice point carries on from chord to chord.  The cut
 // points and mid depths are FP64 (depths are absolute positions along the
 // ray); lengths and scalars are FP32.
-template <class Fn>
-__device__ __forceinline__ void cut_chord(const FrameDev& f, double t0, double t1, float s0, float s1, Fn&& fn) {
-#pragma clang fp contract(off)
-  const double len = t1 - t0;
-  if (!(len > 0.0)) return;
-  const float slope = (s1 - s0) * __builtin_amdgcn_rcpf(float(len));
-  // the first lattice point after t0 (the rounded floor can fall one short)
-  double kf = floor((t0 - f.t_near) * f.inv_step) + 1.0;
-  if (!(f.t_near + kf * f.step > t0)) kf += 1.0;
-  double u = t0;
-  for (int guard = 0; u < t1 && guard < (1 << 22); ++guard) {
-    const double nxt = f.t_near + kf * f.step;
-    kf += 1.0;
-    const double v = fmin(nxt, t1);
-    const double tm = 0.5 * (u + v);
-    const float s = s0 + slope * float(tm - t0);
-    fn(tm, float(v - u), s);
+struct Cutter {
+  double u = 0.0, t1 = 0.0, nxt = 0.0;  // cut so far, chord end, the next lattice point
+  float s1 = 0.0f, slope = 0.0f;        // scalar at the chord's end and along it
+
+  __device__ __forceinline__ bool cutting() const { return u < t1; }
+  // a segment begins at depth t with scalar s
+  __device__ __forceinline__ void start(const FrameDev& f, double t, float s) {
+    u = t1 = t;
+    s1 = s;
+    nxt = fma(floor((t - f.t_near) * f.inv_step) + 1.0, f.step, f.t_near);
+    if (!(nxt > t)) nxt += f.step;  // the rounded floor can fall one short
+  }
+  // the next chord ends at depth t with scalar s
+  __device__ __forceinline__ void to(const FrameDev& f, double t, float s) {
+    const double len = t - t1;
+    slope = (s - s1) * __builtin_amdgcn_rcpf(float(len));
+    t1 = t;
+    s1 = s;
+    if (f.long_chords && !(len <= f.max_chord)) nxt = HUGE_VAL;  // never that many pieces: the chord is one
+  }
+  // the next piece of the chord: its mid depth from the eye (over the range's geometric mean), length and scalar
+  __device__ __forceinline__ void piece(const FrameDev& f, float& wt, float& len, float& s) {
+    const bool lat = nxt <= t1;
+    const double v = lat ? nxt : t1, sum = u + v;
+    wt = float(fma(sum, f.w_scale, f.w_off));
+    len = float(v - u);
+    s = fmaf(slope, float(fma(0.5, sum, -t1)), s1);
+    nxt = lat ? nxt + f.step : nxt;
     u = v;
   }
-}
+};
 
-// Transfer-function table coordinate of scalar s: entry i0 and fraction fr.
+// Transfer-function table coordinate of scalar s, clamped to the table: entry
+// i0 in [0, n_tf - 1] and fraction fr (0 at the last entry).
 __device__ __forceinline__ void tf_coord(const FrameDev& f, float s, int& i0, float& fr) {
-#pragma clang fp contract(off)
-  float u = (s - f.s_min) * f.tf_scale;
-  u = __builtin_amdgcn_fmed3f(u, 0.0f, float(f.n_tf - 1));  // clamp to [0, n_tf - 1] in one instruction
-  i0 = min(int(u), f.n_tf - 2);
-  fr = u - float(i0);
+  const float u = __builtin_amdgcn_fmed3f((s - f.s_min) * f.tf_scale, 0.0f, float(f.n_tf - 1));
+  i0 = int(u);
+  fr = __builtin_amdgcn_fractf(u);
 }
 
-// Optical depth of a piece (Alg. 2: absorbance capped) from the transfer
-// function's alpha at its scalar and its length, and its warped depth (log
-// depth rescaled to [-1, 1]) from its mid depth measured from the eye (wt =
-// tm + t_mid, rounded to FP32).
-__device__ __forceinline__ float piece_a(const FrameDev& f, float A, float len) {
-#pragma clang fp contract(off)
-  return __builtin_amdgcn_fmed3f(f.kappa * A * len, 0.0f, f.amax);  // min with the cap (the product is >= 0)
+// Optical depth of a piece (Alg. 2: absorbance capped) from kappa times the
+// transfer function's alpha at its scalar and its length, and its warped depth
+// (log depth rescaled to [-1, 1], clamped to the range) from its mid depth
+// measured from the eye over the geometric mean of the range's ends: the
+// logarithm is 0 in the middle of the range, so the hardware's relative error
+// (about an ulp, mostly of one sign) is one of z, with no larger number
+// subtracted from it.
+__device__ __forceinline__ float piece_a(const FrameDev& f, float kA, float len) {
+  return __builtin_amdgcn_fmed3f(kA * len, 0.0f, f.amax);  // min with the cap (the product is >= 0)
 }
-__device__ __forceinline__ float piece_z(const FrameDev& f, float wt) {
-#pragma clang fp contract(off)
-  const float z = (__log2f(wt) - f.lg_near) * f.warp_scale - 1.0f;
-  return fminf(fmaxf(z, -1.0f), 1.0f);
-}
-__device__ __forceinline__ void piece_az(const FrameDev& f, double tm, float len, float A, float& a, float& z) {
-  a = piece_a(f, A, len);
-  z = piece_z(f, float(tm + f.t_mid));
+__device__ __forceinline__ double piece_z(const FrameDev& f, float wt) {
+  return double(__builtin_amdgcn_fmed3f(__builtin_amdgcn_logf(wt), -f.lg_half, f.lg_half)) * f.z_scale;
 }
 
 // Opacity 1 - e^-a of a piece of optical depth a >= 0: below 0.35 the Taylor
@@ -357,151 +344,111 @@ __device__ __forceinline__ float lerp_nc(float a, float b, float fr) {
 }
 
 // Where a walk stands: the face (A, B, C) through which the ray entered the
-// current tet, with its positive side products, and the tet with the local
-// index of the vertex opposite that face.
-// a or b, field by field (value selects: no store through a selected address)
-__device__ __forceinline__ VS pick(bool c, const VS& a, const VS& b) {
-  VS r;
-  r.id = c ? a.id : b.id;
-  r.s = c ? a.s : b.s;
-  r.u = c ? a.u : b.u;
-  r.v = c ? a.v : b.v;
-  r.t = c ? a.t : b.t;
-  return r;
-}
-
+// current tet, with its positive side products; the code (tet << 2) | f of
+// that tet and the local index f of the vertex opposite the face; and how the
+// face's vertices A, B, C sit in the tet: slot i (A 0, B 1, C 2) holds the
+// vertex at position (i + rot) mod 3 of the inward order f ^ 1, f ^ 3, f ^ 2.
 struct WalkPos {
   VS A, B, C;
   float pAB, pBC, pCA;
-  int tet, apex;
+  int code;
+  int rot;
 };
 
-__device__ __forceinline__ WalkPos walk_start(const Entry& e, int tet, int apex) {
-  return WalkPos{e.A, e.B, e.C, e.pAB, e.pBC, e.pCA, tet, apex};
+// The walk record of a tet entered through its face f, 32 bytes: the vertex
+// opposite f, the codes of the tets behind the three other faces (in the
+// order of their opposite vertices' positions; -1 where that face lies on the
+// mesh hull or leads out of the subdomain) and packed bits about them
+// (k_walk_records).  All a step needs, in two loads that go out together.
+struct WalkRec {
+  float4 v;
+  int4 n;
+};
+__device__ __forceinline__ WalkRec walk_rec(const MeshDev& M, int code) {
+  const int4* p = M.wrec + 2 * size_t(unsigned(code));
+  WalkRec r;
+  r.v = *reinterpret_cast<const float4*>(p);
+  r.n = p[1];
+  return r;
 }
 
-// One step of the walk: the face through which the ray leaves the current
-// tet and the depth and scalar where it does (tout >= tin); the position moves
-// to the tet behind that face.  Returns false when that face lies on the mesh
-// hull or leads out of the subdomain (tet range [t_lo, t_hi)).
-__device__ __forceinline__ bool walk_step(const MeshDev& M, const Ray& r, WalkPos& w, double tin, int t_lo, int t_hi,
-                                          double& tout, float& sout, LaneCount& cnt) {
-  // ids, neighbours and the apex vertex come from one 128-byte record, so
-  // the three loads go out together (no vertex load waiting on the ids)
-  const int4* rec = M.wrec + 8 * size_t(w.tet);
-  const int4 tv = rec[0];
-  const int4 tn = rec[1];
-  const float4 dp = reinterpret_cast<const float4*>(rec)[2 + w.apex];
-  const int did = sel4m(tv, w.apex);
-  const VS D = vstate(r, did, dp);
-  const float qA = side(D, w.A), qB = side(D, w.B), qC = side(D, w.C);
+// One step of the walk through the tet of record `rec`: the depth and scalar
+// where the ray leaves it (tout >= tin); the position moves to the tet behind
+// (w.code < 0 when the exit face lies on the mesh hull or leads out of the
+// subdomain).  Returns whether the chord has any length.  The whole wavefront
+// takes the step: a lane that walks no more computes with a record it does not
+// use, and its code stays -1 (with the step under a condition the compiler
+// copies the whole position around it).  No vertex ids are needed: what they
+// decide (the sign of a zero product, the first vertex of a face that leaves
+// the subdomain, how the next tet numbers the face's vertices) is in the
+// record's bits.
+__device__ __forceinline__ bool walk_step(const Ray& r, WalkPos& w, const WalkRec& rec, double tin, double& tout,
+                                          float& sout, LaneCount& cnt) {
+  const VS D = vstate(r, rec.v);
+  const unsigned info = unsigned(rec.n.w);
+  float qA = side(D, w.A), qB = side(D, w.B), qC = side(D, w.C);
+  const bool alive = w.code >= 0;
+  if ((fminf(fminf(fabsf(qA), fabsf(qB)), fabsf(qC)) == 0.0f) & alive) {
+    const int p1 = w.rot >= 2 ? w.rot - 2 : w.rot + 1, p2 = w.rot >= 1 ? w.rot - 1 : 2;
+    if (qA == 0.0f) qA = zero_side((info >> (12 + w.rot)) & 1);
+    if (qB == 0.0f) qB = zero_side((info >> (12 + p1)) & 1);
+    if (qC == 0.0f) qC = zero_side((info >> (12 + p2)) & 1);
+  }
   // exit through the face opposite X where q(next of X) > 0 > q(previous of X)
-  int x;
-  if (qB > 0.0f && qC < 0.0f)
-    x = 0;
-  else if (qC > 0.0f && qA < 0.0f)
-    x = 1;
-  else if (qA > 0.0f && qB < 0.0f)
-    x = 2;
-  else {  // sign pattern no line can have (rounding near a vertex): least-violated face
-    float m0 = fminf(qB, -qC), m1 = fminf(qC, -qA), m2 = fminf(qA, -qB);
-    x = (m0 >= m1 && m0 >= m2) ? 0 : (m1 >= m2 ? 1 : 2);
+  const unsigned long long a = ballot(qA > 0.0f), b = ballot(qB > 0.0f), c = ballot(qC > 0.0f);
+  bool x0 = lane_of(b & ~c), x1 = lane_of(c & ~a), x2 = lane_of(a & ~b);
+  const bool none = alive & lane_of((a & b & c) | ~(a | b | c));
+  if (none) {  // sign pattern no line can have (rounding near a vertex): least-violated face
+    const float m0 = fminf(qB, -qC), m1 = fminf(qC, -qA), m2 = fminf(qA, -qB);
+    x0 = m0 >= m1 && m0 >= m2;
+    x1 = !x0 && m1 >= m2;
+    x2 = !x0 && !x1;
     cnt.rare(C_FALLBACK);
   }
-  const int xid = x == 0 ? w.A.id : (x == 1 ? w.B.id : w.C.id);
   // The exit face replaces X by D in place: (D, B, C), (A, D, C) and
   // (A, B, D) are rotations of the exit faces (B, C, D), (C, A, D) and
   // (A, B, D), so the cyclic order with positive products is kept.
-  const float nAB = x == 0 ? qB : (x == 1 ? -qA : w.pAB);
-  const float nBC = x == 0 ? w.pBC : (x == 1 ? qC : -qB);
-  const float nCA = x == 0 ? -qC : (x == 1 ? w.pCA : qA);
-  w.A = pick(x == 0, D, w.A);
-  w.B = pick(x == 1, D, w.B);
-  w.C = pick(x == 2, D, w.C);
-  w.pAB = nAB;
-  w.pBC = nBC;
-  w.pCA = nCA;
-  ++cnt.steps;
-  const int xl = tv.x == xid ? 0 : (tv.y == xid ? 1 : (tv.z == xid ? 2 : 3));
-  const int nb = sel4m(tn, xl);
-  const int t2 = nb >> 2;
-  const bool stays = nb >= 0 && t2 >= t_lo && t2 < t_hi;
-  if (stays)
-    face_point_a(w.A, w.B, w.C, w.pAB, w.pBC, w.pCA, tout, sout);
-  else
-    face_point(w.A, w.B, w.C, w.pAB, w.pBC, w.pCA, tout, sout);
-  if (!(tout >= tin)) tout = tin;
-  if (!stays) return false;
-  w.tet = t2;
-  w.apex = nb & 3;
-  return true;
+  w.pAB = x0 ? qB : (x1 ? -qA : w.pAB);
+  w.pBC = x1 ? qC : (x2 ? -qB : w.pBC);
+  w.pCA = x2 ? qA : (x0 ? -qC : w.pCA);
+  if (none) {  // weights never negative
+    w.pAB = fmaxf(w.pAB, 0.0f);
+    w.pBC = fmaxf(w.pBC, 0.0f);
+    w.pCA = fmaxf(w.pCA, 0.0f);
+    asm volatile("; rare: kept a branch");
+  }
+  w.A = pick(x0, D, w.A);
+  w.B = pick(x1, D, w.B);
+  w.C = pick(x2, D, w.C);
+  const int x = x1 ? 1 : (x2 ? 2 : 0);
+  unsigned y = unsigned(x + w.rot);  // position of X: its face's place in the record
+  y = min(y, y - 3u);
+  // the face's place in the record is 0, 1 or 2: bit 0 and bit 1 of y select
+  const int nb = bit_select(__builtin_amdgcn_sbfe(int(y), 1, 1),
+                            bit_select(__builtin_amdgcn_sbfe(int(y), 0, 1), rec.n.x, rec.n.y), rec.n.z);
+  face_point(w.A, w.B, w.C, w.pAB, w.pBC, w.pCA, tout, sout);
+  if (alive & (nb < 0)) {  // leaves the subdomain
+    unsigned base = unsigned(x) + ((info >> (6 + 2 * y)) & 3u);
+    base = min(base, base - 3u);
+    face_point_from(int(base), w.A, w.B, w.C, w.pAB, w.pBC, w.pCA, tout, sout);
+  }
+  unsigned rot = unsigned(w.rot) + ((info >> (2 * y)) & 3u);
+  w.rot = int(min(rot, rot - 3u));
+  w.code = alive ? nb : -1;
+  const bool forward = alive & (tout > tin);
+  tout = forward ? tout : tin;
+  return forward;
 }
 
-// Walk the ray from an entry through the tets of one subdomain (tet range
-// [t_lo, t_hi)) until it leaves the subdomain, handing every chord to sink.
-// `apex` is the local index of the vertex opposite the entry face.  (The loop
-// body repeats walk_step's, written out: the stage-one kernel keeps fewer
-// registers that way.)
-template <class Sink>
-__device__ void walk(const MeshDev& M, const FrameDev& f, const Ray& r, int tet, int apex, Entry e, int t_lo,
-                     int t_hi, Sink& sink, LaneCount& cnt) {
-  VS A = e.A, B = e.B, C = e.C;
-  float pAB = e.pAB, pBC = e.pBC, pCA = e.pCA, sin_ = e.s;
-  double tin = e.t;
-  for (int step = 0;; ++step) {
-    if (step >= f.max_steps) {
-      cnt.rare(C_STEPLIMIT);
-      return;
-    }
-    const int4* rec = M.wrec + 8 * size_t(tet);
-    const int4 tv = rec[0];
-    const int4 tn = rec[1];
-    const float4 dp = reinterpret_cast<const float4*>(rec)[2 + apex];
-    int did = sel4(tv, apex);
-    VS D = vstate(r, did, dp);
-    float qA = side(D, A), qB = side(D, B), qC = side(D, C);
-    int x;
-    if (qB > 0.0f && qC < 0.0f)
-      x = 0;
-    else if (qC > 0.0f && qA < 0.0f)
-      x = 1;
-    else if (qA > 0.0f && qB < 0.0f)
-      x = 2;
-    else {
-      float m0 = fminf(qB, -qC), m1 = fminf(qC, -qA), m2 = fminf(qA, -qB);
-      x = (m0 >= m1 && m0 >= m2) ? 0 : (m1 >= m2 ? 1 : 2);
-      cnt.rare(C_FALLBACK);
-    }
-    const int xid = x == 0 ? A.id : (x == 1 ? B.id : C.id);
-    const float nAB = x == 0 ? qB : (x == 1 ? -qA : pAB);
-    const float nBC = x == 0 ? pBC : (x == 1 ? qC : -qB);
-    const float nCA = x == 0 ? -qC : (x == 1 ? pCA : qA);
-    A = pick(x == 0, D, A);
-    B = pick(x == 1, D, B);
-    C = pick(x == 2, D, C);
-    pAB = nAB;
-    pBC = nBC;
-    pCA = nCA;
-    double tout;
-    float sout;
-    int xl = tv.x == xid ? 0 : (tv.y == xid ? 1 : (tv.z == xid ? 2 : 3));
-    int nb = sel4m(tn, xl);
-    int t2 = nb >> 2;
-    const bool stays = nb >= 0 && t2 >= t_lo && t2 < t_hi;
-    if (stays)
-      face_point_a(A, B, C, pAB, pBC, pCA, tout, sout);
-    else
-      face_point(A, B, C, pAB, pBC, pCA, tout, sout);
-    if (!(tout >= tin)) tout = tin;
-    ++cnt.steps;
-    sink.chord(tin, tout, sin_, sout);
-    if (!stays) return;
-    tet = t2;
-    apex = nb & 3;
-    tin = tout;
-    sin_ = sout;
-  }
-}
+// A queue of chords per lane in LDS (lane-minor: the 64 lanes hit distinct
+// banks): where each ends, depth and scalar.
+template <int SLOTS>
+struct ChordRing {
+  static_assert((SLOTS & (SLOTS - 1)) == 0, "the ring size is a power of two");
+  double t[SLOTS * WAVE];
+  float s[SLOTS * WAVE];
+};
+constexpr int CHORDS = 8;  // stage one's queue
 
 // Per-lane list of entries (depth, face code) in LDS, kept sorted by
 // (depth, code); lane-minor layout so the 64 lanes hit distinct banks.
@@ -525,9 +472,9 @@ __device__ __forceinline__ void stage_faces(const MeshDev& M, const int* rec, in
     int4 tv = M.tet[2 * t];
     FaceL F;
     F.code = code;
-    F.id0 = sel4(tv, kFaceOut[fc][0]);
-    F.id1 = sel4(tv, kFaceOut[fc][1]);
-    F.id2 = sel4(tv, kFaceOut[fc][2]);
+    F.id0 = sel4(tv, fc ^ 1);
+    F.id1 = sel4(tv, fc ^ 2);
+    F.id2 = sel4(tv, fc ^ 3);
     F.p0 = M.vert[F.id0];
     F.p1 = M.vert[F.id1];
     F.p2 = M.vert[F.id2];
@@ -560,9 +507,9 @@ __device__ int collect_entries(const MeshDev& M, const Ray& r, bool want, const 
     if (!want) continue;
     for (int k = 0; k < nc; ++k) {
       const FaceL& F = faces[k];
-      Entry e;
-      if (!enter_face(r, F.id0, F.id1, F.id2, F.p0, F.p1, F.p2, e)) continue;
-      const float et = float(e.t);  // sort key: the entry depth rounded to FP32
+      double t;
+      if (!enters(r, F.id0, F.id1, F.id2, F.p0, F.p1, F.p2, t)) continue;
+      const float et = float(t);  // sort key: the entry depth rounded to FP32
       if (!key_less(last_t, last_c, et, F.code)) continue;  // walked in an earlier round
       if (n == EMAX) {
         more = true;
@@ -583,24 +530,45 @@ __device__ int collect_entries(const MeshDev& M, const Ray& r, bool want, const 
   return n;
 }
 
-// Entry k of the list: the boundary face it crosses, as an entry state.
-__device__ __forceinline__ bool list_entry(const MeshDev& M, const Ray& r, EntryList& L, int k, Entry& e, int& t,
-                                           int& fc) {
-  const int code = L.Cd(k);
-  t = code >> 2;
-  fc = code & 3;
-  const int4 tv = M.tet[2 * t];
-  const int i0 = sel4(tv, kFaceOut[fc][0]), i1 = sel4(tv, kFaceOut[fc][1]), i2 = sel4(tv, kFaceOut[fc][2]);
-  return enter_face(r, i0, i1, i2, M.vert[i0], M.vert[i1], M.vert[i2], e);  // true: it was listed so
+// Starts a walk at an entry of the list, `code` = (tet << 2) | face: the state
+// at the boundary face (the ray enters there: it was listed so) and the entry
+// depth and scalar, the ones the entry test found.
+__device__ __forceinline__ void start_walk(const MeshDev& M, const Ray& r, int code, WalkPos& w, double& t, float& s) {
+  const int fc = code & 3;
+  const int4 tv = M.tet[2 * (code >> 2)];
+  const int i0 = sel4(tv, fc ^ 1), i1 = sel4(tv, fc ^ 2), i2 = sel4(tv, fc ^ 3);
+  w.A = vstate(r, M.vert[i0]);
+  w.C = vstate(r, M.vert[i1]);
+  w.B = vstate(r, M.vert[i2]);
+  w.pAB = side(w.A, w.B);
+  w.pBC = side(w.B, w.C);
+  w.pCA = side(w.C, w.A);
+  w.pAB = w.pAB == 0.0f ? FLT_MIN : w.pAB;
+  w.pBC = w.pBC == 0.0f ? FLT_MIN : w.pBC;
+  w.pCA = w.pCA == 0.0f ? FLT_MIN : w.pCA;
+  w.code = code;
+  w.rot = 0;
+  face_point_from(first_slot(i0, i1, i2), w.A, w.B, w.C, w.pAB, w.pBC, w.pCA, t, s);
 }
 
 // All entries of this lane's ray into one subdomain, walked in (depth, code)
 // order.  Handles more than E_MAX entries by repeated rounds that pick the
 // next E_MAX entries after the last one walked.  Must be called by the whole
 // wavefront.
+//
+// A walk step hands its chord to the lane's queue, and the pieces are cut and
+// summed in rounds of one piece per lane that run only while most lanes have
+// one (ROUND_LANES of 64): a tet's chord holds 1 to 6 pieces, and a loop over
+// one chord's pieces ran as long as the lane with the most, at 62 % of the
+// lanes on average.  The record of the next tet is asked for before the
+// rounds and used after them.  Bound by vector instructions issued (FP64
+// among them at the same rate).  Measured, m = 8, 2560^2 on 12.6M tets: 17.4 ms
+// with a loop per chord and 64-byte records, 12.0 ms now (56 lanes
+// the same); 1024^2 on 1.6M tets 1.72 -> 1.18 ms at m = 6.
+constexpr int ROUND_LANES = 48;
 template <class Sink>
 __device__ void walk_subdomain(const MeshDev& M, const FrameDev& f, const Ray& r, bool valid, const int* rec,
-                               int n_rec, const SlotDev& sl, FaceL* faces, EntryList& L, Sink& sink,
+                               int n_rec, FaceL* faces, EntryList& L, ChordRing<CHORDS>& ring, Sink& sink,
                                LaneCount& cnt) {
   float last_t = -FLT_MAX;
   int last_c = -1;
@@ -610,14 +578,60 @@ __device__ void walk_subdomain(const MeshDev& M, const FrameDev& f, const Ray& r
     if (!__any(want)) break;
     const int n = collect_entries<E_MAX>(M, r, want, rec, n_rec, faces, L, last_t, last_c, more);
     if (more) cnt.rare(C_OVERFLOW);
-    for (int k = 0; k < n; ++k) {
-      Entry e;
-      int t, fc;
-      if (!list_entry(M, r, L, k, e, t, fc)) continue;  // cannot happen
-      ++cnt.entries;
-      const unsigned before = sink.pieces;
-      walk(M, f, r, t, fc, e, sl.tet_begin, sl.tet_end, sink, cnt);
-      cnt.segments += sink.pieces > before ? 1u : 0u;  // a maximal ray interval inside the subdomain
+    wave_sync();  // the ring may share the staged faces' memory
+    int k = 0, steps = 0, head = 0, tail = 0;
+    bool fresh = false;  // the entry being walked has no chord of some length yet
+    WalkPos w = {};
+    w.code = -1;  // no walk in progress
+    double tin = 0.0;
+    Cutter cut;
+    while (true) {
+      const bool next = (w.code < 0) & (k < n) & (head == tail) & !cut.cutting();
+      if (ballot(next)) steps = 0;
+      fresh |= next;
+      if (next) {  // the next entry
+        start_walk(M, r, L.Cd(k), w, tin, cut.s1);
+        cut.start(f, tin, cut.s1);
+        ++cnt.entries;
+        ++k;
+      }
+      const WalkRec wr = walk_rec(M, max(w.code, 0));
+      const unsigned long long walks = ballot(w.code >= 0), live = walks | ballot(k < n);
+      while (true) {  // rounds of one piece per lane
+        const unsigned long long act = ballot(cut.cutting()) | ballot(head < tail);
+        if (!act || (live && __popcll(act) * 64 < ROUND_LANES * __popcll(act | live) &&
+                     !(walks & ballot(tail - head >= CHORDS))))
+          break;
+        if (!cut.cutting() & (head < tail)) {
+          const int slot = (head & (CHORDS - 1)) * WAVE + L.lane;
+          cut.to(f, ring.t[slot], ring.s[slot]);
+          ++head;
+        }
+        if (cut.cutting()) {
+          float wt, len, s;
+          cut.piece(f, wt, len, s);
+          sink.piece(wt, len, s);
+        }
+      }
+      if (!live) break;
+      const bool alive = w.code >= 0;
+      cnt.w_steps += __popcll(walks);
+      double tout;
+      float sout;
+      const bool forward = walk_step(r, w, wr, tin, tout, sout, cnt);
+      if (alive) {
+        const int slot = (tail & (CHORDS - 1)) * WAVE + L.lane;
+        ring.t[slot] = tout;
+        ring.s[slot] = sout;
+      }
+      tail += alive ? 1 : 0;
+      cnt.segments += forward & fresh ? 1u : 0u;  // a maximal ray interval inside the subdomain
+      fresh &= !forward;
+      tin = tout;
+      if (++steps >= f.max_steps) {  // (every walk has taken at least as many)
+        cnt.rare(C_STEPLIMIT, w.code >= 0 ? 1u : 0u);
+        w.code = -1;
+      }
     }
     if (n > 0) {
       last_t = L.T(n - 1);
@@ -637,12 +651,13 @@ __device__ __forceinline__ void flush_one(unsigned v, unsigned long long* slot) 
 }
 
 __device__ __forceinline__ void flush_counts(const LaneCount& c, unsigned long long* ctr) {
-  flush_one(c.pieces, ctr + C_PIECES);
-  flush_one(c.steps, ctr + C_STEPS);
+  const bool first = (threadIdx.x & (WAVE - 1)) == 0;
+  flush_one(c.pieces + (first ? c.w_pieces : 0u), ctr + C_PIECES);
+  flush_one(first ? c.w_steps : 0u, ctr + C_STEPS);
   flush_one(c.entries, ctr + C_ENTRIES);
   flush_one(c.nonpd, ctr + C_NONPD);
-  flush_one(c.tabled, ctr + C_TABLED);
-  flush_one(c.tab_fallback, ctr + C_TABFB);
+  flush_one(first ? c.w_tabled : 0u, ctr + C_TABLED);
+  flush_one(first ? c.w_fallback : 0u, ctr + C_TABFB);
   flush_one(c.segments, ctr + C_SEGMENTS);
 }
 
@@ -728,28 +743,31 @@ struct LaneStore {
 template <int M1, bool KEEP>
 struct MomentSink {
   const FrameDev* f;
-  const float* tfa;  // LDS alpha column of the table
+  const float2* tfa;  // LDS: kappa times the table's alpha column and its differences
   double b[M1];
   unsigned pieces;
   LaneStore st;      // st.keep false: pieces are not kept
   int lane;
-  __device__ void chord(double t0, double t1, float s0, float s1) {
-    cut_chord(*f, t0, t1, s0, s1, [&](double tm, float len, float s) {
-      int i0;
-      float fr, a, z;
-      tf_coord(*f, s, i0, fr);
-      float A = lerp_nc(tfa[i0], tfa[i0 + 1], fr);
-      piece_az(*f, tm, len, A, a, z);
-      double term = a;  // the powers in FP64 too: one conversion per piece, not one per moment
-      const double zd = z;
+  __device__ __forceinline__ void piece(float wt, float len, float s) {
+    int i0;
+    float fr;
+    tf_coord(*f, s, i0, fr);
+    const float2 e = tfa[i0];
+    const float a = piece_a(*f, fmaf(fr, e.y, e.x), len);
+    const double z = piece_z(*f, wt), ad = a;
+    b[0] += ad;
+    double zj = z;  // Alg. 2: moment j gains absorbance * depth^j
+    const double z2 = z * z;
+    double zk = z2;
 #pragma unroll
-      for (int j = 0; j < M1; ++j) {  // Alg. 2: moment j gains absorbance * depth^j
-        b[j] += term;
-        term *= zd;
-      }
-      if constexpr (KEEP) st.put(z, a, s, lane);
-      ++pieces;
-    });
+    for (int j = 1; j < M1; ++j) {
+      b[j] = fma(ad, zj, b[j]);
+      const double nx = zj * z2;  // z^(j+2): two chains, odd and even powers
+      zj = zk;
+      zk = nx;
+    }
+    if constexpr (KEEP) st.put(float(z), a, s, lane);
+    ++pieces;
   }
 };
 
@@ -767,12 +785,18 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(APC_WALK_W
                                                   PieceStore ps, unsigned long long* ctr, int* queue,
                                                   const int* __restrict__ pair_idx, const int* __restrict__ pair_list) {
   extern __shared__ float4 dyn_lds[];
-  float* tfa = reinterpret_cast<float*>(dyn_lds);  // [n_tf] alpha column
-  __shared__ FaceL faces[CHUNK];
+  float2* tfa = reinterpret_cast<float2*>(dyn_lds);  // [n_tf] kappa * alpha and its differences
+  __shared__ union {
+    FaceL faces[CHUNK];  // while entries are collected: the chord queues are empty then
+    ChordRing<CHORDS> ring;
+  } sh;
   __shared__ float ent_t[E_MAX * WAVE];
   __shared__ int ent_c[E_MAX * WAVE];
   const int lane = threadIdx.x;
-  for (int i = lane; i < f.n_tf; i += WAVE) tfa[i] = tf_rgba[4 * i + 3];
+  for (int i = lane; i < f.n_tf; i += WAVE) {
+    const float a0 = f.kappa * tf_rgba[4 * i + 3], a1 = f.kappa * tf_rgba[4 * min(i + 1, f.n_tf - 1) + 3];
+    tfa[i] = make_float2(a0, a1 - a0);
+  }
   __shared__ unsigned long long blk_base;
   __shared__ int blk_used;
   if (lane == 0) {
@@ -803,9 +827,9 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(APC_WALK_W
   LaneCount cnt = {};
   cnt.ctr = ctr;
   int covering = 0;  // subdomains with at least one piece on this ray
-  // the global sum's FP64 partials: in registers for m <= 6 (room within the register budget of 3
+  // the global sum's FP64 partials: in registers at m = 4 (room within the register budget of 3
   // wavefronts per SIMD), else in the per-pixel scratch gacc; the same additions either way
-  constexpr bool REG_ACC = M1 <= 7;
+  constexpr bool REG_ACC = M1 <= 5;
   double acc[REG_ACC ? M1 : 1];
   MomentSink<M1, KEEP> sink;  // one sink for all subdomains: its piece store runs across them
   sink.f = &f;
@@ -820,8 +844,7 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(APC_WALK_W
 #pragma unroll
     for (int j = 0; j < M1; ++j) sink.b[j] = 0.0;
     if (n_rec > 0 && offsets[bin] + n_rec <= bin_cap) {
-      const SlotDev sl = slots[k];
-      walk_subdomain(M, f, r, valid, records + offsets[bin], n_rec, sl, faces, L, sink, cnt);
+      walk_subdomain(M, f, r, valid, records + offsets[bin], n_rec, sh.faces, L, sh.ring, sink, cnt);
     } else if (n_rec > 0) {
       cnt.rare(C_OVERFLOW);  // binned beyond the record capacity (never on an eagerly sized workspace)
     }
@@ -830,7 +853,9 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(APC_WALK_W
       // the global sum in slot order, one FP64 partial per pixel: a subdomain without pieces adds an exact
       // zero, so only the others are read and written, and the first one needs no read
       if (valid && sink.pieces > 0) {
-        double* g = gacc + pix;
+        size_t at = pix;
+        asm volatile("" : "+v"(at));  // the addresses of the planes are formed here, not kept across the walk
+        double* g = gacc + at;
 #pragma unroll
         for (int j = 0; j < M1; ++j) {
           const double v = double(float(sink.b[j]));
@@ -848,14 +873,18 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(APC_WALK_W
         for (int j = 0; j < M1; ++j) o[j * WAVE] = float(sink.b[j]);
       }
     } else if (valid) {
-      float* o = out + size_t(k) * M1 * HW + pix;
+      size_t at = pix;
+      asm volatile("" : "+v"(at));
+      float* o = out + size_t(k) * M1 * HW + at;
 #pragma unroll
       for (int j = 0; j < M1; ++j) o[size_t(j) * HW] = float(sink.b[j]);
     }
     covering += sink.pieces > 0 ? 1 : 0;
   }
   if (gacc && valid) {
-    float* o = out + pix;
+    size_t at = pix;
+    asm volatile("" : "+v"(at));
+    float* o = out + at;
 #pragma unroll
     for (int j = 0; j < M1; ++j) {
       double t = 0.0;
@@ -863,7 +892,7 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(APC_WALK_W
         if constexpr (REG_ACC)
           t = acc[j];
         else
-          t = gacc[size_t(j) * HW + pix];
+          t = gacc[size_t(j) * HW + at];
       }
       o[size_t(j) * HW] = float(t);
     }
@@ -1111,8 +1140,8 @@ __global__ __launch_bounds__(WAVE * EVAL_WPB) __attribute__((amdgpu_waves_per_eu
       if constexpr (TABLES) {
         if (use_table) {
           closed = !bound.frac_before_tab(R(z), eta, zs, apcm::TablePtr<N, R>{tab_lds}, F);
-          ++cnt.tabled;
-          cnt.tab_fallback += closed ? 1u : 0u;
+          cnt.w_tabled += __popcll(ballot(true));
+          cnt.w_fallback += __popcll(ballot(closed));
         }
       }
       if (closed) F = bound.frac_before(R(z), eta);  // the one inlined copy of the closed forms
@@ -1121,7 +1150,7 @@ __global__ __launch_bounds__(WAVE * EVAL_WPB) __attribute__((amdgpu_waves_per_eu
       int i0;
       float fr;
       tf_coord(f, s, i0, fr);
-      const float4 t0 = tf[i0], t1 = tf[i0 + 1];
+      const float4 t0 = tf[i0], t1 = tf[min(i0 + 1, f.n_tf - 1)];
       const float w = T * opacity(a);
       a0 += w * lerp_nc(t0.x, t1.x, fr);
       a1 += w * lerp_nc(t0.y, t1.y, fr);
@@ -1153,110 +1182,66 @@ __global__ __launch_bounds__(WAVE * EVAL_WPB) __attribute__((amdgpu_waves_per_eu
 // arithmetic, and the evaluation's per-pixel state (inverse Cholesky factor,
 // zeros of the degree-n orthonormal polynomial, continuation of the roots) is
 // what limits how many wavefronts a SIMD holds.  Split this way neither
-// wavefront holds the other's registers (three workgroups of two per SIMD,
-// where one wavefront doing both fits two), and the evaluator's arithmetic
-// fills the issue slots the walker spends waiting on memory.  The pieces pass
-// through a ring of PQ slots per lane in LDS.  The two wavefronts meet at
-// phase boundaries (workgroup barriers): at each the walker publishes how many
-// pieces each lane has produced and the evaluator how many it has evaluated;
-// between two boundaries the evaluator takes only pieces published at the
-// earlier one and the walker writes only ring slots evaluated before it, so
-// they never touch the same slot.  Per lane the pieces are evaluated in walk
-// order, each with the roots the previous one left
-// (apcm::Bound::frac_before_cont, n >= 3).
-#ifndef APC_RES_EMAX
-#define APC_RES_EMAX 8
-#endif
-constexpr int RES_EMAX = APC_RES_EMAX;  // entries per ray held at once in the re-walk
-// walk steps a lane takes per iteration while its ring has room for another chord's pieces
-#ifndef APC_RES_BURST
-#define APC_RES_BURST 4
-#endif
-constexpr int RES_ROOM = 3;  // ring slots a walk step needs free (a chord of one tet rarely has more pieces)
-#ifndef APC_PAIR_QUEUE
-#define APC_PAIR_QUEUE 16
-#endif
-// evaluation rounds per phase at most (one piece per lane per round).  Measured on the large frame (m = 8):
-// 4 rounds 148 ms, 6 130, 7 126, 8 132, 12 156, 16 192: fewer rounds keep the walker waiting for room, more
-// keep it waiting at the boundary
-#ifndef APC_PAIR_ROUNDS
-#define APC_PAIR_ROUNDS 7
-#endif
-// the walker ends its phase once this many 64ths of its lanes that still walk cannot take a step
-#ifndef APC_PAIR_BLOCKED
-#define APC_PAIR_BLOCKED 16
-#endif
-// wavefronts per SIMD the kernel is compiled for (register budget 512 / n)
-#ifndef APC_PAIR_WAVES
-#define APC_PAIR_WAVES 3
-#endif
-constexpr int PQ = APC_PAIR_QUEUE;
-static_assert((PQ & (PQ - 1)) == 0, "the ring size is a power of two");
-
-struct PairLDS {
-  float q[3][PQ * WAVE];  // wt, len, s of ring slot j of lane l at j * WAVE + l (the 64 lanes hit distinct banks)
-  int tail[2][WAVE];      // pieces lane l has produced, published at the boundaries of each parity
-  int head[2][WAVE];      // pieces of lane l evaluated
-  int done[2];            // the walker has no more pieces
+// wavefront holds the other's registers, and the evaluator's arithmetic fills
+// the issue slots the walker spends waiting on memory.  The chords' ends pass
+// through a ring of PQ slots per lane in LDS, and the evaluator cuts them into
+// pieces as stage one does (handing over the pieces themselves cost the walker
+// a loop over each chord's pieces and the pair 16 bytes a piece).  The two wavefronts meet at phase boundaries
+// (workgroup barriers): at each the walker publishes how many chords each lane
+// has produced and the evaluator how many it has taken; between two boundaries
+// the evaluator takes only chords published at the earlier one and the walker
+// writes only ring slots taken before it, so they never touch the same slot.
+// Per lane the pieces are evaluated in walk order, each with the roots the
+// previous one left (apcm::Bound::frac_continued, n >= 3).  Bound by the
+// evaluator's vector instructions: it waits at 5 % of the boundaries' time, the
+// walker at 55 %, and two evaluators to a walker were slower (39 ms against 33
+// at the largest frame below), as were evaluators and walkers on swapped SIMDs.
+// Measured, m = 8, 2560^2 on 12.6M tets: 41.8 ms with pieces in the ring, 33.2 now.
+//
+// The pair's shape for n = N roots: wavefronts per SIMD the kernel is compiled for (register budget 512 / n),
+// slots of the ring (one bit each in half a word) and evaluation rounds (one piece per lane) per phase at most.
+// Four wavefronts per SIMD need 128 registers and 20 KB of LDS per workgroup: the bound's state fits for n <= 3
+// with a ring of 8, and a phase there takes about what half the ring holds.  At n = 4 the state does not fit
+// (spills in the loop: 83 ms), and a ring of 16 lets the walker run further ahead.  Measured, re-walk ms of the
+// 2560^2 frame of a 12.6M-tet mesh at m = 8: 3 wavefronts, ring 16: 33.2 with 12 rounds, 33.4 with 8; ring 8:
+// 34.1 with 5; of the 1024^2 frame of a 1.6M-tet mesh at m = 6 and m = 4: 4 wavefronts, ring 8, 5 rounds: 2.56
+// and 2.18, 3 wavefronts, ring 16, 8 rounds: 2.84 and 2.59.
+template <int N>
+struct PairShape {
+  static constexpr int WAVES = N >= 4 ? 3 : 4, PQ = N >= 4 ? 16 : 8, ROUNDS = N >= 4 ? 12 : 5;
 };
 
-// The walker's side: the chord being cut (bit for bit cut_chord's arithmetic,
-// resumable when the ring is full) and the ring position.  A piece goes into
-// the ring raw -- depth from the eye, length, scalar -- and the evaluator
-// forms its optical depth and warped depth (piece_a, piece_z, the arithmetic
-// of stage one): the walker's divergent cutting loop stays short.
-struct Producer {
-  PairLDS* sh;
-  int lane, parity;
-  int tail;   // pieces produced
-  int limit;  // ring slots free up to here (evaluated count at the last boundary + PQ)
-  unsigned pieces;
-  bool cutting;
-  double cu, ckf, ct0, ct1;
-  float cs0, cslope;
-  int cguard;
+template <int PQ>
+struct PairLDS {
+  static_assert(PQ <= 16, "one bit per ring slot in tail");
+  ChordRing<PQ> ring;
+  // the low PQ bits: which slots hold the start of a segment instead of a chord; above them the number of
+  // records lane l has produced (mod 2^(32 - PQ)), published at the boundaries of each parity
+  unsigned tail[2][WAVE];
+  unsigned head[2][WAVE];  // records lane l has taken
+  int done[2];             // the walker has no more
+};
 
-  __device__ __forceinline__ void start_cut(const FrameDev& f, double t0, double t1, float s0, float s1) {
-#pragma clang fp contract(off)
-    const double len_c = t1 - t0;
-    cutting = len_c > 0.0;
-    if (!cutting) return;
-    cslope = (s1 - s0) * __builtin_amdgcn_rcpf(float(len_c));  // as cut_chord
-    ckf = floor((t0 - f.t_near) * f.inv_step) + 1.0;
-    if (!(f.t_near + ckf * f.step > t0)) ckf += 1.0;
-    cu = t0;
-    ct0 = t0;
-    ct1 = t1;
-    cs0 = s0;
-    cguard = 0;
+// The walker's side of the ring.
+template <int PQ>
+struct Producer {
+  PairLDS<PQ>* sh;
+  int lane, parity;
+  unsigned tail;    // records produced
+  unsigned limit;   // slots free up to here (taken count at the last boundary + PQ)
+  unsigned starts;  // bit per slot
+
+  __device__ __forceinline__ bool full() const { return tail == limit; }
+  __device__ __forceinline__ void put(double t, float s, unsigned start) {
+    const unsigned j = tail & (PQ - 1), slot = j * WAVE + lane;
+    sh->ring.t[slot] = t;
+    sh->ring.s[slot] = s;
+    starts = (starts & ~(1u << j)) | (start << j);
+    ++tail;
   }
-  // ring the pieces of the chord being cut until it ends or the ring is full
-  __device__ __forceinline__ void cut_more(const FrameDev& f) {
-#pragma clang fp contract(off)
-    while (cutting && tail < limit) {
-      if (!(cu < ct1) || cguard >= (1 << 22)) {
-        cutting = false;
-        break;
-      }
-      ++cguard;
-      const double nxt = f.t_near + ckf * f.step;
-      ckf += 1.0;
-      const double v = fmin(nxt, ct1);
-      const double tm = 0.5 * (cu + v);
-      const float s = cs0 + cslope * float(tm - ct0);
-      const int slot = (tail & (PQ - 1)) * WAVE + lane;
-      sh->q[0][slot] = float(tm + f.t_mid);
-      sh->q[1][slot] = float(v - cu);
-      sh->q[2][slot] = s;
-      ++tail;
-      ++pieces;
-      cu = v;
-    }
-  }
-  __device__ __forceinline__ bool can_step() const { return tail <= limit - RES_ROOM; }
-  // phase boundary (the whole walker wavefront): publish, meet the evaluator, learn what it evaluated
+  // phase boundary (the whole walker wavefront): publish, meet the evaluator, learn what it has taken
   __device__ __forceinline__ void boundary(bool finished) {
-    sh->tail[parity][lane] = tail;
+    sh->tail[parity][lane] = (tail << PQ) | starts;
     if (lane == 0) sh->done[parity] = finished ? 1 : 0;
     __syncthreads();
     limit = sh->head[parity][lane] + PQ;
@@ -1265,76 +1250,57 @@ struct Producer {
 };
 
 // All entries of this lane's ray into one subdomain, walked in (depth, code)
-// order as in walk_subdomain (same pieces, same order), one entry start, the
-// rest of a chord or a few walk steps per lane per iteration of a loop the
-// whole walker wavefront runs; a lane whose ring has no room waits, and the
-// wavefront ends its phase when enough of its lanes wait.
+// order as in walk_subdomain (same chords, same order).  The wavefront steps
+// together; when a lane's ring is full it ends its phase.
+template <int PQ>
 __device__ void walk_subdomain_paired(const MeshDev& M, const FrameDev& f, const Ray& r, bool valid, const int* rec,
-                                      int n_rec, const SlotDev& sl, FaceL* faces, EntryList& L, Producer& q,
-                                      LaneCount& cnt) {
+                                      int n_rec, FaceL* faces, EntryList& L, Producer<PQ>& q, LaneCount& cnt) {
   float last_t = -FLT_MAX;
   int last_c = -1;
   bool more = true;
   while (true) {
     const bool want = valid && more;
     if (!__any(want)) break;
-    const int n = collect_entries<RES_EMAX>(M, r, want, rec, n_rec, faces, L, last_t, last_c, more);
+    const int n = collect_entries<E_MAX>(M, r, want, rec, n_rec, faces, L, last_t, last_c, more);
     if (more) cnt.rare(C_OVERFLOW);
     int k = 0, steps = 0;
-    bool walking = false, open = false;  // a walk in progress; an entry whose segment is still counted
-    unsigned seg_start = 0;
-    WalkPos w;
+    bool fresh = false;  // the entry being walked has no chord of some length yet
+    WalkPos w = {};
+    w.code = -1;  // no walk in progress
     double tin = 0.0;
-    float sin_ = 0.0f;
     while (true) {
-      const bool busy = q.cutting || walking || k < n;
-      const unsigned long long act = __ballot(busy);
-      if (!act) break;
-      if (!q.cutting && !walking && k < n) {  // the next entry
-        Entry e;
-        int t, fc;
-        if (list_entry(M, r, L, k, e, t, fc)) {
-          ++cnt.entries;
-          w = walk_start(e, t, fc);
-          tin = e.t;
-          sin_ = e.s;
-          walking = true;
-          steps = 0;
-          open = true;
-          seg_start = q.pieces;
-        }
+      const unsigned long long todo = ballot(w.code >= 0) | ballot(k < n);
+      if (!todo) break;
+      if (todo & ballot(q.full())) {
+        q.boundary(false);
+        continue;
+      }
+      const bool next = (w.code < 0) & (k < n);
+      if (ballot(next)) steps = 0;
+      fresh |= next;
+      if (next) {  // the next entry
+        float s;
+        start_walk(M, r, L.Cd(k), w, tin, s);
+        q.put(tin, s, 1);
+        ++cnt.entries;
         ++k;
       }
-      if (q.cutting) q.cut_more(f);  // the rest of a chord that did not fit the ring
-      for (int burst = 0; burst < APC_RES_BURST; ++burst) {  // a uniform loop: lanes that stop just idle
-        const bool act = !q.cutting && walking && q.can_step();
-        if (!__any(act)) break;
-        if (act) {
-          if (steps >= f.max_steps) {
-            cnt.rare(C_STEPLIMIT);
-            walking = false;
-          } else {
-            double tout;
-            float sout;
-            walking = walk_step(M, r, w, tin, sl.tet_begin, sl.tet_end, tout, sout, cnt);
-            ++steps;
-            q.start_cut(f, tin, tout, sin_, sout);
-            q.cut_more(f);
-            tin = tout;
-            sin_ = sout;
-          }
-        }
+      const WalkRec wr = walk_rec(M, max(w.code, 0));
+      const unsigned long long walks = ballot(w.code >= 0);
+      while (walks & ballot(q.full())) q.boundary(false);
+      const bool alive = w.code >= 0;
+      cnt.w_steps += __popcll(walks);
+      double tout;
+      float sout;
+      const bool forward = walk_step(r, w, wr, tin, tout, sout, cnt);
+      if (alive) q.put(tout, sout, 0);
+      cnt.segments += forward & fresh ? 1u : 0u;  // a maximal ray interval inside the subdomain
+      fresh &= !forward;
+      tin = tout;
+      if (++steps >= f.max_steps) {  // (every walk has taken at least as many)
+        cnt.rare(C_STEPLIMIT, w.code >= 0 ? 1u : 0u);
+        w.code = -1;
       }
-      if (open && !walking && !q.cutting) {  // a maximal ray interval inside the subdomain ended
-        cnt.segments += q.pieces > seg_start ? 1u : 0u;
-        open = false;
-      }
-      // lanes that still have work here but no room to go on
-      const bool stuck = (q.cutting || walking || k < n) && !(q.cutting ? q.tail < q.limit : q.can_step());
-      const unsigned long long blocked = __ballot(stuck);
-      const unsigned long long still = __ballot(q.cutting || walking || k < n);
-      if (blocked && (blocked == still || __popcll(blocked) * 64 >= APC_PAIR_BLOCKED * __popcll(still)))
-        q.boundary(false);
     }
     if (n > 0) {
       last_t = L.T(n - 1);
@@ -1344,20 +1310,24 @@ __device__ void walk_subdomain_paired(const MeshDev& M, const FrameDev& f, const
 }
 
 template <int N, class R, bool QUEUE, bool PAIRS>
-__global__ __launch_bounds__(2 * WAVE) __attribute__((amdgpu_waves_per_eu(APC_PAIR_WAVES, 8))) void k_resolve(
+__global__ __launch_bounds__(2 * WAVE) __attribute__((amdgpu_waves_per_eu(PairShape<N>::WAVES, 8))) void k_resolve(
     MeshDev M, FrameDev f, const SlotDev* __restrict__ slots, const int* __restrict__ offsets,
     const int* __restrict__ counts, const int* __restrict__ records, long long bin_cap,
     const float* __restrict__ tf_rgba, const void* __restrict__ moments, BoundParams bp, float* __restrict__ rgba,
     unsigned long long* ctr, int* queue, const int* __restrict__ pair_list, float* __restrict__ part) {
   extern __shared__ float4 dyn_lds[];
-  float4* tf = dyn_lds;  // [n_tf] RGBA
+  float4* tf = dyn_lds;  // [n_tf + 1] RGB and kappa * alpha
   __shared__ FaceL faces[CHUNK];
-  __shared__ float ent_t[RES_EMAX * WAVE];
-  __shared__ int ent_c[RES_EMAX * WAVE];
-  __shared__ PairLDS sh;
+  __shared__ float ent_t[E_MAX * WAVE];
+  __shared__ int ent_c[E_MAX * WAVE];
+  constexpr int PQ = PairShape<N>::PQ;
+  __shared__ PairLDS<PQ> sh;
+  __shared__ R zs_lds[N >= 3 ? N * WAVE : 1];  // per pixel, the zeros of the degree-N orthonormal polynomial
   __shared__ int next_tile;
-  for (int i = threadIdx.x; i < f.n_tf; i += 2 * WAVE)
-    tf[i] = make_float4(tf_rgba[4 * i], tf_rgba[4 * i + 1], tf_rgba[4 * i + 2], tf_rgba[4 * i + 3]);
+  for (int i = threadIdx.x; i <= f.n_tf; i += 2 * WAVE) {  // (the last entry twice: the end of an interpolation)
+    const float* e = tf_rgba + 4 * min(i, f.n_tf - 1);
+    tf[i] = make_float4(e[0], e[1], e[2], f.kappa * e[3]);
+  }
   // PAIRS (a launch over pair_list): this workgroup walks the one (tile, subdomain) pair `pair` and writes
   // its colour sums, unfinalised, to part[pair]; else every subdomain of its tile, into the image
   int pair = 0, k_first = 0, k_end = f.n_slots;
@@ -1381,31 +1351,30 @@ __global__ __launch_bounds__(2 * WAVE) __attribute__((amdgpu_waves_per_eu(APC_PA
   cnt.ctr = ctr;
   if (walker) {
     const Ray r = pixel_ray(f, valid ? py : 0, valid ? px : 0);
-    Producer q;
+    Producer<PQ> q;
     q.sh = &sh;
     q.lane = lane;
     q.parity = 0;
-    q.tail = 0;
+    q.tail = 0u;
     q.limit = PQ;
-    q.pieces = 0u;
-    q.cutting = false;
+    q.starts = 0u;
     EntryList L{ent_t, ent_c, lane};
     for (int k = k_first; k < k_end; ++k) {
       const int bin = tile * f.n_slots + k;
       const int n_rec = counts[bin];
       if (n_rec > 0 && offsets[bin] + n_rec <= bin_cap)
-        walk_subdomain_paired(M, f, r, valid, records + offsets[bin], n_rec, slots[k], faces, L, q, cnt);
+        walk_subdomain_paired(M, f, r, valid, records + offsets[bin], n_rec, faces, L, q, cnt);
       else if (n_rec > 0)
         cnt.rare(C_OVERFLOW);  // binned beyond the record capacity (never on an eagerly sized workspace)
     }
     q.boundary(true);
-    cnt.pieces += q.pieces;
   } else {
     const size_t HW = size_t(f.W) * f.H, pix = size_t(py) * f.W + px;
-    // per-pixel part of Alg. 3, once per pixel instead of once per sample; the bound, its zeros and the
-    // continuation are separate locals (a structure holding a run-time indexed array would live in scratch)
+    // per-pixel part of Alg. 3, once per pixel instead of once per sample; the bound and the continuation are
+    // separate locals (a structure holding a run-time indexed array would live in scratch), the zeros live in
+    // LDS (8 registers less across the loop)
     apcm::Bound<N, R> bound;
-    apcm::RegArray<N, R> zs;
+    const apcm::StridedStore<N, R, WAVE> zs{zs_lds + lane};
     typename apcm::Bound<N, R>::Cont cont;
     cont.k = -1;
 #pragma unroll
@@ -1417,59 +1386,107 @@ __global__ __launch_bounds__(2 * WAVE) __attribute__((amdgpu_waves_per_eu(APC_PA
 #pragma unroll
       for (int j = 0; j < 2 * N; ++j) bias[j] = R(bp.bias[j]);
       cnt.nonpd += bound.setup(b, R(bp.alpha), bias, zsr);
-#pragma unroll
-      for (int i = 0; i < N; ++i) zs.v[i] = zsr[i];
       // no zeros found (never expected for a positive definite factor): no shortcut, every sample solves
       if (bound.mode == 2 && !(zsr[0] < zsr[N - 1])) {
-        bound.xlo = -R(HUGE_VAL);
-        bound.xhi = R(HUGE_VAL);
+        bound.xlo = zsr[0] = -R(HUGE_VAL);
+        bound.xhi = zsr[N - 1] = R(HUGE_VAL);
+      }
+      if constexpr (N >= 3) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) zs[i] = zsr[i];
       }
     }
     const R eta = R(bp.eta);
     float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
     unsigned solved = 0u, closed_used = 0u;  // samples needing roots; of those, by the closed forms
-    int head = 0, avail = 0, parity = 0;
-    auto eval_one = [&]() {  // Alg. 1 second loop with Alg. 3's bound, for the piece at `head`
-      const int slot = (head & (PQ - 1)) * WAVE + lane;
-      const float wt = sh.q[0][slot], len = sh.q[1][slot], s = sh.q[2][slot];
-      ++head;
-      if (bound.mode == 0) return;  // no absorbance on the ray: every piece has a = 0
-      int i0;
-      float fr;
-      tf_coord(f, s, i0, fr);
-      const float4 c0 = tf[i0], c1 = tf[i0 + 1];
-      const float a = piece_a(f, lerp_nc(c0.w, c1.w, fr), len), z = piece_z(f, wt);  // as stage one
-      R F;
-      if constexpr (N >= 3) {
-        int how;
-        F = bound.frac_before_cont(R(z), eta, zs, cont, how);
-        solved += how != 0 ? 1u : 0u;
-        closed_used += how == 2 ? 1u : 0u;
-      } else {
-        F = bound.frac_before(R(z), eta);
-      }
-      float T = __expf(-float(bound.b0 * F));
-      T = fminf(fmaxf(T, 0.0f), 1.0f);
-      const float w = T * opacity(a);
-      a0 += w * lerp_nc(c0.x, c1.x, fr);
-      a1 += w * lerp_nc(c0.y, c1.y, fr);
-      a2 += w * lerp_nc(c0.z, c1.z, fr);
-      a3 += w;
+    const R exponent = bound.b0 * R(-1.4426950408889634074);
+    unsigned head = 0u, ready = 0u, starts = 0u;  // records taken; records to take; which of them are starts
+    int parity = 0, n = 0;
+    bool fin = false;
+    Cutter cut;
+    double next_t = 0.0;  // the record at `head`, read ahead (the one before it while none is ready)
+    float next_s = 0.0f;
+    auto fetch = [&]() {
+      const unsigned slot = ((ready > 0u ? head : head - 1u) & (PQ - 1)) * WAVE + lane;
+      next_t = sh.ring.t[slot];
+      next_s = sh.ring.s[slot];
     };
-    while (true) {  // one phase per iteration, as many as the walker has
-      for (int round = 0; round < APC_PAIR_ROUNDS && __any(head < avail); ++round)
-        if (head < avail) eval_one();
+    // Alg. 1 second loop with Alg. 3's bound, a round of one piece per lane at a time (the next chord where the
+    // last is used up), in phases of at most PairShape<N>::ROUNDS.  A lane whose bound did not settle leaves the loop
+    // with its piece, and the closed forms, out of line, are called outside it (a call inside would cost the
+    // loop half its registers).
+    while (true) {
+      R z = R(0);
+      float a = 0.0f, fr = 0.0f;
+      int i0 = 0;
+      auto add = [&](R F, bool now) {  // the piece's colour, weighted
+        const float T = fminf(__builtin_amdgcn_exp2f(float(exponent * F)), 1.0f);
+        const float w = now ? T * opacity(a) : 0.0f;
+        asm volatile("" : "+v"(i0));  // the colours are read here, not held in registers across the bound
+        const float4 c0 = tf[i0], c1 = tf[i0 + 1];
+        a0 = fmaf(w, fmaf(fr, c1.x - c0.x, c0.x), a0);
+        a1 = fmaf(w, fmaf(fr, c1.y - c0.y, c0.y), a1);
+        a2 = fmaf(w, fmaf(fr, c1.z - c0.z, c0.z), a2);
+        a3 += w;
+      };
+      bool unsettled = false;
+      while ((ballot(cut.cutting()) | ballot(ready > 0u)) && (fin || n < PairShape<N>::ROUNDS)) {
+        ++n;
+        if (!cut.cutting() & (ready > 0u)) {
+          if ((starts >> (head & (PQ - 1))) & 1)
+            cut.start(f, next_t, next_s);
+          else
+            cut.to(f, next_t, next_s);
+          --ready;
+          head += 1u;
+        }
+        fetch();
+        const unsigned long long has = ballot(cut.cutting());
+        cnt.w_pieces += __popcll(has);
+        if (cut.cutting()) {
+          float wt, len, s;
+          cut.piece(f, wt, len, s);
+          if (bound.mode != 0) {  // (no absorbance on the ray: every piece has a = 0)
+            tf_coord(f, s, i0, fr);
+            const float ka0 = tf[i0].w, ka1 = tf[i0 + 1].w;
+            z = R(piece_z(f, wt));
+            R F;
+            if constexpr (N >= 3) {
+              int how;
+              unsettled = !bound.frac_continued(z, eta, zs, cont, F, how);
+              solved += how != 0 ? 1u : 0u;
+              closed_used += how == 2 ? 1u : 0u;
+            } else {
+              F = bound.frac_before(z, eta);
+            }
+            a = piece_a(f, fmaf(fr, ka1 - ka0, ka0), len);  // as stage one
+            add(F, !unsettled);
+          }
+        }
+        if constexpr (N >= 3) {
+          if (ballot(unsettled)) break;
+        }
+      }
+      if constexpr (N >= 3) {
+        if (ballot(unsettled)) {
+          if (unsettled) add(bound.frac_closed(z, eta, zs, cont), true);
+          continue;
+        }
+      }
+      if (fin) break;
       sh.head[parity][lane] = head;
       __syncthreads();
-      avail = sh.tail[parity][lane];
-      const bool fin = sh.done[parity] != 0;
+      starts = sh.tail[parity][lane];
+      ready = ((starts >> PQ) - head) & (~0u >> PQ);
+      fin = sh.done[parity] != 0;
       parity ^= 1;
-      if (fin) break;
+      n = 0;
+      fetch();
     }
-    while (__any(head < avail))
-      if (head < avail) eval_one();
-    cnt.tabled += solved;
-    cnt.tab_fallback += closed_used;
+    solved = wave_sum(solved);
+    closed_used = wave_sum(closed_used);
+    cnt.w_tabled += solved;
+    cnt.w_fallback += closed_used;
     if constexpr (PAIRS) {  // [pairs][4][64], every lane
       float* o = part + size_t(pair) * 4 * WAVE + lane;
       o[0] = a0;
@@ -1491,20 +1508,55 @@ __global__ __launch_bounds__(2 * WAVE) __attribute__((amdgpu_waves_per_eu(APC_PA
   }  // tiles
 }
 
-// walk records: [ids][neighbours][v0][v1][v2][v3], 8 x 16 bytes per tet
+// Walk records: tet t entered through its face f has 32 bytes at wrec[2 * ((t << 2) | f)] -- vertex f, then for
+// the exits at positions 0, 1, 2 (the faces opposite the local vertices f ^ 1, f ^ 3, f ^ 2) the code of the tet
+// behind (-1 on the hull or where it belongs to another subdomain), then a word of bits about exit p:
+//   2p..2p+1   what to add to the walk's `rot` (mod 3): with k = local index ^ exit face here and there, the next
+//              tet numbers the face's vertices by a reflection of {1, 2, 3}; it fixes one k, at position q of the
+//              order (1, 3, 2), and rot grows by p - q
+//   6+2p..     which vertex of the exit face has the smallest id: 0 vertex f, 1 / 2 the one at position p + 1 / p + 2
+//   12+p       whether vertex f has a smaller id than the vertex at position p
+// sub_begin [n_sub + 1]: first tet of each subdomain.
 __global__ void k_walk_records(const int4* __restrict__ tet, const float4* __restrict__ vert, int64_t n,
-                               int4* __restrict__ wrec) {
-  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  const int4 tv = tet[2 * t];
-  int4* o = wrec + 8 * t;
-  o[0] = tv;
-  o[1] = tet[2 * t + 1];
-  float4* ov = reinterpret_cast<float4*>(o + 2);
-  ov[0] = vert[tv.x];
-  ov[1] = vert[tv.y];
-  ov[2] = vert[tv.z];
-  ov[3] = vert[tv.w];
+                               const int* __restrict__ sub_begin, int n_sub, int4* __restrict__ wrec) {
+  const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (g >= 4 * n) return;
+  const int t = int(g >> 2), fc = int(g & 3);
+  int lo = 0, hi = n_sub;  // the subdomain of t: sub_begin[lo] <= t < sub_begin[lo + 1]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (sub_begin[mid] <= t)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  const int t_lo = sub_begin[lo], t_hi = sub_begin[lo + 1];
+  const int4 tv = tet[2 * int64_t(t)], tn = tet[2 * int64_t(t) + 1];
+  const int id = sel4(tv, fc);
+  unsigned info = 0;
+  int out[3];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    const int c = p == 0 ? 1 : (p == 1 ? 3 : 2), c1 = p == 0 ? 3 : (p == 1 ? 2 : 1), c2 = p == 0 ? 2 : (p == 1 ? 1 : 3);
+    const int ex = fc ^ c;
+    const int i1 = sel4(tv, fc ^ c1), i2 = sel4(tv, fc ^ c2);
+    info |= (id < i1 && id < i2 ? 0u : (i1 < i2 ? 1u : 2u)) << (6 + 2 * p);
+    info |= (id < sel4(tv, ex) ? 1u : 0u) << (12 + p);
+    const int nb = sel4(tn, ex), t2 = nb >> 2;
+    out[p] = nb >= 0 && t2 >= t_lo && t2 < t_hi ? nb : -1;
+    if (out[p] < 0) continue;
+    const int4 w = tet[2 * int64_t(t2)];
+    int q = 0;
+    for (int k = 1; k < 4; ++k) {
+      const int v = sel4(tv, ex ^ k);
+      const int l2 = w.x == v ? 0 : (w.y == v ? 1 : (w.z == v ? 2 : 3));
+      if ((l2 ^ (nb & 3)) == k) q = k == 1 ? 0 : (k == 3 ? 1 : 2);
+    }
+    info |= unsigned((p - q + 3) % 3) << (2 * p);
+  }
+  float4* v = reinterpret_cast<float4*>(wrec + 2 * g);
+  *v = vert[id];
+  wrec[2 * g + 1] = make_int4(out[0], out[1], out[2], int(info));
 }
 
 // ------------------------------------------------------------------ binning
@@ -1538,9 +1590,9 @@ __global__ void k_bin(MeshDev M, FrameDev f, const SlotDev* __restrict__ slots,
   const int code = bface[i];
   const int t = code >> 2, fc = code & 3;
   const int4 tv = M.tet[2 * t];
-  const float4 a = M.vert[sel4(tv, kFaceOut[fc][0])];
-  const float4 b = M.vert[sel4(tv, kFaceOut[fc][1])];
-  const float4 c = M.vert[sel4(tv, kFaceOut[fc][2])];
+  const float4 a = M.vert[sel4(tv, fc ^ 1)];
+  const float4 b = M.vert[sel4(tv, fc ^ 2)];
+  const float4 c = M.vert[sel4(tv, fc ^ 3)];
   // conservative back-face cull: drop faces every ray crosses outwards
   {
     float ux = b.x - a.x, uy = b.y - a.y, uz = b.z - a.z, vx = c.x - a.x, vy = c.y - a.y, vz = c.z - a.z;
@@ -1897,7 +1949,7 @@ hipError_t launch_moments(int mm, const MeshDev& m, const FrameDev& f, const Slo
                           double* gacc, int* pcount, int* segs, const PieceStore& store,
                           unsigned long long* counters, int* queue, const int* pair_idx, const int* pair_list,
                           int64_t n_pairs, hipStream_t s) {
-  const size_t lds = size_t(f.n_tf) * sizeof(float);
+  const size_t lds = size_t(f.n_tf) * sizeof(float2);
   const dim3 block(WAVE);
   if (pair_list) {
     queue = nullptr;  // a workgroup per pair
@@ -1959,7 +2011,7 @@ hipError_t launch_resolve(int mm, const MeshDev& m, const FrameDev& f, const Slo
                           const int* counts, const int* records, long long bin_cap, const float* tf_rgba,
                           const void* moments, const BoundParams& bp, float* rgba, unsigned long long* counters,
                           int* queue, const int* pair_list, float* part, int64_t n_pairs, hipStream_t s) {
-  const size_t lds = size_t(f.n_tf) * sizeof(float4);
+  const size_t lds = size_t(f.n_tf + 1) * sizeof(float4);
   const dim3 block(2 * WAVE);  // a tile (or a pair) per workgroup at a time: its walker and its evaluator
   if (pair_list) {
     queue = nullptr;
@@ -2001,9 +2053,11 @@ hipError_t launch_pack_f16(const float* in, int m1, int64_t pixels, void* out_f1
   return hipGetLastError();
 }
 
-hipError_t launch_walk_records(const int4* tet, const float4* vert, int64_t n_tets, int4* wrec, hipStream_t s) {
+hipError_t launch_walk_records(const int4* tet, const float4* vert, int64_t n_tets, const int* sub_begin, int n_sub,
+                               int4* wrec, hipStream_t s) {
   if (n_tets <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_walk_records, dim3(grid1(n_tets, 256)), dim3(256), 0, s, tet, vert, n_tets, wrec);
+  hipLaunchKernelGGL(k_walk_records, dim3(grid1(4 * n_tets, 256)), dim3(256), 0, s, tet, vert, n_tets, sub_begin,
+                     n_sub, wrec);
   return hipGetLastError();
 }
 

@@ -576,16 +576,14 @@ struct Bound {
     }
   }
 
-  // P = Li (1, z, ..., z^N): the orthonormal polynomials at z
+  // P = Li (1, z, ..., z^N): the orthonormal polynomials at z, row by row (Horner)
   APC_HD void values(R z, R* P) const {
 #pragma unroll
-    for (int k = 0; k <= N; ++k) P[k] = R(0);
-    R v = R(1);
+    for (int k = 0; k <= N; ++k) {
+      R v = Li[k * (k + 1) / 2 + k];
 #pragma unroll
-    for (int j = 0; j <= N; ++j) {
-#pragma unroll
-      for (int k = j; k <= N; ++k) P[k] += Li[k * (k + 1) / 2 + j] * v;
-      v *= z;
+      for (int j = k - 1; j >= 0; --j) v = v * z + Li[k * (k + 1) / 2 + j];
+      P[k] = v;
     }
   }
 
@@ -615,7 +613,10 @@ struct Bound {
     R x[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) x[i] = R(0);
-    const int nr = poly_roots<N, R>(q, x);
+    return closed_sum(z, eta, lam0, x, poly_roots<N, R>(q, x));
+  }
+  // the bound from nr finite roots x of K(., z)
+  APC_HD R closed_sum(R z, R eta, R lam0, const R* x, int nr) const {
     int below = 0;
 #pragma unroll
     for (int i = 0; i < N; ++i) below += (i < nr && x[i] < z) ? 1 : 0;
@@ -785,134 +786,192 @@ struct Bound {
   // ---- continuation along one ray (the fused re-walk of stage two)
   //
   // Consecutive samples of a ray lie close in depth, and inside one gap the
-  // roots a sample needs move smoothly with z -- except that the outer roots
-  // run to infinity like 1 / (distance to one gap end).  Cont therefore holds
-  // each root in the table's regularised coordinate (to_table), which stays
-  // smooth up to both gap ends, and the previous sample's value, mapped back
-  // with this sample's gap coordinate, is the Newton start.  Cont also holds
-  // the gap of the last sample whose roots were found (-1: none).  A sample in
-  // another gap (or after a failure) takes its starts from the closed forms.
-  // Either way the roots must converge inside their gaps (the table path's
-  // test), else the sample takes the closed-form bound, so the start changes
-  // the cost of a sample but not its result beyond rounding.
-  static constexpr int CONT_STEPS = 4;  // steps from a continued (or closed-form) start: 3 Newton, 1 chord
+  // roots a sample needs move smoothly with z, at a known speed: with p the
+  // degree-N orthonormal polynomial, (x - z) K(x, z) = p(x) p(z) (h(x) - h(z))
+  // for one function h of the pixel, so a root keeps h(x) = h(z) and
+  //   dx/dz = h'(z) / h'(x) = K(z, z) p(x)^2 / (K(x, x) p(z)^2),
+  // all of which the sample has at hand.  The next sample starts from the
+  // roots carried along their tangents; one Newton step and one with the same
+  // slope follow (the start is off by the square of the sample distance), more
+  // only for a lane that has not settled.  The outer root runs to infinity at
+  // one end of its gap, so it is carried as u = 1 / (x - pivot), which passes
+  // through 0 there, with the pivot one zero inside the gap's finite end.
+  // Cont also holds the gap of the last sample whose roots were found (-1:
+  // none).  A sample in another gap (or after a failure) starts from where the
+  // roots stand at the gap's ends, in between by z's place in the gap: at the
+  // lower end the outer left root is at infinity and the one of gap 1 on its
+  // lower zero, at the upper end both are on the upper zeros of their gaps (the
+  // outer right root the other way round).  Either way the roots must settle
+  // inside their gaps (the table path's test), else the sample takes the
+  // closed-form bound, so the start changes the cost of a sample but not its
+  // result beyond rounding.
+  static constexpr int CONT_STEPS = 4;  // pairs of steps at most
   struct Cont {
     int k;
-    R v[Gaps<N>::NC > 0 ? Gaps<N>::NC : 1];  // regularised roots (to_table) of gap k
+    R v[1 + 2 * (Gaps<N>::NC > 0 ? Gaps<N>::NC : 1)];  // z, then each root (slot 0 as u) and its derivative in z
   };
 
-  // Fraction of the absorbance in front of z; `how` says how the roots were
-  // found: 0 none needed, 1 Newton from the previous sample's roots, 2 the
-  // closed forms ran (a new gap, or no convergence).  zs: the sorted zeros.
+  // q and its derivative at x
+  APC_HD static void poly(const R* q, R x, R& p, R& dp) {
+    dp = q[N];
+    p = q[N] * x + q[N - 1];
+#pragma unroll
+    for (int t = N - 2; t >= 0; --t) {
+      dp = dp * x + p;
+      p = p * x + q[t];
+    }
+  }
+
+  // Fraction F of the absorbance in front of z; `how` says how the roots were
+  // found: 0 none needed, 1 Newton from the previous sample's roots, 2 from
+  // z's place in the gap (a new gap).  zs: the sorted zeros (-inf first and inf
+  // last: no zeros known).  Returns false, F unset, when a root did not settle
+  // or all absorbance sits at one depth: the caller then takes frac_closed.  (No
+  // call is made from here: a call would take half the registers away from the
+  // loop around it.)
   template <class Z>
-  APC_HD R frac_before_cont(R z, R eta, const Z& zs, Cont& c, int& how) const {
+  APC_HD bool frac_continued(R z, R eta, const Z& zs, Cont& c, R& F, int& how) const {
     static_assert(N == 3 || N == 4, "the continuation serves m = 6 and m = 8");
     constexpr int NC = Gaps<N>::NC;
-    bool closed = false;
     how = 0;
-    if (mode == 1) {
-      if (m_abs(z1 - z) <= Num<R>::same_depth) return eta;
-      return z1 < z ? R(1) : R(0);
-    }
+    const R t0 = zs[0], t1 = zs[1], t2 = zs[N - 2], t3 = zs[N - 1];
     R P[N + 1];
     values(z, P);
     R K0 = R(0);
 #pragma unroll
     for (int k = 0; k <= N; ++k) K0 += P[k] * P[k];
     const R lam0 = m_rcp1(K0);
-    if (z < xlo) return eta * lam0;
-    if (z > xhi) return R(1) - (R(1) - eta) * lam0;
+    if (z < t0 || z > t3) {
+      const R e = z < t0 ? eta : R(1) - eta;
+      F = z < t0 ? e * lam0 : R(1) - e * lam0;
+      return mode == 2;
+    }
     R q[N + 1];
     coeffs(P, q);
-    int k = 0;
-#pragma unroll
-    for (int t = 0; t < N; ++t) k += zs[t] < z ? 1 : 0;
-    bool ok = k >= 1 && k <= N - 1;
-    const int kk = ok ? k : 1;
-    // For N <= 4 the nodes on the fewer side of gap kk (side_gap) are the one
-    // of gap 0 (left: 2 kk <= N) or of gap N (right), and for N = 4, kk = 2
-    // also the one of gap 1 = (zs[0], zs[1]).  So root slot 0 always lies in
+    // For N <= 4 the nodes on the fewer side of z's gap kk (side_gap) are the
+    // one of gap 0 (left: 2 kk <= N) or of gap N (right), and for N = 4, kk = 2
+    // also the one of gap 1 = (t0, t1).  So root slot 0 always lies in
     // an outer gap and slot 1 in gap 1, and every zero is read at a constant
     // index (a run-time index costs a select over all N of them).
-    const bool left = 2 * kk <= N;
-    const bool two = N == 4 && kk == 2;  // slot 1 in use
-    R lo = zs[0], hi = zs[1];            // the gap of z: (zs[kk - 1], zs[kk])
+    const bool past1 = t1 < z;
+    const bool past2 = N == 4 && t2 < z;
+    const int kk = 1 + (past1 ? 1 : 0) + (past2 ? 1 : 0);
+    const bool left = N == 4 ? !past2 : !past1;
+    const bool two = N == 4 && past1 && !past2;  // slot 1 in use
+    const R base = left ? t0 : t3;     // slot 0: the finite end of its gap
+    const R pivot = left ? t1 : t2;
+    const R dz = z - c.v[0];
+    R x0 = pivot + m_rcp_est(c.v[1] + c.v[2] * dz), x1 = R(0);
+    if constexpr (NC > 1) x1 = c.v[3] + c.v[4] * dz;
+    how = 1;
+    if (kk != c.k) {
+      how = 2;
+      const R lo = two ? t1 : (left ? t0 : t2), hi = two ? t2 : (left ? t1 : t3);
+      const bool upper = z - lo > hi - z;  // nearer the gap's upper end
+      R p, dp;
+      if (left == upper) {
+        poly(q, base, p, dp);
+        x0 = base - p * m_rcp_est(dp);
+      } else {  // the roots' sum less the others, which are near the zeros
+        x0 = -q[N - 1] * m_rcp_est(q[N]) + (left ? lo : hi);
 #pragma unroll
-    for (int t = 2; t < N; ++t) {
-      lo = kk == t ? zs[t - 1] : lo;
-      hi = kk == t ? zs[t] : hi;
-    }
-    const R base = left ? zs[0] : zs[N - 1];  // slot 0: the finite end of its gap
-    const R sz = (z - lo) * m_rcp_est(hi - z);  // the gap coordinate only maps Newton starts
-    R x[NC];
-    if (ok && kk == c.k) {  // from_table of each slot's root
-      const R isz = (hi - z) * m_rcp_est(z - lo);  // the start needs no more
-      x[0] = base + c.v[0] * (left ? isz : sz);
-      if constexpr (NC > 1) {
-        const R e = c.v[1] * sz;
-        x[1] = two ? zs[0] + (zs[1] - zs[0]) * e * m_rcp_est(R(1) + e) : R(0);
+        for (int t = 0; t < N; ++t) x0 -= t == 0 ? t0 : (t == 1 ? t1 : (t == 2 ? zs[2] : t3));
       }
-    } else {  // starts from the closed forms, sorted: gap j's root is r[j] below kk, r[j - 1] above
-      closed = true;
-      R r[N];
-#pragma unroll
-      for (int t = 0; t < N; ++t) r[t] = R(0);
-      const int nr = poly_roots<N, R, 1>(q, r);
-      sort_up(r);
-      ok = ok && nr == N;
-      x[0] = left ? r[0] : r[N - 1];
-      if constexpr (NC > 1) x[1] = two ? r[1] : R(0);
+      if constexpr (NC > 1) {
+        const R end = upper ? t1 : t0;
+        poly(q, end, p, dp);
+        x1 = end - p * m_rcp_est(dp);
+      }
     }
+    bool ok = true;
     R S = R(0);
+    const R ip = m_rcp_est(P[N]);
+    const R speed = K0 * ip * ip;
+    c.v[0] = z;
 #pragma unroll
     for (int cc = 0; cc < NC; ++cc) {
       if (cc == 0 || two) {
-        R xi = x[cc], d = R(0), rd = R(0);
-#pragma unroll
+        R x = cc == 0 ? x0 : x1;
+        const R scale = cc == 0 ? m_abs(x - pivot) : t1 - t0;
+        R d = R(0);
+#pragma unroll 1
         for (int it = 0; it < CONT_STEPS; ++it) {
-          R p = q[N], dp = R(0);
-          if (it < CONT_STEPS - 1) {  // Newton steps
+          R p, dp;
+          poly(q, x, p, dp);
+          const R rd = m_rcp_est(dp);
+          x -= p * rd;
+          p = q[N];
 #pragma unroll
-            for (int t = N - 1; t >= 0; --t) {
-              dp = dp * xi + p;
-              p = p * xi + q[t];
-            }
-            rd = m_rcp_est(dp);
-          } else {  // the last step keeps the previous slope
-#pragma unroll
-            for (int t = N - 1; t >= 0; --t) p = p * xi + q[t];
-          }
+          for (int t = N - 1; t >= 0; --t) p = p * x + q[t];
           d = p * rd;
-          xi -= d;
+          x -= d;
+          if (!(m_abs(d) > R(1e-8) * scale)) break;
         }
-        const R blo = cc == 0 ? (left ? -R(HUGE_VAL) : zs[N - 1]) : zs[0];
-        const R bhi = cc == 0 ? (left ? zs[0] : R(HUGE_VAL)) : zs[1];
-        const R lam = m_rcp1(kernel_diag(xi));
+        R Q[N + 1];
+        values(x, Q);
+        R K = R(0);
+#pragma unroll
+        for (int k = 0; k <= N; ++k) K += Q[k] * Q[k];
+        const R lam = m_rcp1(K);
+        const R blo = cc == 0 ? (left ? -R(HUGE_VAL) : base) : t0;
+        const R bhi = cc == 0 ? (left ? base : R(HUGE_VAL)) : t1;
         const R ad = m_abs(d);
-        // converged: a small last step, or (outer gaps, where K grows away
-        // from the zeros) a weight too small for the step to matter -- from an
-        // iterate that has settled against its distance to the gap's end
-        const bool conv = ad <= R(1e-7) * m_max(R(1), m_abs(xi)) ||
-                          (cc == 0 && lam * ad <= R(1e-12) * m_abs(xi - base) &&
-                           ad <= R(1e-3) * m_abs(xi - base));
-        ok = ok && xi > blo && xi < bhi && conv;
-        x[cc] = xi;
+        // settled: a small last step, or (outer gaps, where K grows away from the zeros) a weight too small
+        // for the step to matter -- from an iterate that has settled against its distance to the gap's end
+        const bool conv = ad <= R(1e-7) * scale || (cc == 0 && lam * ad <= R(1e-12) * m_abs(x - base) &&
+                                                    ad <= R(1e-3) * m_abs(x - base));
+        ok = ok && x > blo && x < bhi && conv;
         S += lam;
+        const R dx = speed * lam * Q[N] * Q[N];
+        const R u = cc == 0 ? m_rcp_est(x - pivot) : x;
+        c.v[1 + 2 * cc] = u;
+        c.v[2 + 2 * cc] = cc == 0 ? -dx * u * u : dx;
       }
     }
-    if (!ok) {
-      c.k = -1;
-      how = 2;
-      return closed_tail(z, eta, lam0, q);
+    c.k = ok ? kk : -1;
+    F = left ? eta * lam0 + S : R(1) - (R(1) - eta) * lam0 - S;
+    return ok && mode == 2;
+  }
+
+  // The sample frac_continued gave up: the closed-form bound; its roots (sorted:
+  // gap j's root is r[j] below z's gap, r[j - 1] above) are left for the next.
+  template <class Z>
+  APC_HD R frac_closed(R z, R eta, const Z& zs, Cont& c) const {
+    c.k = -1;
+    if (mode == 1) return m_abs(z1 - z) <= Num<R>::same_depth ? eta : (z1 < z ? R(1) : R(0));
+    R P[N + 1], q[N + 1], r[N];
+    values(z, P);
+    coeffs(P, q);
+    R K0 = R(0);
+#pragma unroll
+    for (int k = 0; k <= N; ++k) K0 += P[k] * P[k];
+#pragma unroll
+    for (int t = 0; t < N; ++t) r[t] = R(0);
+    const int nr = poly_roots<N, R>(q, r);
+    const R F = closed_sum(z, eta, m_rcp(K0), r, nr);
+    if (nr == N) {
+      sort_up(r);
+      const bool past1 = zs[1] < z, past2 = N == 4 && zs[2] < z;
+      const bool left = N == 4 ? !past2 : !past1;
+      c.k = 1 + (past1 ? 1 : 0) + (past2 ? 1 : 0);
+      c.v[0] = z;
+      c.v[1] = left ? m_rcp(r[0] - zs[1]) : m_rcp(r[N - 1] - zs[N - 2]);
+      c.v[2] = R(0);
+      if constexpr (N == 4) {
+        c.v[3] = r[1];
+        c.v[4] = R(0);
+      }
     }
-    how = closed ? 2 : 1;
-    c.k = kk;
-    c.v[0] = (x[0] - base) * (left ? sz : m_rcp_est(sz));  // to_table of slot 0
-    if constexpr (NC > 1) {
-      const R fr = (x[1] - zs[0]) * m_rcp_est(zs[1] - zs[0]);
-      c.v[1] = two ? fr * m_rcp_est((R(1) - fr) * sz) : R(0);
-    }
-    return left ? eta * lam0 + S : R(1) - (R(1) - eta) * lam0 - S;
+    return F;
+  }
+
+  // frac_continued, or the closed forms where it does not settle (how = 2).
+  template <class Z>
+  APC_HD R frac_before_cont(R z, R eta, const Z& zs, Cont& c, int& how) const {
+    R F;
+    if (frac_continued(z, eta, zs, c, F, how)) return F;
+    how = 2;
+    return frac_closed(z, eta, zs, c);
   }
 
 };
