@@ -635,7 +635,7 @@ apc_status apc_create(int device, apc_ctx* out) {
   if (!c) return fail(APC_E_NOMEM, "host allocation failed");
   c->device = device;
   noalloc_setup(device);
-  hipError_t e = c->counters.ensure(sizeof(unsigned long long) * apc::C_COUNT);
+  hipError_t e = c->counters.ensure(sizeof(unsigned long long) * apc::CTR_COPIES * apc::CTR_STRIDE);
   if (e == hipSuccess) e = hipMemset(c->counters.p, 0, c->counters.bytes);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->staging_done, hipEventDisableTiming);
   for (int k = 0; k < EV_COUNT && e == hipSuccess; ++k)
@@ -1639,8 +1639,10 @@ apc_status apc_get_counters(apc_ctx ctx, apc_counters* out, int32_t reset) {
   if (!out) return fail(APC_E_ARG, "out is NULL");
   if (ctx->host_only) return no_device("apc_get_counters");
   HIPCHK(hipDeviceSynchronize());
-  unsigned long long c[apc::C_COUNT];
-  HIPCHK(hipMemcpy(c, ctx->counters.p, sizeof(c), hipMemcpyDeviceToHost));
+  unsigned long long all[apc::CTR_COPIES][apc::CTR_STRIDE], c[apc::C_COUNT] = {};
+  HIPCHK(hipMemcpy(all, ctx->counters.p, sizeof(all), hipMemcpyDeviceToHost));
+  for (const auto& copy : all)
+    for (int k = 0; k < apc::C_COUNT; ++k) c[k] += copy[k];
   out->pieces = int64_t(c[apc::C_PIECES]);
   out->tet_steps = int64_t(c[apc::C_STEPS]);
   out->entries = int64_t(c[apc::C_ENTRIES]);
@@ -1653,7 +1655,7 @@ apc_status apc_get_counters(apc_ctx ctx, apc_counters* out, int32_t reset) {
   out->table_fallback = int64_t(c[apc::C_TABFB]);
   out->segments = int64_t(c[apc::C_SEGMENTS]);
   if (reset) {
-    HIPCHK(hipMemset(ctx->counters.p, 0, sizeof(c)));
+    HIPCHK(hipMemset(ctx->counters.p, 0, sizeof(all)));
     ctx->bin_records = 0;
   }
   return APC_OK;

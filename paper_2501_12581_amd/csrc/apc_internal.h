@@ -86,9 +86,12 @@ struct BoundParams {
   int moments_f16;  // the moment image is the packed FP16 form (ln b0, b_j / b0)
 };
 
-// Diagnostic counters (device memory, int64 each), in apc_counters order.
+// Diagnostic counters (device memory, int64 each), in apc_counters order, CTR_COPIES times at a stride of
+// CTR_STRIDE (a 128-byte line): a workgroup adds to one copy, a reader takes the sum of all.
 enum { C_PIECES = 0, C_STEPS, C_ENTRIES, C_BINREC, C_STEPLIMIT, C_FALLBACK, C_OVERFLOW, C_NONPD, C_TABLED,
        C_TABFB, C_SEGMENTS, C_COUNT };
+constexpr int CTR_COPIES = 64, CTR_STRIDE = 16;
+static_assert(C_COUNT <= CTR_STRIDE, "a copy of the counters fits its line");
 
 constexpr int MAX_TF = 1024;
 
