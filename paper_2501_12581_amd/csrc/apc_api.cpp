@@ -126,6 +126,8 @@ struct apc_ctx_s {
   size_t staging_bytes = 0;
   hipEvent_t staging_done = nullptr;
   int64_t bin_records = 0;  // (face, tile) records binned, counted on the host
+  unsigned long long* totals = nullptr;  // pinned: records and pairs of the last scan of bins
+  hipEvent_t totals_done = nullptr;
   // event pairs around the launches: binning, moments, sum, resolve, re-walk, evaluation
   hipEvent_t ev[6][2] = {};
   bool ev_used[6] = {};
@@ -167,6 +169,7 @@ struct apc_ctx_s {
   apc_view bin_view = {};
   int bin_tw = -1;
   std::vector<int> bin_subs;
+  int64_t bin_pairs = -1;  // bins with records, numbered in pidx (-1: not numbered)
 };
 
 struct apc_graph_s {
@@ -405,14 +408,17 @@ long long bin_cap(apc_ctx ctx) { return (long long)(ctx->records.bytes / sizeof(
 struct BinSpace {
   SlotDev* slots;
   int *counts, *offsets, *cursors, *tmp, *records;
+  int* pidx;          // where the pairs are numbered (null: they are not)
   long long rec_cap;  // records the record buffer holds (sized after counting when `grow`)
   bool grow;          // records live in ctx->records and may be grown
 };
 
 // Bin the boundary faces of the listed subdomains into (tile, slot) bins:
-// slot table upload, count pass, exclusive scan, the record total read back
-// (to size or check the record buffer; not while capturing a graph, whose
-// buffers were sized by an eager frame), fill pass.
+// slot table upload, count pass, scan, fill pass.  The scan writes the record
+// total to pinned memory, which the host waits for (to size or check the
+// record buffer; not while capturing a graph, whose buffers were sized by an
+// eager frame) while the fill pass already runs: it writes within the buffer
+// it has, and runs again where that turns out too small.
 apc_status bin_faces(apc_ctx ctx, const apc_mesh_s* m, const FrameDev& f, const int32_t* subs, int32_t n_sub,
                      BinSpace& B, hipStream_t s, MeshDev& md) {
   SlotDev sl_fixed[64];
@@ -446,35 +452,39 @@ apc_status bin_faces(apc_ctx ctx, const apc_mesh_s* m, const FrameDev& f, const 
   HIPCHK(ev_mark(ctx, EV_BIN, 0, s));
   HIPCHK(apc::launch_fill_i32(B.counts, 0, nb, s));
   HIPCHK(apc::launch_bin_count(md, f, B.slots, max_faces, m->bface, B.counts, s));
-  HIPCHK(apc::launch_exclusive_scan(B.counts, B.offsets, nb, B.tmp, s));
+  HIPCHK(apc::launch_bin_scan(B.counts, nb, B.offsets, B.cursors, B.pidx, B.tmp,
+                              ctx->capturing ? nullptr : ctx->totals, s));
+  if (!ctx->capturing) HIPCHK(hipEventRecord(ctx->totals_done, s));
+  if (B.rec_cap > 0)  // (a context's first frame has no records yet)
+    HIPCHK(apc::launch_bin_fill(md, f, B.slots, max_faces, m->bface, B.offsets, B.cursors, B.records, B.rec_cap, s));
   if (!ctx->capturing) {
-    int tail[2];
-    HIPCHK(hipMemcpyAsync(&tail[0], B.offsets + nb - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(&tail[1], B.counts + nb - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    const int64_t total = int64_t(tail[0]) + tail[1];
-    if (total < 0 || total > (int64_t(1) << 31) - 1)
-      return fail(APC_E_NUMERIC, "bin records overflow (%lld)", (long long)total);
-    if (B.grow) {
-      HIPCHK(ctx->records.ensure(sizeof(int) * std::max<int64_t>(total, 1)));
+    HIPCHK(hipEventSynchronize(ctx->totals_done));
+    const int64_t total = int64_t(ctx->totals[0]);
+    if (total > (int64_t(1) << 31) - 1) return fail(APC_E_NUMERIC, "bin records overflow (%lld)", (long long)total);
+    if (total > B.rec_cap) {
+      if (!B.grow)
+        return fail(APC_E_NOMEM, "the frame bins %lld (face, tile) records; the static workspace holds %lld",
+                    (long long)total, B.rec_cap);
+      HIPCHK(hipStreamSynchronize(s));
+      HIPCHK(ctx->records.ensure(sizeof(int) * total));
       B.records = ctx->records.as<int>();
       B.rec_cap = bin_cap(ctx);
-    } else if (total > B.rec_cap) {
-      return fail(APC_E_NOMEM, "the frame bins %lld (face, tile) records; the static workspace holds %lld",
-                  (long long)total, B.rec_cap);
+      HIPCHK(apc::launch_fill_i32(B.cursors, 0, nb, s));
+      HIPCHK(apc::launch_bin_fill(md, f, B.slots, max_faces, m->bface, B.offsets, B.cursors, B.records, B.rec_cap, s));
     }
     ctx->bin_records += total;
   }
-  HIPCHK(apc::launch_fill_i32(B.cursors, 0, nb, s));
-  HIPCHK(apc::launch_bin_fill(md, f, B.slots, max_faces, m->bface, B.offsets, B.cursors, B.records, B.rec_cap, s));
   HIPCHK(ev_mark(ctx, EV_BIN, 1, s));
   return APC_OK;
 }
 
 // bin_faces into the context's growable buffers, unless they already hold the bins of this mesh, view, tile
-// shape and subdomain list (stage two after stage one of the same frame); a captured frame always bins
+// shape and subdomain list (stage two after stage one of the same frame); a captured frame always bins.  With
+// `pairs` the bins with faces are numbered in ctx->pidx, ctx->bin_pairs of them.
 apc_status build_bins(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const FrameDev& f, const int32_t* subs,
-                      int32_t n_sub, hipStream_t s, MeshDev& md) {
+                      int32_t n_sub, bool pairs, hipStream_t s, MeshDev& md) {
+  const int64_t nb = int64_t(f.n_tiles) * n_sub;
+  if (pairs) HIPCHK(ctx->pidx.ensure(sizeof(int) * nb));
   if (!ctx->capturing && ctx->bins_valid && ctx->bin_mesh == m->uid && ctx->bin_tw == ctx->tw_log2 &&
       std::memcmp(&ctx->bin_view, v, sizeof(apc_view)) == 0 && ctx->bin_subs.size() == size_t(n_sub) &&
       std::equal(subs, subs + n_sub, ctx->bin_subs.begin())) {
@@ -483,17 +493,24 @@ apc_status build_bins(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const
     md.wrec = m->wrec;
     md.n_vertices = m->V;
     md.n_tets = m->T;
+    if (pairs && ctx->bin_pairs < 0) {  // binned without them
+      HIPCHK(apc::launch_bin_scan(ctx->counts.as<int>(), nb, nullptr, nullptr, ctx->pidx.as<int>(),
+                                  ctx->scan_tmp.as<int>(), ctx->totals, s));
+      HIPCHK(hipEventRecord(ctx->totals_done, s));
+      HIPCHK(hipEventSynchronize(ctx->totals_done));
+      ctx->bin_pairs = int64_t(ctx->totals[1]);
+    }
     return APC_OK;
   }
   ctx->bins_valid = false;
-  const int64_t nb = int64_t(f.n_tiles) * n_sub;
   HIPCHK(ctx->slots.ensure(sizeof(SlotDev) * n_sub));
   HIPCHK(ctx->counts.ensure(sizeof(int) * nb));
   HIPCHK(ctx->offsets.ensure(sizeof(int) * (nb + 1)));
   HIPCHK(ctx->cursors.ensure(sizeof(int) * nb));
   HIPCHK(ctx->scan_tmp.ensure(sizeof(int) * apc::scan_tmp_elems(nb)));
   BinSpace B = {ctx->slots.as<SlotDev>(), ctx->counts.as<int>(), ctx->offsets.as<int>(), ctx->cursors.as<int>(),
-                ctx->scan_tmp.as<int>(), ctx->records.as<int>(), bin_cap(ctx), true};
+                ctx->scan_tmp.as<int>(), ctx->records.as<int>(), pairs ? ctx->pidx.as<int>() : nullptr, bin_cap(ctx),
+                true};
   const apc_status st = bin_faces(ctx, m, f, subs, n_sub, B, s, md);
   if (st == APC_OK && !ctx->capturing) {
     ctx->bins_valid = true;
@@ -501,6 +518,7 @@ apc_status build_bins(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const
     ctx->bin_view = *v;
     ctx->bin_tw = ctx->tw_log2;
     ctx->bin_subs.assign(subs, subs + n_sub);
+    ctx->bin_pairs = pairs ? int64_t(ctx->totals[1]) : -1;
   }
   return st;
 }
@@ -638,6 +656,9 @@ apc_status apc_create(int device, apc_ctx* out) {
   hipError_t e = c->counters.ensure(sizeof(unsigned long long) * apc::CTR_COPIES * apc::CTR_STRIDE);
   if (e == hipSuccess) e = hipMemset(c->counters.p, 0, c->counters.bytes);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->staging_done, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&c->totals_done, hipEventDisableTiming);
+  if (e == hipSuccess)
+    e = hipHostMalloc(reinterpret_cast<void**>(&c->totals), 2 * sizeof(*c->totals), hipHostMallocCoherent);
   for (int k = 0; k < EV_COUNT && e == hipSuccess; ++k)
     for (int w = 0; w < 2 && e == hipSuccess; ++w) e = hipEventCreate(&c->ev[k][w]);
   if (e != hipSuccess) {
@@ -663,6 +684,8 @@ apc_status apc_destroy(apc_ctx ctx) {
     b->release();
   if (ctx->staging) (void)hipHostFree(ctx->staging);
   if (ctx->staging_done) (void)hipEventDestroy(ctx->staging_done);
+  if (ctx->totals) (void)hipHostFree(ctx->totals);
+  if (ctx->totals_done) (void)hipEventDestroy(ctx->totals_done);
   for (int k = 0; k < EV_COUNT; ++k)
     for (int w = 0; w < 2; ++w)
       if (ctx->ev[k][w]) (void)hipEventDestroy(ctx->ev[k][w]);
@@ -978,7 +1001,7 @@ apc_status apc_moments_pass(apc_ctx ctx, apc_mesh m, const apc_view* view, const
   if (ctx->host_only) return no_device("apc_moments_pass");
   hipStream_t s = static_cast<hipStream_t>(stream);
   MeshDev md;
-  if ((st = build_bins(ctx, m, view, f, subs, n_sub, s, md)) != APC_OK) return st;
+  if ((st = build_bins(ctx, m, view, f, subs, n_sub, false, s, md)) != APC_OK) return st;
   HIPCHK(ctx->pcount.ensure(sizeof(int) * size_t(f.n_tiles) * 64));
   // keep the pieces for stage two unless asked not to (or the pool cannot be had)
   apc::PieceStore ps = {};
@@ -1038,17 +1061,9 @@ apc_status moments_tiles(apc_ctx ctx, apc_mesh m, const apc_view* view, const ap
   if (ctx->host_only) return no_device(name);
   hipStream_t s = static_cast<hipStream_t>(stream);
   MeshDev md;
-  if ((st = build_bins(ctx, m, view, f, subs, n_sub, s, md)) != APC_OK) return st;
-  // number the (tile, slot) bins that have faces: those are the pairs (the binning's cursors are free now)
-  const int64_t nb = int64_t(f.n_tiles) * n_sub;
-  HIPCHK(ctx->pidx.ensure(sizeof(int) * nb));
-  HIPCHK(apc::launch_pair_scan(ctx->counts.as<int>(), nb, ctx->cursors.as<int>(), ctx->pidx.as<int>(),
-                               ctx->scan_tmp.as<int>(), s));
-  int tail[2];
-  HIPCHK(hipMemcpyAsync(&tail[0], ctx->pidx.as<int>() + nb - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(&tail[1], ctx->cursors.as<int>() + nb - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
-  const int64_t pairs = int64_t(tail[0]) + tail[1];
+  // the pairs: the (tile, slot) bins that have faces, numbered
+  if ((st = build_bins(ctx, m, view, f, subs, n_sub, true, s, md)) != APC_OK) return st;
+  const int64_t nb = int64_t(f.n_tiles) * n_sub, pairs = ctx->bin_pairs;
   *n_pairs = pairs;
   if (max_pairs == 0 && !tiles) return APC_OK;  // a query: the caller sizes its buffers from *n_pairs
   if (pairs > max_pairs)
@@ -1247,19 +1262,11 @@ static apc_status resolve_frame(apc_ctx ctx, apc_mesh m, const apc_view* view, c
   }
   // the plain form: walk the rays again and evaluate every piece at once
   MeshDev md;
-  if ((st = build_bins(ctx, m, view, f, subs, n_sub, s, md)) != APC_OK) return st;
+  if ((st = build_bins(ctx, m, view, f, subs, n_sub, (flags & APC_BY_PAIR) != 0, s, md)) != APC_OK) return st;
   if (flags & APC_BY_PAIR) {
-    // number the (tile, slot) bins with faces (the binning's cursors are free now), list them, walk each
-    // pair in a workgroup of its own, then sum each pixel's pairs in slot order and finalise
-    const int64_t nb = int64_t(f.n_tiles) * n_sub;
-    HIPCHK(ctx->pidx.ensure(sizeof(int) * nb));
-    HIPCHK(apc::launch_pair_scan(ctx->counts.as<int>(), nb, ctx->cursors.as<int>(), ctx->pidx.as<int>(),
-                                 ctx->scan_tmp.as<int>(), s));
-    int tail[2];
-    HIPCHK(hipMemcpyAsync(&tail[0], ctx->pidx.as<int>() + nb - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(&tail[1], ctx->cursors.as<int>() + nb - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    const int64_t pairs = int64_t(tail[0]) + tail[1];
+    // list the (tile, slot) bins with faces, walk each pair in a workgroup of its own, then sum each pixel's
+    // pairs in slot order and finalise
+    const int64_t nb = int64_t(f.n_tiles) * n_sub, pairs = ctx->bin_pairs;
     HIPCHK(ctx->rpair.ensure(sizeof(int) * size_t(std::max<int64_t>(pairs, 1))));
     HIPCHK(ctx->rpart.ensure(sizeof(float) * 4 * 64 * size_t(std::max<int64_t>(pairs, 1))));
     HIPCHK(apc::launch_pair_list(ctx->counts.as<int>(), nb, ctx->pidx.as<int>(), ctx->rpair.as<int>(), s));
@@ -1311,7 +1318,7 @@ apc_status apc_resolve_pass_noalloc(apc_ctx ctx, apc_mesh m, const apc_view* vie
   unsigned char* base = static_cast<unsigned char*>(g_noalloc_ptr[dev]);
   BinSpace B = {reinterpret_cast<SlotDev*>(base), reinterpret_cast<int*>(base + o_counts),
                 reinterpret_cast<int*>(base + o_offsets), reinterpret_cast<int*>(base + o_cursors),
-                reinterpret_cast<int*>(base + o_tmp), reinterpret_cast<int*>(base + o_rec),
+                reinterpret_cast<int*>(base + o_tmp), reinterpret_cast<int*>(base + o_rec), nullptr,
                 (long long)((NOALLOC_BYTES - o_rec) / sizeof(int)), false};
   hipStream_t s = static_cast<hipStream_t>(stream);
   unsigned long long* ctr = ctx->counters.as<unsigned long long>();

@@ -145,9 +145,12 @@ hipError_t launch_walk_records(const int4* tet, const float4* vert, int64_t n_te
 // exclusive scan of n int32 values; tmp must hold scan_tmp_elems(n) ints
 int64_t scan_tmp_elems(int64_t n);
 hipError_t launch_exclusive_scan(const int* in, int* out, int64_t n, int* tmp, hipStream_t s);
-// tiles form: pidx[b] = pair number of bin b when counts[b] > 0 (bins with faces, numbered in bin order; the
-// pair count is pidx[nb-1] + flags[nb-1]); flags: nb ints; tmp as for the scan.  Then pair_bin[p] = its bin.
-hipError_t launch_pair_scan(const int* counts, int64_t nb, int* flags, int* pidx, int* tmp, hipStream_t s);
+// the bins' scan: offsets[b] = records before bin b, with cursors[b] = 0 (both or none); pidx[b] = bins with
+// records before b, the pair number of such a bin; totals[0..1] = records, pairs.  Each of the three may be null.
+// tmp: scan_tmp_elems(nb) ints, 8-byte aligned.
+hipError_t launch_bin_scan(const int* counts, int64_t nb, int* offsets, int* cursors, int* pidx, int* tmp,
+                           unsigned long long* totals, hipStream_t s);
+// pair_bin[p] = the bin of pair p
 hipError_t launch_pair_list(const int* counts, int64_t nb, const int* pidx, int* pair_bin, hipStream_t s);
 // global [m1][H][W] moments from n_pairs tiles (pair_bin ascending, n_slots slots per tile, ascending ids)
 hipError_t launch_sum_tiles(const float* tiles, const int* pair_bin, int64_t n_pairs, int n_slots, int m1, int W,

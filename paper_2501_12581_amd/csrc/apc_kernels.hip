@@ -625,7 +625,7 @@ __device__ void walk_subdomain(const MeshDev& M, const FrameDev& f, const Ray& r
         ring.s[slot] = sout;
       }
       tail += alive ? 1 : 0;
-      cnt.segments += forward & fresh ? 1u : 0u;  // a maximal ray interval inside the subdomain
+      cnt.segments += (forward & fresh) ? 1u : 0u;  // a maximal ray interval inside the subdomain
       fresh &= !forward;
       tin = tout;
       if (++steps >= f.max_steps) {  // (every walk has taken at least as many)
@@ -1296,7 +1296,7 @@ __device__ void walk_subdomain_paired(const MeshDev& M, const FrameDev& f, const
       float sout;
       const bool forward = walk_step(r, w, wr, tin, tout, sout, cnt);
       if (alive) q.put(tout, sout, 0);
-      cnt.segments += forward & fresh ? 1u : 0u;  // a maximal ray interval inside the subdomain
+      cnt.segments += (forward & fresh) ? 1u : 0u;  // a maximal ray interval inside the subdomain
       fresh &= !forward;
       tin = tout;
       if (++steps >= f.max_steps) {  // (every walk has taken at least as many)
@@ -1647,8 +1647,8 @@ __global__ void k_bin(MeshDev M, FrameDev f, const SlotDev* __restrict__ slots,
       if (!fill) {
         atomicAdd(counts + bin, 1);
       } else {
-        const int pos = offsets[bin] + atomicAdd(cursors + bin, 1);
-        if (pos < rec_cap) records[pos] = code;  // the walks skip bins beyond the capacity
+        const unsigned pos = unsigned(offsets[bin] + atomicAdd(cursors + bin, 1));
+        if (pos < (unsigned long long)rec_cap) records[pos] = code;  // the walks skip bins beyond the capacity
       }
     }
 }
@@ -1678,12 +1678,8 @@ __global__ void k_sum_moments(const float* __restrict__ in, int n_slots, const i
   }
 }
 
-// The tiles form's pairs: bin b = tile * n_slots + slot with binned faces is pair pidx[b] (exclusive scan of
-// the flags, so in bin order); pair_bin lists the bins of the pairs in that order.
-__global__ void k_pair_flags(const int* __restrict__ counts, int64_t nb, int* __restrict__ flags) {
-  const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (b < nb) flags[b] = counts[b] > 0 ? 1 : 0;
-}
+// A bin b = tile * n_slots + slot with binned faces is a pair; pidx[b] numbers them in bin order, and pair_bin
+// lists their bins in that order.
 __global__ void k_pair_list(const int* __restrict__ counts, int64_t nb, const int* __restrict__ pidx,
                             int* __restrict__ pair_bin) {
   const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -1829,6 +1825,100 @@ __global__ void k_sum_images(const float4* __restrict__ in, int n_slots, const i
 // ------------------------------------------------------------------ scan / fill
 
 constexpr int SCAN_THREADS = 256, SCAN_ITEMS = 8, SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
+
+// The bins' scan: where each bin's records start (the exclusive sums of the counts) and the numbers of the bins
+// that have any (the pairs), with the fill pass's cursors cleared on the way.  Two launches: the sums of each
+// SCAN_TILE bins, then every workgroup adds up the sums before its own (a few thousand words from L2 at the
+// largest frames) and scans its bins.  A scan of the counts, one of the pair flags, the clearing and the copies
+// of their last elements to the host took 9 launches and 4 copies; a small frame's time is its launches (binning
+// of a 128^2 frame of 4 subdomains 75 -> 32 us, of a 256^2 frame of 72 by pairs, its pairs' scan included, 220 ->
+// 102 us).
+// sums[w]: records of workgroup w's bins << 12 | its pairs (at most SCAN_TILE).
+__device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
+  return v;
+}
+__device__ __forceinline__ void load_bins(const int* __restrict__ counts, int64_t at, int64_t nb, int v[SCAN_ITEMS]) {
+#pragma unroll
+  for (int k = 0; k < SCAN_ITEMS; ++k) v[k] = at + k < nb ? counts[at + k] : 0;
+}
+
+__global__ __launch_bounds__(SCAN_THREADS) void k_bin_sums(const int* __restrict__ counts, int64_t nb,
+                                                           unsigned long long* __restrict__ sums) {
+  __shared__ unsigned long long part[SCAN_THREADS / WAVE];
+  int v[SCAN_ITEMS];
+  load_bins(counts, int64_t(blockIdx.x) * SCAN_TILE + threadIdx.x * SCAN_ITEMS, nb, v);
+  unsigned long long t = 0;
+#pragma unroll
+  for (int k = 0; k < SCAN_ITEMS; ++k) t += (static_cast<unsigned long long>(v[k]) << 12) + (v[k] > 0 ? 1 : 0);
+  t = wave_sum64(t);
+  if (threadIdx.x % WAVE == 0) part[threadIdx.x / WAVE] = t;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < SCAN_THREADS / WAVE; ++w) t += part[w];
+    sums[blockIdx.x] = t;
+  }
+}
+
+// offsets and cursors, pidx, totals (records, pairs): each may be null
+__global__ __launch_bounds__(SCAN_THREADS) void k_bin_scan(const int* __restrict__ counts, int64_t nb,
+                                                           const unsigned long long* __restrict__ sums,
+                                                           int* __restrict__ offsets, int* __restrict__ cursors,
+                                                           int* __restrict__ pidx,
+                                                           unsigned long long* __restrict__ totals) {
+  constexpr int WAVES = SCAN_THREADS / WAVE;
+  __shared__ unsigned long long prec[WAVES], ppair[WAVES], part[WAVES];
+  const int lane = threadIdx.x % WAVE, wv = threadIdx.x / WAVE;
+  const int64_t at = int64_t(blockIdx.x) * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
+  int v[SCAN_ITEMS];
+  load_bins(counts, at, nb, v);
+  unsigned long long rec = 0, pairs = 0;  // before this workgroup's bins
+  for (unsigned w = threadIdx.x; w < blockIdx.x; w += SCAN_THREADS) {
+    rec += sums[w] >> 12;
+    pairs += sums[w] & 0xfffu;
+  }
+  rec = wave_sum64(rec);
+  pairs = wave_sum64(pairs);
+  unsigned long long mine = 0;
+#pragma unroll
+  for (int k = 0; k < SCAN_ITEMS; ++k) mine += (static_cast<unsigned long long>(v[k]) << 12) + (v[k] > 0 ? 1 : 0);
+  unsigned long long run = mine;  // inclusive over the wavefront's lanes
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const unsigned long long up = __shfl_up(run, o, WAVE);
+    run += lane >= o ? up : 0;
+  }
+  if (lane == WAVE - 1) part[wv] = run;
+  if (lane == 0) {
+    prec[wv] = rec;
+    ppair[wv] = pairs;
+  }
+  __syncthreads();
+  rec = pairs = 0;
+  for (int w = 0; w < WAVES; ++w) {
+    rec += prec[w];
+    pairs += ppair[w];
+    run += w < wv ? part[w] : 0;
+  }
+  run -= mine;
+  rec += run >> 12;
+  pairs += run & 0xfffu;
+#pragma unroll
+  for (int k = 0; k < SCAN_ITEMS; ++k) {
+    if (at + k < nb) {
+      if (offsets) {
+        offsets[at + k] = int(rec);
+        cursors[at + k] = 0;
+      }
+      if (pidx) pidx[at + k] = int(pairs);
+    }
+    rec += unsigned(v[k]);
+    pairs += v[k] > 0 ? 1 : 0;
+  }
+  if (totals && blockIdx.x == gridDim.x - 1 && threadIdx.x == SCAN_THREADS - 1) {
+    totals[0] = rec;
+    totals[1] = pairs;
+  }
+}
 
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_local(const int* __restrict__ in, int* __restrict__ out,
                                                              int64_t n, int* __restrict__ sums) {
@@ -2089,12 +2179,14 @@ hipError_t launch_sum_moments(const float* in, int n_slots, const int* order, in
   return hipGetLastError();
 }
 
-hipError_t launch_pair_scan(const int* counts, int64_t nb, int* flags, int* pidx, int* tmp, hipStream_t s) {
+hipError_t launch_bin_scan(const int* counts, int64_t nb, int* offsets, int* cursors, int* pidx, int* tmp,
+                           unsigned long long* totals, hipStream_t s) {
   if (nb <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pair_flags, dim3(grid1(nb, 256)), dim3(256), 0, s, counts, nb, flags);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_exclusive_scan(flags, pidx, nb, tmp, s);
+  unsigned long long* sums = reinterpret_cast<unsigned long long*>(tmp);
+  const dim3 grid(grid1(nb, SCAN_TILE)), block(SCAN_THREADS);
+  hipLaunchKernelGGL(k_bin_sums, grid, block, 0, s, counts, nb, sums);
+  hipLaunchKernelGGL(k_bin_scan, grid, block, 0, s, counts, nb, sums, offsets, cursors, pidx, totals);
+  return hipGetLastError();
 }
 
 hipError_t launch_pair_list(const int* counts, int64_t nb, const int* pidx, int* pair_bin, hipStream_t s) {
@@ -2146,7 +2238,7 @@ int64_t scan_tmp_elems(int64_t n) {
     n = (n + SCAN_TILE - 1) / SCAN_TILE;
     total += 2 * n + 1;
   }
-  return total + 1;
+  return total < 1 ? 2 : total + 1;
 }
 
 hipError_t launch_exclusive_scan(const int* in, int* out, int64_t n, int* tmp, hipStream_t s) {
