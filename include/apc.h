@@ -484,12 +484,11 @@ typedef struct apc_counters {
   int64_t entry_overflow;   /* per-ray entry lists refilled in extra rounds (results stay correct), plus
                                stage-two re-walks whose piece count differed from the count (never expected) */
   int64_t nonpd_pivots;     /* Cholesky pivots floored in the resolve pass */
-  int64_t table_samples;    /* samples (m >= 6) whose moment bound needed roots, found by Newton from a
-                               start: their pixel's gap table (kept pieces) or the ray's previous sample
-                               (re-walk) */
-  int64_t table_fallback;   /* of those, samples without a carried start: with tables the ones that took the
-                               closed-form roots (~1e-4: a start that did not converge), in the re-walk every
-                               first sample of a ray in a new gap of the bound (a few percent) */
+  int64_t table_samples;    /* samples (m >= 6) whose moment bound needed roots, found by Newton from those of
+                               the ray's previous sample */
+  int64_t table_fallback;   /* of those, samples without a carried start: with kept pieces the ones that took
+                               the closed-form roots (0.1 to 0.5 %: a start that did not converge), in the
+                               re-walk every first sample of a ray in a new gap of the bound (a few percent) */
   int64_t segments;         /* maximal ray intervals inside one subdomain with at least one piece, every walk */
 } apc_counters;
 

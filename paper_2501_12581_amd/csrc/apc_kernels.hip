@@ -35,6 +35,11 @@
 // are compiled without floating-point contraction.
 #include <float.h>
 
+// Products and sums are fused within an expression only, as written: fused across statements too (the compiler's
+// default) it depends on the code around, and the variants of a kernel (tiles from a grid or a queue, by pair)
+// would round differently.
+#pragma clang fp contract(on)
+
 #include "apc_internal.h"
 #include "apc_mboit.h"
 
@@ -336,11 +341,6 @@ __device__ __forceinline__ float opacity(float a) {
   p = fmaf(p, -a, 0.5f);
   p = fmaf(p, -a, 1.0f);
   return a < 0.35f ? a * p : 1.0f - __expf(-a);
-}
-
-__device__ __forceinline__ float lerp_nc(float a, float b, float fr) {
-#pragma clang fp contract(off)
-  return a * (1.0f - fr) + b * fr;
 }
 
 // Where a walk stands: the face (A, B, C) through which the ray entered the
@@ -911,23 +911,7 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(APC_WALK_W
 // ------------------------------------------------------------------ stage two, kept pieces
 //
 // When stage one kept its pieces, stage two evaluates them without a walk:
-// one wavefront per tile takes the tile's pixels one at a time, and its 64
-// lanes evaluate 64 consecutive pieces of that pixel with the pixel's factor
-// from LDS; every pixel then adds its own contributions in a fixed order, so
-// the sum is deterministic.
-
-__device__ __forceinline__ float wave_uniform(float v) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
-}
-__device__ __forceinline__ double wave_uniform(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readfirstlane(int(b & 0xffffffffll));
-  const int hi = __builtin_amdgcn_readfirstlane(int(b >> 32));
-  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
-}
-
-template <int N, class R>
-using LdsBound = apcm::Bound<N, R, apcm::StridedStore<(N + 1) * (N + 2) / 2, R, WAVE>>;
+// one wavefront per tile, a lane per pixel, each lane its pieces in walk order.
 
 __device__ __forceinline__ float4 finalize_px(float4 acc, float b0, int finalize, int renormalize) {
   if (!finalize) return acc;
@@ -935,11 +919,6 @@ __device__ __forceinline__ float4 finalize_px(float4 acc, float b0, int finalize
   float A = -expm1f(-b0);
   float sc = acc.w > 1e-30f ? A / acc.w : 0.0f;
   return make_float4(acc.x * sc, acc.y * sc, acc.z * sc, A);
-}
-
-__device__ __forceinline__ float wave_sum_f(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-  return v;
 }
 
 // The global moments b_0..b_2N of one pixel (zero for an invalid lane), from
@@ -981,192 +960,173 @@ __device__ __forceinline__ float pixel_moments(const void* moments, int f16, boo
   return b0f;
 }
 
-// Moment bound for every staged piece of a tile and the per-pixel colour
-// sums (Alg. 1 second loop, Alg. 3).  The tile's pixels are taken one at a
-// time: the 64 lanes evaluate that pixel's consecutive pieces (so they share
-// the pixel's factor and, with nearby depths, mostly the same branches), each
-// lane keeps a partial sum, and a fixed butterfly adds the partials, so the
-// result does not depend on scheduling.  For n >= 3 a pixel with at least
-// TABLE_MIN_PIECES pieces first fills its gap table (one node per lane) and
-// its pieces take their roots from it.
-// Waves per SIMD the FP64 evaluation is compiled for (register budget 512 / n):
-// the closed-form root solver is out of line, which keeps n = 4 within 168.
-#ifndef APC_EVAL_WAVES
-#define APC_EVAL_WAVES 3
-#endif
-#ifndef APC_EVAL_WAVES_N4
-#define APC_EVAL_WAVES_N4 3
-#endif
-#ifndef APC_TABLE_MIN_PIECES
-#define APC_TABLE_MIN_PIECES 128
-#endif
+// The per-pixel part of Alg. 3, once per pixel instead of once per sample: the bound, its zeros (in LDS, 8
+// registers less across the loop over the samples; n >= 3) and an empty continuation.  Returns b0 in FP32.
+template <int N, class R, class Z>
+__device__ __forceinline__ float pixel_bound(const void* moments, const BoundParams& bp, bool valid, size_t pix,
+                                             size_t HW, apcm::Bound<N, R>& bound, const Z& zs,
+                                             typename apcm::Bound<N, R>::Cont& cont, LaneCount& cnt) {
+  cont.k = -1;
+#pragma unroll
+  for (int c = 0; c < int(sizeof(cont.v) / sizeof(R)); ++c) cont.v[c] = R(0);
+  R b[2 * N + 1], bias[2 * N], zsr[N];
+  const float b0f = pixel_moments<N, R>(moments, bp.moments_f16, valid, pix, HW, b);
+#pragma unroll
+  for (int j = 0; j < 2 * N; ++j) bias[j] = R(bp.bias[j]);
+  cnt.nonpd += bound.setup(b, R(bp.alpha), bias, zsr);
+  // no zeros found (never expected for a positive definite factor): no shortcut, every sample solves
+  if (bound.mode == 2 && !(zsr[0] < zsr[N - 1])) {
+    bound.xlo = zsr[0] = -R(HUGE_VAL);
+    bound.xhi = zsr[N - 1] = R(HUGE_VAL);
+  }
+  if constexpr (N >= 3) {
+    if (bound.mode != 2) zsr[0] = zsr[N - 1] = __builtin_nan("");  // never continued
+#pragma unroll
+    for (int i = 0; i < N; ++i) zs[i] = zsr[i];
+  }
+  return b0f;
+}
 
-// Wavefronts per workgroup of the evaluation: they share one copy of the
-// transfer-function table in LDS (the per-pixel state is per wavefront).
-constexpr int EVAL_WPB = 4;
+// Moment bound for every kept piece of a tile and the per-pixel colour sums
+// (Alg. 1 second loop, Alg. 3).  A lane takes its pixel's pieces in walk order,
+// each with the roots the previous one left (apcm::Bound::frac_continued, n >= 3).
+// Bound by FP64
+// arithmetic at n >= 3, whose few wavefronts re-read their lanes' lines from L2;
+// at n = 2 the lanes of all wavefronts hold more lines than L2 does, so a lane
+// reads four pieces at once (1024^2, m = 4: 2.9 ms one at a time, 1.1 now).  The form before took a pixel's pieces 64 at a time, one per lane,
+// each from a table of its gaps' roots that the 64 lanes filled with closed
+// forms first: a third of the time, and four Newton steps a piece.  Measured,
+// 1024^2 on 1.6M tets, before and now: m = 8 3.67 and 1.75 ms, m = 6 2.61 and 1.60,
+// m = 4 1.14 and 1.09.
+constexpr int EVAL_WPB = 4;  // wavefronts (tiles) per workgroup: they share the transfer function in LDS
 
 template <int N, class R>
-__global__ __launch_bounds__(WAVE * EVAL_WPB) __attribute__((amdgpu_waves_per_eu(N >= 4 ? APC_EVAL_WAVES_N4 : APC_EVAL_WAVES, 8))) void k_eval(
+__global__ __launch_bounds__(WAVE * EVAL_WPB) __attribute__((amdgpu_waves_per_eu(N >= 4 ? 3 : 4, 8))) void k_eval(
     FrameDev f, int tile_lo, int tile_hi, PieceStore ps, const int* __restrict__ pcount,
-                                               const float* __restrict__ tf_rgba, const void* __restrict__ moments,
-                                               BoundParams bp, float* __restrict__ rgba,
-                                               unsigned long long* ctr) {
+    const float* __restrict__ tf_rgba, const void* __restrict__ moments, BoundParams bp, float* __restrict__ rgba,
+    unsigned long long* ctr) {
   extern __shared__ float4 dyn_lds[];
-  float4* tf = dyn_lds;  // [n_tf] RGBA
-  constexpr int M1 = 2 * N + 1;
-  constexpr int NL = (N + 1) * (N + 2) / 2;
-  constexpr bool TABLES = N >= 3;
-  constexpr int TAB_ENTRIES = TABLES ? apcm::Gaps<N>::NODES * apcm::Gaps<N>::NC : 1;
-  __shared__ R li_all[EVAL_WPB][NL * WAVE];  // per-pixel inverse Cholesky factors, lane-minor
-  __shared__ R zs_all[EVAL_WPB][N * WAVE];   // per-pixel sorted zeros of the degree-N orthonormal polynomial
-  __shared__ R b0_all[EVAL_WPB][WAVE], z1_all[EVAL_WPB][WAVE];
-  __shared__ R tab_all[EVAL_WPB][TAB_ENTRIES];  // gap table of the pixel being evaluated
-  __shared__ int mode_all[EVAL_WPB][WAVE];
-  __shared__ int off_all[EVAL_WPB][WAVE + 1];  // piece offsets of the tile's pixels, relative to the tile
-  for (int i = threadIdx.x; i < f.n_tf; i += WAVE * EVAL_WPB)
-    tf[i] = make_float4(tf_rgba[4 * i], tf_rgba[4 * i + 1], tf_rgba[4 * i + 2], tf_rgba[4 * i + 3]);
-  __syncthreads();  // the only workgroup barrier: every later wait is within a wavefront
+  float4* tf = dyn_lds;  // [n_tf + 1] RGBA
+  __shared__ R zs_all[EVAL_WPB][N >= 3 ? N * WAVE : 1];
+  for (int i = threadIdx.x; i <= f.n_tf; i += WAVE * EVAL_WPB) {  // (the last entry twice)
+    const float* e = tf_rgba + 4 * min(i, f.n_tf - 1);
+    tf[i] = make_float4(e[0], e[1], e[2], e[3]);
+  }
+  __syncthreads();  // the only workgroup barrier
   const int wv = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
   const int tile = tile_lo + xcd_tile(blockIdx.x, gridDim.x, (XCD_RUN + EVAL_WPB - 1) / EVAL_WPB) * EVAL_WPB + wv;
   if (tile >= tile_hi) return;
-  R* li_lds = li_all[wv];
-  R* zs_lds = zs_all[wv];
-  R* b0_lds = b0_all[wv];
-  R* z1_lds = z1_all[wv];
-  R* tab_lds = tab_all[wv];
-  int* mode_lds = mode_all[wv];
-  int* off_lds = off_all[wv];
   const int tx = tile % f.tiles_x, ty = tile / f.tiles_x;
   const int px = (tx << f.tw_log2) + (lane & ((1 << f.tw_log2) - 1)),
             py = ty * (WAVE >> f.tw_log2) + (lane >> f.tw_log2);
   const bool valid = px < f.W && py < f.H;
   const size_t HW = size_t(f.W) * f.H, pix = size_t(py) * f.W + px;
-  const size_t slot0 = size_t(tile) * WAVE;
-  // per-pixel offsets within the tile: scan of the piece counts.  A lane of stage one that could not keep
-  // its pieces leaves its chunk table unset: then nothing is read (counted)
+  const size_t slot = size_t(tile) * WAVE + lane;
+  // a lane of stage one that could not keep its pieces leaves its chunk table unset: then nothing is read (counted)
   const bool staged = ps.next[1] == 0;
-  {
-    int c = staged ? pcount[slot0 + lane] : 0;
-    const int own = c;
-    for (int o = 1; o < WAVE; o <<= 1) {
-      const int up = __shfl_up(c, o, WAVE);
-      if (lane >= o) c += up;
-    }
-    off_lds[lane] = c - own;
-    if (lane == WAVE - 1) off_lds[WAVE] = c;
-  }
   LaneCount cnt = {};
   cnt.ctr = ctr;
   if (!staged && lane == 0) cnt.rare(C_OVERFLOW);
-  // per-pixel part of Alg. 3, once per pixel instead of once per sample
-  float b0f = 0.0f;
-  {
-    LdsBound<N, R> bound;
-    bound.Li.base = li_lds + lane;
-    R b[M1], bias[2 * N], zs[N];
-    b0f = pixel_moments<N, R>(moments, bp.moments_f16, valid, pix, HW, b);
-#pragma unroll
-    for (int j = 0; j < 2 * N; ++j) bias[j] = R(bp.bias[j]);
-    cnt.nonpd += bound.setup(b, R(bp.alpha), bias, zs);
-    b0_lds[lane] = bound.b0;
-    z1_lds[lane] = bound.z1;
-#pragma unroll
-    for (int i = 0; i < N; ++i) zs_lds[i * WAVE + lane] = zs[i];
-    mode_lds[lane] = valid ? bound.mode : 0;
-  }
-  wave_sync();
-  const R eta = R(bp.eta);
-  float4 mine = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  for (int p = 0; p < WAVE; ++p) {  // uniform loop over the tile's pixels
-    const int lo = off_lds[p], hi = off_lds[p + 1];
-    const int md = mode_lds[p];
-    if (lo == hi || md == 0) continue;
-    // the pixel's factor, uniform over the wavefront: held in scalar registers
-    apcm::Bound<N, R> bound;
-#pragma unroll
-    for (int k = 0; k < NL; ++k) bound.Li[k] = wave_uniform(li_lds[k * WAVE + p]);
-    bound.b0 = b0_lds[p];
-    bound.z1 = z1_lds[p];
-    bound.mode = md;
-    const apcm::StridedStore<N, R, WAVE> zs{zs_lds + p};
-    bound.xlo = md == 2 ? zs[0] : R(1);
-    bound.xhi = md == 2 ? zs[N - 1] : R(-1);
-    // no zeros found (never expected for a positive definite factor): no shortcut, no table
-    if (md == 2 && !(zs[0] < zs[N - 1])) {
-      bound.xlo = R(1);
-      bound.xhi = R(-1);
-    }
-    bool use_table = false;
-    if constexpr (TABLES) {
-      use_table = md == 2 && bound.xlo < bound.xhi && hi - lo >= APC_TABLE_MIN_PIECES;
-      if (use_table) {
-        apcm::TablePtr<N, R> tab{tab_lds};
-        if (lane < apcm::Gaps<N>::NODES) bound.gap_node(zs, lane, tab);
-        wave_sync();
+  apcm::Bound<N, R> bound;
+  const apcm::StridedStore<N, R, WAVE> zs{zs_all[wv] + lane};
+  typename apcm::Bound<N, R>::Cont cont;
+  const float b0f = pixel_bound<N, R>(moments, bp, valid, pix, HW, bound, zs, cont, cnt);
+  // (no absorbance on the ray: every piece has a = 0)
+  const int np = staged && valid && bound.mode != 0 ? min(pcount[slot], ps.maxc * PIECE_CHUNK) : 0;
+  const int* chunks = ps.ptab + slot * size_t(ps.maxc);
+  const R eta = R(bp.eta), exponent = bound.b0 * R(-1.4426950408889634074);
+  float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
+  unsigned solved = 0u, fresh = 0u, closed_used = 0u;
+  constexpr int BATCH = N >= 3 ? 1 : 4;  // pieces read at once
+  int at = 0;                            // the next batch; read ahead:
+  int ahead = np > 0 ? chunks[0] : 0;    // the id of the chunk after the one being read
+  const float* chunk = ps.pool;          // the chunk being read
+  float next[3 * BATCH] = {};            // z, a, s of each piece
+  auto fetch = [&]() {
+    if (at >= np) return;
+    const int i = at & (PIECE_CHUNK - 1);
+    if (i == 0) {
+      if (unsigned(ahead) >= unsigned(ps.n_chunks)) {  // cannot happen when every lane kept its pieces; never read
+        cnt.rare(C_OVERFLOW);
+        ahead = 0;
       }
+      chunk = ps.pool + size_t(ahead) * (PIECE_CHUNK * 3);
+      ahead = at + PIECE_CHUNK < np ? chunks[at / PIECE_CHUNK + 1] : 0;
     }
-    float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
-    const int* chunks = ps.ptab + (slot0 + p) * size_t(ps.maxc);
-    // the pixel's first 64 chunk ids, one per lane, fetched before the loop
-    const int n_ch = (hi - lo + PIECE_CHUNK - 1) / PIECE_CHUNK;
-    const int my_ch = (lane < n_ch && lane < ps.maxc) ? chunks[lane] : 0;
-    // the piece of step ib for this lane (z, a, s), or ok = false past the pixel's end.  Steps start at
-    // lo + 64 k and a chunk holds 64 pieces, so a step's pieces are exactly chunk k of the pixel: its id is
-    // the same for the whole wavefront (a scalar), and lane l reads the chunk's l-th record
-    static_assert(PIECE_CHUNK == WAVE, "one evaluation step reads one chunk");
-    auto fetch = [&](int ib, float& z, float& a, float& s, bool& ok) {
-      ok = ib + lane < hi;
-      const int k = (ib - lo) / PIECE_CHUNK;  // uniform
-      const int ch = k < WAVE ? __builtin_amdgcn_readlane(my_ch, k) : __builtin_amdgcn_readfirstlane(chunks[k]);
-      if (unsigned(ch) >= unsigned(ps.n_chunks)) {  // cannot happen when every lane kept its pieces; never read
-        if (ok) cnt.rare(C_OVERFLOW);
-        ok = false;
-        return;
-      }
-      const float* pr = ps.pool + (size_t(ch) * PIECE_CHUNK + lane) * 3;
-      if (!ok) return;
-      z = pr[0];
-      a = pr[1];
-      s = pr[2];
+#pragma unroll
+    for (int k = 0; k < 3 * BATCH; ++k) next[k] = chunk[3 * i + k];  // (a chunk is whole batches)
+  };
+  static_assert(PIECE_CHUNK % BATCH == 0, "a chunk is whole batches");
+  fetch();
+  // the colour sums: FP32 over 8 pieces (every lane's at the same time), then FP64
+  double sum[4] = {};
+  auto flush = [&]() {
+    sum[0] += double(a0);
+    sum[1] += double(a1);
+    sum[2] += double(a2);
+    sum[3] += double(a3);
+    a0 = a1 = a2 = a3 = 0.0f;
+  };
+  while (true) {
+    R z = R(0);
+    float a = 0.0f, fr = 0.0f;
+    int i0 = 0;
+    auto add = [&](R F, bool now) {  // the piece's colour, weighted
+      const float T = fminf(__builtin_amdgcn_exp2f(float(exponent * F)), 1.0f);
+      const float w = now ? T * opacity(a) : 0.0f;
+      const float4 c0 = tf[i0], c1 = tf[i0 + 1];
+      a0 = fmaf(w, fmaf(fr, c1.x - c0.x, c0.x), a0);
+      a1 = fmaf(w, fmaf(fr, c1.y - c0.y, c0.y), a1);
+      a2 = fmaf(w, fmaf(fr, c1.z - c0.z, c0.z), a2);
+      a3 += w;
     };
-    float nz = 0.0f, na = 0.0f, ns = 0.0f;
-    bool nok = false;
-    if (lo < hi) fetch(lo, nz, na, ns, nok);
-    for (int ib = lo; ib < hi; ib += WAVE) {  // uniform loop; the next step's piece is loaded first
-      const float z = nz, a = na, s = ns;
-      const bool ok = nok;
-      if (ib + WAVE < hi) fetch(ib + WAVE, nz, na, ns, nok);
-      if (!ok) continue;
-      R F = R(0);
-      bool closed = true;
-      if constexpr (TABLES) {
-        if (use_table) {
-          closed = !bound.frac_before_tab(R(z), eta, zs, apcm::TablePtr<N, R>{tab_lds}, F);
-          cnt.w_tabled += __popcll(ballot(true));
-          cnt.w_fallback += __popcll(ballot(closed));
+    bool unsettled = false;
+    while (ballot(at < np)) {  // a batch per lane
+      if (at < np) {
+        float now[3 * BATCH];
+#pragma unroll
+        for (int k = 0; k < 3 * BATCH; ++k) now[k] = next[k];
+        const int left = np - at;
+        if ((at & 7) == 0) flush();
+        at += BATCH;
+        fetch();
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) {
+          if (k > 0 && k >= left) continue;
+          z = R(now[3 * k]);
+          a = now[3 * k + 1];
+          tf_coord(f, now[3 * k + 2], i0, fr);
+          R F;
+          if constexpr (N >= 3) {
+            unsettled = !bound.frac_continued(z, eta, zs, cont, F, solved, fresh);
+          } else {
+            F = bound.frac_before(z, eta);
+          }
+          add(F, !unsettled);
         }
       }
-      if (closed) F = bound.frac_before(R(z), eta);  // the one inlined copy of the closed forms
-      float T = __expf(-float(bound.b0 * F));
-      T = fminf(fmaxf(T, 0.0f), 1.0f);
-      int i0;
-      float fr;
-      tf_coord(f, s, i0, fr);
-      const float4 t0 = tf[i0], t1 = tf[min(i0 + 1, f.n_tf - 1)];
-      const float w = T * opacity(a);
-      a0 += w * lerp_nc(t0.x, t1.x, fr);
-      a1 += w * lerp_nc(t0.y, t1.y, fr);
-      a2 += w * lerp_nc(t0.z, t1.z, fr);
-      a3 += w;
+      if constexpr (N >= 3) {
+        if (ballot(unsettled)) break;
+      }
     }
-    if (use_table) wave_sync();  // the next pixel's table overwrites this one
-    a0 = wave_sum_f(a0);
-    a1 = wave_sum_f(a1);
-    a2 = wave_sum_f(a2);
-    a3 = wave_sum_f(a3);
-    if (lane == p) mine = make_float4(a0, a1, a2, a3);
+    if constexpr (N >= 3) {
+      if (ballot(unsettled)) {  // the closed forms, out of line: not inside the loop
+        if (unsettled) {
+          add(bound.frac_closed(z, eta, zs, cont), true);
+          ++closed_used;
+        }
+        continue;
+      }
+    }
+    break;
   }
-  if (valid) reinterpret_cast<float4*>(rgba)[pix] = finalize_px(mine, b0f, bp.finalize, bp.renormalize);
+  cnt.w_tabled += wave_sum(solved);
+  cnt.w_fallback += wave_sum(closed_used);
+  flush();
+  if (valid)
+    reinterpret_cast<float4*>(rgba)[pix] =
+        finalize_px(make_float4(float(sum[0]), float(sum[1]), float(sum[2]), float(sum[3])), b0f, bp.finalize,
+                    bp.renormalize);
   flush_counts(cnt, ctr);
 }
 
@@ -1198,7 +1158,8 @@ __global__ __launch_bounds__(WAVE * EVAL_WPB) __attribute__((amdgpu_waves_per_eu
 // evaluator's vector instructions: it waits at 5 % of the boundaries' time, the
 // walker at 55 %, and two evaluators to a walker were slower (39 ms against 33
 // at the largest frame below), as were evaluators and walkers on swapped SIMDs.
-// Measured, m = 8, 2560^2 on 12.6M tets: 41.8 ms with pieces in the ring, 33.2 now.
+// Measured, m = 8: 2560^2 on 12.6M tets 41.8 ms with pieces in the ring, 33.4 now;
+// 1024^2 on 1.6M tets in 72 uneven subdomains 5.07, 3.93.
 //
 // The pair's shape for n = N roots: wavefronts per SIMD the kernel is compiled for (register budget 512 / n),
 // slots of the ring (one bit each in half a word) and evaluation rounds (one piece per lane) per phase at most.
@@ -1372,35 +1333,15 @@ __global__ __launch_bounds__(2 * WAVE) __attribute__((amdgpu_waves_per_eu(PairSh
     q.boundary(true);
   } else {
     const size_t HW = size_t(f.W) * f.H, pix = size_t(py) * f.W + px;
-    // per-pixel part of Alg. 3, once per pixel instead of once per sample; the bound and the continuation are
-    // separate locals (a structure holding a run-time indexed array would live in scratch), the zeros live in
-    // LDS (8 registers less across the loop)
+    // the bound and the continuation are separate locals (a structure holding a run-time indexed array would live
+    // in scratch)
     apcm::Bound<N, R> bound;
     const apcm::StridedStore<N, R, WAVE> zs{zs_lds + lane};
     typename apcm::Bound<N, R>::Cont cont;
-    cont.k = -1;
-#pragma unroll
-    for (int c = 0; c < int(sizeof(cont.v) / sizeof(R)); ++c) cont.v[c] = R(0);
-    float b0f;
-    {
-      R b[2 * N + 1], bias[2 * N], zsr[N];
-      b0f = pixel_moments<N, R>(moments, bp.moments_f16, valid, pix, HW, b);
-#pragma unroll
-      for (int j = 0; j < 2 * N; ++j) bias[j] = R(bp.bias[j]);
-      cnt.nonpd += bound.setup(b, R(bp.alpha), bias, zsr);
-      // no zeros found (never expected for a positive definite factor): no shortcut, every sample solves
-      if (bound.mode == 2 && !(zsr[0] < zsr[N - 1])) {
-        bound.xlo = zsr[0] = -R(HUGE_VAL);
-        bound.xhi = zsr[N - 1] = R(HUGE_VAL);
-      }
-      if constexpr (N >= 3) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) zs[i] = zsr[i];
-      }
-    }
+    const float b0f = pixel_bound<N, R>(moments, bp, valid, pix, HW, bound, zs, cont, cnt);
     const R eta = R(bp.eta);
     float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
-    unsigned solved = 0u, closed_used = 0u;  // samples needing roots; of those, by the closed forms
+    unsigned solved = 0u, fresh = 0u;  // samples needing roots; of those, in another gap than the last
     const R exponent = bound.b0 * R(-1.4426950408889634074);
     unsigned head = 0u, ready = 0u, starts = 0u;  // records taken; records to take; which of them are starts
     int parity = 0, n = 0;
@@ -1454,10 +1395,7 @@ __global__ __launch_bounds__(2 * WAVE) __attribute__((amdgpu_waves_per_eu(PairSh
             z = R(piece_z(f, wt));
             R F;
             if constexpr (N >= 3) {
-              int how;
-              unsettled = !bound.frac_continued(z, eta, zs, cont, F, how);
-              solved += how != 0 ? 1u : 0u;
-              closed_used += how == 2 ? 1u : 0u;
+              unsettled = !bound.frac_continued(z, eta, zs, cont, F, solved, fresh);
             } else {
               F = bound.frac_before(z, eta);
             }
@@ -1485,10 +1423,8 @@ __global__ __launch_bounds__(2 * WAVE) __attribute__((amdgpu_waves_per_eu(PairSh
       n = 0;
       fetch();
     }
-    solved = wave_sum(solved);
-    closed_used = wave_sum(closed_used);
-    cnt.w_tabled += solved;
-    cnt.w_fallback += closed_used;
+    cnt.w_tabled += wave_sum(solved);
+    cnt.w_fallback += wave_sum(fresh);
     if constexpr (PAIRS) {  // [pairs][4][64], every lane
       float* o = part + size_t(pair) * 4 * WAVE + lane;
       o[0] = a0;
@@ -2104,7 +2040,7 @@ hipError_t launch_eval(int mm, const FrameDev& f, int tile_lo, int tile_hi, cons
                        const int* pcount, const float* tf_rgba, const void* moments, const BoundParams& bp,
                        float* rgba, unsigned long long* counters, hipStream_t s) {
   if (tile_hi <= tile_lo) return hipSuccess;
-  const size_t lds = size_t(f.n_tf) * sizeof(float4);
+  const size_t lds = size_t(f.n_tf + 1) * sizeof(float4);
   const dim3 grid((tile_hi - tile_lo + EVAL_WPB - 1) / EVAL_WPB), block(WAVE * EVAL_WPB);
   if (mm == 4)
     hipLaunchKernelGGL((k_eval<2, float>), grid, block, lds, s, f, tile_lo, tile_hi, store, pcount, tf_rgba, moments,

@@ -105,3 +105,27 @@ def test_smallest_and_largest_tables(apc, ctx, entries, m):
     lo, hi = sc.s_min, sc.s_max
     sc.s_min, sc.s_max = lo + 0.25 * (hi - lo), lo + 0.75 * (hi - lo)
     _check_frame(apc, ctx, sc, oracle.render(sc))
+
+
+@pytest.mark.parametrize("m", [4, 6, 8])
+@pytest.mark.parametrize("per_cell", [0.01, 0.5, 12.0])
+def test_kept_pieces_of_uneven_rays(apc, ctx, m, per_cell):
+    """Kept pieces evaluated a lane per pixel: rays of no piece, of a few (less than a batch of 4, a group of 8
+    or a chunk of 64) and of many chunks side by side in a tile, against the oracle and the plain form (whose
+    colour sums are FP32 throughout: the bar of the other forms, 2e-5)."""
+    sc = _with_order(synth.scene_tiny(), m)
+    sc.view = synth.perspective_view(synth.sphere_eye(5), (0.5, 0.5, 0.5), 61, 43)
+    sc.step = 1.0 / 16 / per_cell
+    ref = oracle.render(sc)
+    r = apc.Renderer(ctx, sc)
+    for _ in range(3):  # the first frames size the piece pool
+        r.rgba.fill_(-1.0)
+        r.frame(global_sum=True, keep=True)
+    torch.cuda.synchronize()
+    assert ctx.timings()["eval_ms"] > 0
+    kept = r.rgba.clone()
+    d = _np(kept).reshape(-1, 4) - ref["rgba"]
+    assert np.abs(d).max() <= 2e-3 and math.sqrt(np.mean(d ** 2)) <= 5e-4
+    r.frame(global_sum=True)
+    torch.cuda.synchronize()
+    assert float((r.rgba - kept).abs().max()) <= 2e-5
