@@ -161,7 +161,8 @@ struct apc_ctx_s {
   int dispatch = APC_DISPATCH_GRID;  // how both passes spread their tiles (apc_set_dispatch)
   DevBuf queue;                      // the work queue's per-XCD tile counters (APC_DISPATCH_QUEUE)
   DevBuf pidx;                       // tiles form: the pair number of each (tile, slot) bin
-  DevBuf rpair, rpart;               // stage two by pairs: the pairs' bins, their colour sums [pairs][4][64]
+  DevBuf rpair, rpart;               // passes by pairs: the pairs' bins, stage two's colour sums [pairs][4][64]
+  DevBuf mtile;                      // stage one by pairs: the pairs' moments [pairs][m+1][64]
   // the (tile, slot) bins in counts / offsets / records / slots were made for this mesh, view, tile shape
   // and subdomain list (stage two of a frame reuses stage one's)
   bool bins_valid = false;
@@ -680,7 +681,7 @@ apc_status apc_destroy(apc_ctx ctx) {
   (void)hipDeviceSynchronize();
   for (DevBuf* b : {&ctx->counts, &ctx->offsets, &ctx->cursors, &ctx->records, &ctx->scan_tmp, &ctx->slots,
                     &ctx->order, &ctx->counters, &ctx->pcount, &ctx->segs, &ctx->gacc, &ctx->queue, &ctx->pidx,
-                    &ctx->rpair, &ctx->rpart, &ctx->pool, &ctx->ptab, &ctx->store_next})
+                    &ctx->rpair, &ctx->rpart, &ctx->mtile, &ctx->pool, &ctx->ptab, &ctx->store_next})
     b->release();
   if (ctx->staging) (void)hipHostFree(ctx->staging);
   if (ctx->staging_done) (void)hipEventDestroy(ctx->staging_done);
@@ -982,6 +983,51 @@ static bool grow_piece_store(apc_ctx ctx, size_t slots) {
   return ctx->store_next.ensure(4 * sizeof(unsigned long long)) == hipSuccess;
 }
 
+// Stage one of frames of few tiles runs by pairs: a workgroup per (tile, subdomain) pair with binned faces, since
+// a workgroup per tile walks every subdomain on its rays in turn and the device waits for the longest chains.
+// The same moments bit for bit (each pair is the same walk, the sum takes the slots in the same order).  Measured,
+// per tile and by pairs, ms: 256^2 on 1.6M tets in 16 subdomains 0.93, 0.30; 512^2 0.85, 0.42; 768^2 0.93, 0.67; 1024^2
+// (16384 tiles) 1.12, 1.03; 1280^2 1.52, 1.47: beyond it is the larger buffers for little.  Pieces are kept in one
+// order per pixel, so not with APC_KEEP_PIECES; a work queue is of tiles.
+static constexpr int STAGE_ONE_PAIR_TILES = 16384;
+// ... and while the pairs' moments (the sum's input; per-subdomain images need none) stay below this.
+static constexpr size_t STAGE_ONE_PAIR_BYTES = size_t(64) << 20;
+
+// The buffers of stage one by pairs; false: too large, or not to be had (the per-tile form needs none of them).
+static bool pairs_fit(apc_ctx ctx, int mm, bool global) {
+  const size_t pairs = size_t(std::max<int64_t>(ctx->bin_pairs, 1)), bytes = sizeof(float) * 64 * (mm + 1) * pairs;
+  if (global && bytes > STAGE_ONE_PAIR_BYTES) return false;
+  const bool ok = ctx->rpair.ensure(sizeof(int) * pairs) == hipSuccess &&
+                  (!global || ctx->mtile.ensure(bytes) == hipSuccess);
+  if (!ok) (void)hipGetLastError();
+  return ok;
+}
+
+static apc_status moments_by_pair(apc_ctx ctx, const apc_view* view, const apc_tf* tf, int mm, const MeshDev& md,
+                                  const FrameDev& f, int n_sub, float* out, bool global, hipStream_t s) {
+  const int64_t nb = int64_t(f.n_tiles) * n_sub, pairs = ctx->bin_pairs, HW = int64_t(view->width) * view->height;
+  HIPCHK(ctx->segs.ensure(sizeof(int) * 2 * size_t(HW)));
+  ctx->seg_h = view->height;
+  ctx->seg_w = view->width;
+  HIPCHK(apc::launch_pair_list(ctx->counts.as<int>(), nb, ctx->pidx.as<int>(), ctx->rpair.as<int>(), pairs, s));
+  HIPCHK(ev_mark(ctx, EV_MOM, 0, s));
+  HIPCHK(apc::launch_fill_i32(ctx->segs.as<int>(), 0, 2 * HW, s));
+  if (global)
+    ctx->ev_used[EV_SUM] = false;  // its time is the stage's
+  else
+    HIPCHK(apc::launch_fill_i32(reinterpret_cast<int*>(out), 0, int64_t(n_sub) * (mm + 1) * HW, s));
+  HIPCHK(apc::launch_moments(mm, md, f, ctx->slots.as<SlotDev>(), ctx->offsets.as<int>(), ctx->counts.as<int>(),
+                             ctx->records.as<int>(), bin_cap(ctx), tf->rgba, global ? ctx->mtile.as<float>() : out,
+                             nullptr, nullptr, ctx->segs.as<int>(), apc::PieceStore{},
+                             ctx->counters.as<unsigned long long>(), nullptr, global ? ctx->pidx.as<int>() : nullptr,
+                             ctx->rpair.as<int>(), pairs, s));
+  if (global)
+    HIPCHK(apc::launch_sum_tiles(ctx->mtile.as<float>(), ctx->rpair.as<int>(), pairs, n_sub, mm + 1, f.W, f.H,
+                                 ctx->tw_log2, out, s));
+  HIPCHK(ev_mark(ctx, EV_MOM, 1, s));
+  return APC_OK;
+}
+
 apc_status apc_moments_pass(apc_ctx ctx, apc_mesh m, const apc_view* view, const apc_tf* tf, int32_t mm,
                             const int32_t* subs, int32_t n_sub, float* out, uint32_t flags, void* stream) {
   apc_status st = check_ctx(ctx);
@@ -1001,7 +1047,14 @@ apc_status apc_moments_pass(apc_ctx ctx, apc_mesh m, const apc_view* view, const
   if (ctx->host_only) return no_device("apc_moments_pass");
   hipStream_t s = static_cast<hipStream_t>(stream);
   MeshDev md;
-  if ((st = build_bins(ctx, m, view, f, subs, n_sub, false, s, md)) != APC_OK) return st;
+  const bool few = f.n_tiles <= STAGE_ONE_PAIR_TILES && ctx->dispatch == APC_DISPATCH_GRID && !(flags & APC_KEEP_PIECES);
+  if ((st = build_bins(ctx, m, view, f, subs, n_sub, few, s, md)) != APC_OK) return st;
+  if (few && pairs_fit(ctx, mm, global)) {
+    ctx->store_ready = false;
+    if ((st = moments_by_pair(ctx, view, tf, mm, md, f, n_sub, out, global, s)) != APC_OK) return st;
+    set_piece_key(ctx, m, view, subs, n_sub);
+    return APC_OK;
+  }
   HIPCHK(ctx->pcount.ensure(sizeof(int) * size_t(f.n_tiles) * 64));
   // keep the pieces for stage two unless asked not to (or the pool cannot be had)
   apc::PieceStore ps = {};
@@ -1078,7 +1131,7 @@ apc_status moments_tiles(apc_ctx ctx, apc_mesh m, const apc_view* view, const ap
     ctx->seg_h = view->height;
     ctx->seg_w = view->width;
   }
-  HIPCHK(apc::launch_pair_list(ctx->counts.as<int>(), nb, ctx->pidx.as<int>(), pair_bin, s));
+  HIPCHK(apc::launch_pair_list(ctx->counts.as<int>(), nb, ctx->pidx.as<int>(), pair_bin, pairs, s));
   HIPCHK(ev_mark(ctx, EV_MOM, 0, s));
   HIPCHK(apc::launch_moments(mm, md, f, ctx->slots.as<SlotDev>(), ctx->offsets.as<int>(), ctx->counts.as<int>(),
                              ctx->records.as<int>(), bin_cap(ctx), tf->rgba, tiles, nullptr,
@@ -1269,7 +1322,7 @@ static apc_status resolve_frame(apc_ctx ctx, apc_mesh m, const apc_view* view, c
     const int64_t nb = int64_t(f.n_tiles) * n_sub, pairs = ctx->bin_pairs;
     HIPCHK(ctx->rpair.ensure(sizeof(int) * size_t(std::max<int64_t>(pairs, 1))));
     HIPCHK(ctx->rpart.ensure(sizeof(float) * 4 * 64 * size_t(std::max<int64_t>(pairs, 1))));
-    HIPCHK(apc::launch_pair_list(ctx->counts.as<int>(), nb, ctx->pidx.as<int>(), ctx->rpair.as<int>(), s));
+    HIPCHK(apc::launch_pair_list(ctx->counts.as<int>(), nb, ctx->pidx.as<int>(), ctx->rpair.as<int>(), pairs, s));
     HIPCHK(ev_mark(ctx, EV_STG, 0, s));
     HIPCHK(apc::launch_resolve(mb->m, md, f, ctx->slots.as<SlotDev>(), ctx->offsets.as<int>(),
                                ctx->counts.as<int>(), ctx->records.as<int>(), bin_cap(ctx), tf->rgba, moments, bp,
@@ -1460,7 +1513,7 @@ apc_status apc_get_workspace_bytes(apc_ctx ctx, int64_t* bytes) {
   int64_t total = 0;
   for (const DevBuf* b : {&ctx->counts, &ctx->offsets, &ctx->cursors, &ctx->records, &ctx->scan_tmp, &ctx->slots,
                           &ctx->order, &ctx->counters, &ctx->pcount, &ctx->segs, &ctx->gacc, &ctx->queue, &ctx->pidx,
-                          &ctx->rpair, &ctx->rpart, &ctx->pool, &ctx->ptab, &ctx->store_next})
+                          &ctx->rpair, &ctx->rpart, &ctx->mtile, &ctx->pool, &ctx->ptab, &ctx->store_next})
     total += int64_t(b->bytes);
   *bytes = total;
   return APC_OK;

@@ -111,8 +111,9 @@ hipError_t launch_moments(int mm, const MeshDev& m, const FrameDev& f, const Slo
                           unsigned long long* counters, int* queue, const int* pair_idx, const int* pair_list,
                           int64_t n_pairs, hipStream_t s);
 // pair_idx (tiles form, gacc null): per bin with faces its pair number; out is then [pairs][m+1][64]
-// (lane-minor), every lane of every pair written.  pair_list (tiles form, may be null): the bin of each of
-// the n_pairs pairs; a workgroup per pair then walks that pair alone (pcount and segs must be null)
+// (lane-minor), every lane of every pair written.  pair_list (may be null; gacc must be null): the bin of each of
+// the n_pairs pairs; a workgroup per pair then walks that pair alone (pcount must be null; segs and, without
+// pair_idx, out must hold zeros: what no pair covers stays, and a pixel's segments are added up)
 // queue (both passes): null for one workgroup per tile; else QUEUE_INTS device ints that the launch
 // resets and a persistent launch (as many workgroups as the device holds) takes the tiles from
 constexpr int QUEUE_INTS = 8;
@@ -150,8 +151,9 @@ hipError_t launch_exclusive_scan(const int* in, int* out, int64_t n, int* tmp, h
 // tmp: scan_tmp_elems(nb) ints, 8-byte aligned.
 hipError_t launch_bin_scan(const int* counts, int64_t nb, int* offsets, int* cursors, int* pidx, int* tmp,
                            unsigned long long* totals, hipStream_t s);
-// pair_bin[p] = the bin of pair p
-hipError_t launch_pair_list(const int* counts, int64_t nb, const int* pidx, int* pair_bin, hipStream_t s);
+// pair_bin[p] = the bin of pair p < n_pairs
+hipError_t launch_pair_list(const int* counts, int64_t nb, const int* pidx, int* pair_bin, int64_t n_pairs,
+                            hipStream_t s);
 // global [m1][H][W] moments from n_pairs tiles (pair_bin ascending, n_slots slots per tile, ascending ids)
 hipError_t launch_sum_tiles(const float* tiles, const int* pair_bin, int64_t n_pairs, int n_slots, int m1, int W,
                             int H, int tw_log2, float* out, hipStream_t s);

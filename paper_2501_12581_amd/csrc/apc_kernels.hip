@@ -869,7 +869,7 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(APC_WALK_W
       }
     } else if (pair_idx) {  // tiles form: only pairs with binned faces, every lane (zeros outside the image)
       if (n_rec > 0) {
-        const int p = pair_idx[bin];
+        const int p = !QUEUE && pair_list ? int(blockIdx.x) : pair_idx[bin];
         float* o = out + size_t(p) * M1 * WAVE + lane;
 #pragma unroll
         for (int j = 0; j < M1; ++j) o[j * WAVE] = float(sink.b[j]);
@@ -901,8 +901,13 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(APC_WALK_W
   }
   if (pcount) pcount[size_t(tile) * WAVE + lane] = int(cnt.pieces);
   if (segs && valid) {  // [2][H][W]: segments, covering subdomains
-    segs[pix] = int(cnt.segments);
-    segs[HW + pix] = covering;
+    if (!QUEUE && pair_list) {  // a part of the pixel's, onto zeros
+      if (cnt.segments) atomicAdd(segs + pix, int(cnt.segments));
+      if (covering) atomicAdd(segs + HW + pix, covering);
+    } else {
+      segs[pix] = int(cnt.segments);
+      segs[HW + pix] = covering;
+    }
   }
   flush_counts(cnt, ctr);
   }  // tiles
@@ -1617,9 +1622,9 @@ __global__ void k_sum_moments(const float* __restrict__ in, int n_slots, const i
 // A bin b = tile * n_slots + slot with binned faces is a pair; pidx[b] numbers them in bin order, and pair_bin
 // lists their bins in that order.
 __global__ void k_pair_list(const int* __restrict__ counts, int64_t nb, const int* __restrict__ pidx,
-                            int* __restrict__ pair_bin) {
+                            int* __restrict__ pair_bin, int64_t n_pairs) {
   const int64_t b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (b < nb && counts[b] > 0) pair_bin[pidx[b]] = int(b);
+  if (b < nb && counts[b] > 0 && pidx[b] < n_pairs) pair_bin[pidx[b]] = int(b);
 }
 
 // A tile's pairs are contiguous in pair_bin (ascending): the first one with a bin >= first_bin, searched by the
@@ -2125,9 +2130,10 @@ hipError_t launch_bin_scan(const int* counts, int64_t nb, int* offsets, int* cur
   return hipGetLastError();
 }
 
-hipError_t launch_pair_list(const int* counts, int64_t nb, const int* pidx, int* pair_bin, hipStream_t s) {
-  if (nb <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pair_list, dim3(grid1(nb, 256)), dim3(256), 0, s, counts, nb, pidx, pair_bin);
+hipError_t launch_pair_list(const int* counts, int64_t nb, const int* pidx, int* pair_bin, int64_t n_pairs,
+                            hipStream_t s) {
+  if (nb <= 0 || n_pairs <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_pair_list, dim3(grid1(nb, 256)), dim3(256), 0, s, counts, nb, pidx, pair_bin, n_pairs);
   return hipGetLastError();
 }
 

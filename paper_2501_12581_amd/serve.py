@@ -29,6 +29,10 @@ import numpy as np
 
 from . import Context, make_mboit, make_tf, make_view
 
+# the library walks stage one of a frame of at most so many tiles by pairs by itself, into buffers of at most so many
+# bytes (per-tile beyond either)
+LIBRARY_PAIR_TILES, LIBRARY_PAIR_BYTES = 16384, 64 << 20
+
 
 def look_at_view(eye, target, width: int, height: int, fovy_deg: float = 45.0) -> dict:
     """Pinhole camera frame for apc_view: un-normalised pixel direction dir + (j+1/2-W/2) right + (i+1/2-H/2) down."""
@@ -126,7 +130,10 @@ class Server:
                     torch.empty(cap * (self.max_m + 1) * 64, dtype=torch.float32, device=self.dev),
                     # as many bins as the FP32 buffer holds tiles of the smallest m (4)
                     torch.empty(cap * (self.max_m + 1) // 5, dtype=torch.int32, device=self.dev))
-            sizes = sorted({ps, self._pair_size(k, self.pair_max_tiles)} - {0, req["size"]}) if self.by_pair else []
+            sizes = {self._pair_size(k, LIBRARY_PAIR_TILES)}
+            if self.by_pair:
+                sizes |= {ps, self._pair_size(k, self.pair_max_tiles)}
+            sizes = sorted(sizes - {0, req["size"]})
             for _ in range(2):  # the second frame runs at the grown size
                 self.render(k, req)
                 for size in sizes:  # the largest frames by pairs of each pass size their buffers
@@ -140,7 +147,8 @@ class Server:
         partials, segment statistics, piece counts, binning state, and the piece pool when frames keep their
         pieces), so after warm() the workspace of every slot that could take the request is measured with
         apc_get_workspace_bytes and the largest is counted; before it, an estimate from the request's size
-        (8 (m+1) + 12 bytes per pixel, 12 bytes per (tile, subdomain) pair, 4 per binned face record -- two
+        (8 (m+1) + 12 bytes per pixel, 12 bytes per (tile, subdomain) pair -- and what walking by
+        pairs takes in a frame of few tiles --, 4 per binned face record -- two
         per boundary face, since a face's conservative pixel box can reach into a neighbouring tile -- with the
         library's growth slack, plus the pool limit when frames keep their pieces)."""
         size, m = req["size"], req["m"]
@@ -149,8 +157,10 @@ class Server:
         eligible = [k for k, s in enumerate(self.slot_size) if s >= size]
         if self.slot_ws is not None and eligible:
             return own + max(self.slot_ws[k] for k in eligible)
-        tiles = -(-size // 8) ** 2
+        tiles = (-(-size // 8)) ** 2
         ws = px * (8 * (m + 1) + 12) + tiles * 12 * self.n_sub + 4 * 2 * max(self.n_boundary_faces, 16 * tiles)
+        if tiles <= LIBRARY_PAIR_TILES:  # stage one by pairs inside the library: numbers, bins, moments of the pairs
+            ws += tiles * 8 * self.n_sub + min(tiles * self.n_sub * 256 * (m + 1), LIBRARY_PAIR_BYTES)
         ws = ws * 5 // 4 + (64 << 10)  # the library's buffers grow with a quarter of slack, 4 KiB at least
         if self.keep:
             ws += self.workspace_limit

@@ -46,3 +46,38 @@ def test_frames_are_those_of_a_fresh_context(apc, sizes):
             fresh.close()
     finally:
         shared.close()
+
+
+@pytest.mark.parametrize("W,H,n_sub,m", [
+    (1, 1, 1, 4), (61, 43, 5, 8), (200, 120, 16, 6),
+    (1024, 1024, 2, 4),    # 16384 tiles, the most that go by pairs; 32768 pairs of 1280 bytes
+    (1025, 1024, 2, 4),    # a column of tiles more: per tile
+    (1024, 1024, 16, 8),   # 262144 pairs, 604 MB of moments: per tile
+])
+def test_stage_one_of_few_tiles_by_pairs_is_the_per_tile_pass(apc, ctx, W, H, n_sub, m):
+    """A work queue takes whole tiles, the grid of a frame of few tiles (tile, subdomain) pairs: the same moments,
+    per subdomain and global, segment counts, images and counters, bit for bit; also for a subset in another
+    order."""
+    sc = _scene(W, H, n_sub)
+    sc.view = synth.perspective_view((0.5, 2.3, 0.9), (0.5, 0.5, 0.5), W, H)  # some tiles meet few subdomains
+    sc.m, sc.bias = m, synth.default_bias(m)
+    r = apc.Renderer(ctx, sc)
+    part = np.asarray([n_sub - 1] + list(range(0, n_sub - 1, 2)), np.int32)
+    got = {}
+    try:
+        for mode in (apc.APC_DISPATCH_QUEUE, apc.APC_DISPATCH_GRID):
+            ctx.set_dispatch(mode)
+            out = []
+            for kw in (dict(global_sum=True), dict(), dict(subdomains=part)):
+                ctx.counters(reset=True)
+                r.moments.fill_(-1.0)
+                r.per_sub.fill_(-1.0)
+                img = r.frame(**kw).clone()
+                c = ctx.counters()
+                out += [img, r.moments.clone(), r.per_sub.clone(), ctx.segment_counts(H, W),
+                        torch.tensor([c[k] for k in ("pieces", "tet_steps", "entries", "segments", "nonpd_pivots")])]
+            got[mode] = out
+    finally:
+        ctx.set_dispatch(apc.APC_DISPATCH_GRID)
+    for k, (a, b) in enumerate(zip(*got.values())):
+        assert torch.equal(a, b), k
