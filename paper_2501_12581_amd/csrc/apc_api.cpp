@@ -171,6 +171,7 @@ struct apc_ctx_s {
   int bin_tw = -1;
   std::vector<int> bin_subs;
   int64_t bin_pairs = -1;  // bins with records, numbered in pidx (-1: not numbered)
+  bool captured_bins = false;  // the graph being captured has binned the frame (its key is the eager frame's)
 };
 
 struct apc_graph_s {
@@ -480,13 +481,13 @@ apc_status bin_faces(apc_ctx ctx, const apc_mesh_s* m, const FrameDev& f, const 
 }
 
 // bin_faces into the context's growable buffers, unless they already hold the bins of this mesh, view, tile
-// shape and subdomain list (stage two after stage one of the same frame); a captured frame always bins.  With
-// `pairs` the bins with faces are numbered in ctx->pidx, ctx->bin_pairs of them.
+// shape and subdomain list (stage two after stage one of the same frame); a captured frame bins once, in its
+// stage one.  With `pairs` the bins with faces are numbered in ctx->pidx, ctx->bin_pairs of them.
 apc_status build_bins(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const FrameDev& f, const int32_t* subs,
                       int32_t n_sub, bool pairs, hipStream_t s, MeshDev& md) {
   const int64_t nb = int64_t(f.n_tiles) * n_sub;
   if (pairs) HIPCHK(ctx->pidx.ensure(sizeof(int) * nb));
-  if (!ctx->capturing && ctx->bins_valid && ctx->bin_mesh == m->uid && ctx->bin_tw == ctx->tw_log2 &&
+  if ((ctx->capturing ? ctx->captured_bins : ctx->bins_valid) && ctx->bin_mesh == m->uid && ctx->bin_tw == ctx->tw_log2 &&
       std::memcmp(&ctx->bin_view, v, sizeof(apc_view)) == 0 && ctx->bin_subs.size() == size_t(n_sub) &&
       std::equal(subs, subs + n_sub, ctx->bin_subs.begin())) {
     md.vert = m->vert;
@@ -494,7 +495,7 @@ apc_status build_bins(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const
     md.wrec = m->wrec;
     md.n_vertices = m->V;
     md.n_tets = m->T;
-    if (pairs && ctx->bin_pairs < 0) {  // binned without them
+    if (pairs && ctx->bin_pairs < 0 && !ctx->capturing) {  // binned without them
       HIPCHK(apc::launch_bin_scan(ctx->counts.as<int>(), nb, nullptr, nullptr, ctx->pidx.as<int>(),
                                   ctx->scan_tmp.as<int>(), ctx->totals, s));
       HIPCHK(hipEventRecord(ctx->totals_done, s));
@@ -513,6 +514,7 @@ apc_status build_bins(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const
                 ctx->scan_tmp.as<int>(), ctx->records.as<int>(), pairs ? ctx->pidx.as<int>() : nullptr, bin_cap(ctx),
                 true};
   const apc_status st = bin_faces(ctx, m, f, subs, n_sub, B, s, md);
+  if (ctx->capturing) ctx->captured_bins = st == APC_OK;
   if (st == APC_OK && !ctx->capturing) {
     ctx->bins_valid = true;
     ctx->bin_mesh = m->uid;
