@@ -1018,7 +1018,7 @@ static apc_status moments_by_pair(apc_ctx ctx, const apc_view* view, const apc_t
     ctx->ev_used[EV_SUM] = false;  // its time is the stage's
   else
     HIPCHK(apc::launch_fill_i32(reinterpret_cast<int*>(out), 0, int64_t(n_sub) * (mm + 1) * HW, s));
-  HIPCHK(apc::launch_moments(mm, md, f, ctx->slots.as<SlotDev>(), ctx->offsets.as<int>(), ctx->counts.as<int>(),
+  HIPCHK(apc::launch_moments(mm, md, f, ctx->offsets.as<int>(), ctx->counts.as<int>(),
                              ctx->records.as<int>(), bin_cap(ctx), tf->rgba, global ? ctx->mtile.as<float>() : out,
                              nullptr, nullptr, ctx->segs.as<int>(), apc::PieceStore{},
                              ctx->counters.as<unsigned long long>(), nullptr, global ? ctx->pidx.as<int>() : nullptr,
@@ -1084,7 +1084,7 @@ apc_status apc_moments_pass(apc_ctx ctx, apc_mesh m, const apc_view* view, const
     HIPCHK(ctx->gacc.ensure(sizeof(double) * size_t(mm + 1) * view->width * view->height));
     ctx->ev_used[EV_SUM] = false;  // no separate sum in this frame
   }
-  HIPCHK(apc::launch_moments(mm, md, f, ctx->slots.as<SlotDev>(), ctx->offsets.as<int>(), ctx->counts.as<int>(),
+  HIPCHK(apc::launch_moments(mm, md, f, ctx->offsets.as<int>(), ctx->counts.as<int>(),
                              ctx->records.as<int>(), bin_cap(ctx), tf->rgba, out,
                              global ? ctx->gacc.as<double>() : nullptr, ctx->pcount.as<int>(), ctx->segs.as<int>(), ps,
                              ctx->counters.as<unsigned long long>(), tile_queue(ctx), nullptr, nullptr, 0, s));
@@ -1135,7 +1135,7 @@ apc_status moments_tiles(apc_ctx ctx, apc_mesh m, const apc_view* view, const ap
   }
   HIPCHK(apc::launch_pair_list(ctx->counts.as<int>(), nb, ctx->pidx.as<int>(), pair_bin, pairs, s));
   HIPCHK(ev_mark(ctx, EV_MOM, 0, s));
-  HIPCHK(apc::launch_moments(mm, md, f, ctx->slots.as<SlotDev>(), ctx->offsets.as<int>(), ctx->counts.as<int>(),
+  HIPCHK(apc::launch_moments(mm, md, f, ctx->offsets.as<int>(), ctx->counts.as<int>(),
                              ctx->records.as<int>(), bin_cap(ctx), tf->rgba, tiles, nullptr,
                              by_pair ? nullptr : ctx->pcount.as<int>(), by_pair ? nullptr : ctx->segs.as<int>(),
                              apc::PieceStore{}, ctx->counters.as<unsigned long long>(),
@@ -1326,7 +1326,7 @@ static apc_status resolve_frame(apc_ctx ctx, apc_mesh m, const apc_view* view, c
     HIPCHK(ctx->rpart.ensure(sizeof(float) * 4 * 64 * size_t(std::max<int64_t>(pairs, 1))));
     HIPCHK(apc::launch_pair_list(ctx->counts.as<int>(), nb, ctx->pidx.as<int>(), ctx->rpair.as<int>(), pairs, s));
     HIPCHK(ev_mark(ctx, EV_STG, 0, s));
-    HIPCHK(apc::launch_resolve(mb->m, md, f, ctx->slots.as<SlotDev>(), ctx->offsets.as<int>(),
+    HIPCHK(apc::launch_resolve(mb->m, md, f, ctx->offsets.as<int>(),
                                ctx->counts.as<int>(), ctx->records.as<int>(), bin_cap(ctx), tf->rgba, moments, bp,
                                rgba, ctr, nullptr, ctx->rpair.as<int>(), ctx->rpart.as<float>(), pairs, s));
     HIPCHK(apc::launch_sum_color_tiles(ctx->rpart.as<float>(), ctx->rpair.as<int>(), pairs, n_sub, f.W, f.H,
@@ -1336,7 +1336,7 @@ static apc_status resolve_frame(apc_ctx ctx, apc_mesh m, const apc_view* view, c
     return APC_OK;
   }
   HIPCHK(ev_mark(ctx, EV_STG, 0, s));
-  HIPCHK(apc::launch_resolve(mb->m, md, f, ctx->slots.as<SlotDev>(), ctx->offsets.as<int>(), ctx->counts.as<int>(),
+  HIPCHK(apc::launch_resolve(mb->m, md, f, ctx->offsets.as<int>(), ctx->counts.as<int>(),
                              ctx->records.as<int>(), bin_cap(ctx), tf->rgba, moments, bp, rgba, ctr, tile_queue(ctx),
                              nullptr, nullptr, 0, s));
   HIPCHK(ev_mark(ctx, EV_STG, 1, s));
@@ -1383,7 +1383,7 @@ apc_status apc_resolve_pass_noalloc(apc_ctx ctx, apc_mesh m, const apc_view* vie
   HIPCHK(ev_mark(ctx, EV_RES, 0, s));
   if ((st = bin_faces(ctx, m, f, subs, n_sub, B, s, md)) != APC_OK) return st;
   HIPCHK(ev_mark(ctx, EV_STG, 0, s));
-  HIPCHK(apc::launch_resolve(mb->m, md, f, B.slots, B.offsets, B.counts, B.records, B.rec_cap, tf->rgba, moments, bp,
+  HIPCHK(apc::launch_resolve(mb->m, md, f, B.offsets, B.counts, B.records, B.rec_cap, tf->rgba, moments, bp,
                              rgba, ctr, tile_queue(ctx), nullptr, nullptr, 0, s));
   HIPCHK(ev_mark(ctx, EV_STG, 1, s));
   HIPCHK(ev_mark(ctx, EV_RES, 1, s));

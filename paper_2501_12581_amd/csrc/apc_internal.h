@@ -105,7 +105,7 @@ hipError_t launch_bin_fill(const MeshDev& m, const FrameDev& f, const SlotDev* s
 // ([2][H][W], may be null) the segments per pixel and the subdomains with pieces on each ray.  With gacc
 // ([m+1][H][W] FP64 scratch) set, out is the global [m+1][H][W] image: the slots' FP32 moments summed in
 // FP64 in slot order; else out is [n_slots][m+1][H][W]
-hipError_t launch_moments(int mm, const MeshDev& m, const FrameDev& f, const SlotDev* slots, const int* offsets,
+hipError_t launch_moments(int mm, const MeshDev& m, const FrameDev& f, const int* offsets,
                           const int* counts, const int* records, long long bin_cap, const float* tf_rgba, float* out,
                           double* gacc, int* pcount, int* segs, const PieceStore& store,
                           unsigned long long* counters, int* queue, const int* pair_idx, const int* pair_list,
@@ -121,7 +121,7 @@ constexpr int QUEUE_INTS = 8;
 // is kept); rgba [H][W][4] receives the listed subdomains' colour sums, finalised with bp.finalize.
 // pair_list (may be null): the bins of n_pairs (tile, subdomain) pairs, ascending; a workgroup per pair then
 // writes that pair's unfinalised colour sums to part [n_pairs][4][64] instead of rgba (queue ignored)
-hipError_t launch_resolve(int mm, const MeshDev& m, const FrameDev& f, const SlotDev* slots, const int* offsets,
+hipError_t launch_resolve(int mm, const MeshDev& m, const FrameDev& f, const int* offsets,
                           const int* counts, const int* records, long long bin_cap, const float* tf_rgba,
                           const void* moments, const BoundParams& bp, float* rgba, unsigned long long* counters,
                           int* queue, const int* pair_list, float* part, int64_t n_pairs, hipStream_t s);

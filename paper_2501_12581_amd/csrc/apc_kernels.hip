@@ -774,12 +774,10 @@ struct MomentSink {
 };
 
 // Waves per SIMD the walk kernels are compiled for (register budget 512 / n).
-#ifndef APC_WALK_WAVES
-#define APC_WALK_WAVES 3
-#endif
+constexpr int WALK_WAVES = 3;
 
 template <int M1, bool KEEP, bool QUEUE>
-__global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(APC_WALK_WAVES, 8))) void k_moments(MeshDev M, FrameDev f, const SlotDev* __restrict__ slots,
+__global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(WALK_WAVES, 8))) void k_moments(MeshDev M, FrameDev f,
                                                   const int* __restrict__ offsets, const int* __restrict__ counts,
                                                   const int* __restrict__ records, const float* __restrict__ tf_rgba,
                                                   float* __restrict__ out, double* __restrict__ gacc,
@@ -1279,8 +1277,7 @@ __device__ void walk_subdomain_paired(const MeshDev& M, const FrameDev& f, const
 
 template <int N, class R, bool QUEUE, bool PAIRS>
 __global__ __launch_bounds__(2 * WAVE) __attribute__((amdgpu_waves_per_eu(PairShape<N>::WAVES, 8))) void k_resolve(
-    MeshDev M, FrameDev f, const SlotDev* __restrict__ slots, const int* __restrict__ offsets,
-    const int* __restrict__ counts, const int* __restrict__ records, long long bin_cap,
+    MeshDev M, FrameDev f, const int* __restrict__ offsets, const int* __restrict__ counts, const int* __restrict__ records, long long bin_cap,
     const float* __restrict__ tf_rgba, const void* __restrict__ moments, BoundParams bp, float* __restrict__ rgba,
     unsigned long long* ctr, int* queue, const int* __restrict__ pair_list, float* __restrict__ part) {
   extern __shared__ float4 dyn_lds[];
@@ -1996,7 +1993,7 @@ static hipError_t reset_queue(int* queue, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_moments(int mm, const MeshDev& m, const FrameDev& f, const SlotDev* slots, const int* offsets,
+hipError_t launch_moments(int mm, const MeshDev& m, const FrameDev& f, const int* offsets,
                           const int* counts, const int* records, long long bin_cap, const float* tf_rgba, float* out,
                           double* gacc, int* pcount, int* segs, const PieceStore& store,
                           unsigned long long* counters, int* queue, const int* pair_idx, const int* pair_list,
@@ -2016,10 +2013,10 @@ hipError_t launch_moments(int mm, const MeshDev& m, const FrameDev& f, const Slo
   do {                                                                                                  \
     if (queue)                                                                                          \
       hipLaunchKernelGGL((k_moments<M1, KP, true>), dim3(resident_blocks(k_moments<M1, KP, true>, WAVE, lds)), \
-                         block, lds, s, m, f, slots, offsets, counts, records, tf_rgba, out, gacc, pcount, \
+                         block, lds, s, m, f, offsets, counts, records, tf_rgba, out, gacc, pcount, \
                          segs, bin_cap, store, counters, queue, pair_idx, nullptr);                     \
     else                                                                                                \
-      hipLaunchKernelGGL((k_moments<M1, KP, false>), grid, block, lds, s, m, f, slots, offsets, counts,   \
+      hipLaunchKernelGGL((k_moments<M1, KP, false>), grid, block, lds, s, m, f, offsets, counts,   \
                          records, tf_rgba, out, gacc, pcount, segs, bin_cap, store, counters, queue, pair_idx, \
                          pair_list);                                                                    \
   } while (0)
@@ -2059,7 +2056,7 @@ hipError_t launch_eval(int mm, const FrameDev& f, int tile_lo, int tile_hi, cons
   return hipGetLastError();
 }
 
-hipError_t launch_resolve(int mm, const MeshDev& m, const FrameDev& f, const SlotDev* slots, const int* offsets,
+hipError_t launch_resolve(int mm, const MeshDev& m, const FrameDev& f, const int* offsets,
                           const int* counts, const int* records, long long bin_cap, const float* tf_rgba,
                           const void* moments, const BoundParams& bp, float* rgba, unsigned long long* counters,
                           int* queue, const int* pair_list, float* part, int64_t n_pairs, hipStream_t s) {
@@ -2077,15 +2074,15 @@ hipError_t launch_resolve(int mm, const MeshDev& m, const FrameDev& f, const Slo
 #define APC_LAUNCH_RESOLVE(N, R)                                                                               \
   do {                                                                                                         \
     if (pair_list)                                                                                             \
-      hipLaunchKernelGGL((k_resolve<N, R, false, true>), grid, block, lds, s, m, f, slots, offsets, counts,   \
+      hipLaunchKernelGGL((k_resolve<N, R, false, true>), grid, block, lds, s, m, f, offsets, counts,   \
                          records, bin_cap, tf_rgba, moments, bp, rgba, counters, nullptr, pair_list, part);   \
     else if (queue)                                                                                            \
       hipLaunchKernelGGL((k_resolve<N, R, true, false>),                                                      \
                          dim3(resident_blocks(k_resolve<N, R, true, false>, 2 * WAVE, lds)), block, lds, s, m, \
-                         f, slots, offsets, counts, records, bin_cap, tf_rgba, moments, bp, rgba, counters,    \
+                         f, offsets, counts, records, bin_cap, tf_rgba, moments, bp, rgba, counters,    \
                          queue, nullptr, nullptr);                                                             \
     else                                                                                                       \
-      hipLaunchKernelGGL((k_resolve<N, R, false, false>), grid, block, lds, s, m, f, slots, offsets, counts,  \
+      hipLaunchKernelGGL((k_resolve<N, R, false, false>), grid, block, lds, s, m, f, offsets, counts,  \
                          records, bin_cap, tf_rgba, moments, bp, rgba, counters, nullptr, nullptr, nullptr);  \
   } while (0)
   if (mm == 4)

@@ -433,18 +433,12 @@ struct Gaps {
   static constexpr int NODES = (N - 1) * NI;
 };
 
-// Storage of one pixel's gap table: a plain array (host tests) or a slice of
-// LDS shared by the wavefront (kernels).  Entry (node, c) at node * NC + c.
+// Storage of one pixel's gap table (host tests): entry (node, c) at node * NC + c.
 template <int N, class R>
 struct TableArray {
   R v[Gaps<N>::NODES * Gaps<N>::NC];
   APC_HD R& at(int node, int c) { return v[node * Gaps<N>::NC + c]; }
   APC_HD const R& at(int node, int c) const { return v[node * Gaps<N>::NC + c]; }
-};
-template <int N, class R>
-struct TablePtr {
-  R* base;
-  APC_HD R& at(int node, int c) const { return base[node * Gaps<N>::NC + c]; }
 };
 
 // a[i] for a run-time i: plain indexing for memory-backed accessors (the
