@@ -31,7 +31,7 @@ from . import Context, make_mboit, make_tf, make_view
 
 # the library walks stage one of a frame of at most so many tiles by pairs by itself, into buffers of at most so many
 # bytes (per-tile beyond either)
-LIBRARY_PAIR_TILES, LIBRARY_PAIR_BYTES = 16384, 64 << 20
+LIBRARY_PAIR_TILES, LIBRARY_PAIR_BYTES = 16384, 256 << 20
 
 
 def look_at_view(eye, target, width: int, height: int, fovy_deg: float = 45.0) -> dict:
