@@ -277,7 +277,8 @@ apc_status apc_pack_moments_f16(apc_ctx ctx, const float* moments_global, int32_
  * (one chain of dependent steps per tile through every subdomain otherwise);
  * the same pieces, the image equal to the per-tile form's to FP32 rounding
  * (another grouping of the colour sums, and each pair's root solver starts
- * afresh).  Reads the pair count back (one stream synchronisation); not with
+ * afresh).  Reads the pair count back (the host waits for the binning's scan,
+ * or for nothing when this frame's pairs are numbered already); not with
  * APC_MOMENTS_F16 or in a captured frame (APC_E_ARG).
  * flags: APC_FINALIZE, APC_MOMENTS_F16, APC_BY_PAIR. */
 apc_status apc_resolve_pass(apc_ctx ctx, apc_mesh mesh, const apc_view* view, const apc_tf* tf,
@@ -292,14 +293,15 @@ apc_status apc_resolve_pass(apc_ctx ctx, apc_mesh mesh, const apc_view* view, co
  * of 64 MiB in the library's code object (every GPU the library runs on holds
  * one, until the process ends) instead of the context's growable buffers, so
  * the call allocates nothing.  The call reads back the number of binned
- * (face, tile) records (one stream synchronisation) before it walks.
+ * (face, tile) records (the host waits for the binning's scan) before it
+ * walks.
  * Limits: the slot table, 3 x 4 bytes per (tile, subdomain) pair and the
  * binned records must fit the 64 MiB (about 16 subdomains at 2048^2 or all
  * 72 of a 100M-tet mesh at 1024^2); a frame beyond them returns APC_E_NOMEM
- * with the sizes in the message and writes nothing to rgba_out.  Every call on
- * one GPU shares that GPU's workspace: calls that overlap in time on one GPU
- * (any contexts, any streams) race.  Everything it needs is cleared by its own
- * kernels on every call. */
+ * with the sizes in the message, writes nothing to rgba_out and leaves nothing
+ * in flight.  Every call on one GPU shares that GPU's workspace: calls that
+ * overlap in time on one GPU (any contexts, any streams) race.  Everything it
+ * needs is cleared by its own kernels on every call. */
 apc_status apc_resolve_pass_noalloc(apc_ctx ctx, apc_mesh mesh, const apc_view* view, const apc_tf* tf,
                                     const apc_mboit* mboit, const void* moments_global,
                                     const int32_t* subdomains, int32_t n_sub, float* rgba_out, uint32_t flags,
@@ -324,7 +326,9 @@ apc_status apc_resolve_pass_noalloc(apc_ctx ctx, apc_mesh mesh, const apc_view* 
  *               max_pairs == 0 the call only counts the pairs (a query)
  *   n_pairs     host out: the frame's pair count (also on APC_E_NOMEM)
  * More pairs than max_pairs: APC_E_NOMEM, nothing written.  Reads the pair
- * count back (one stream synchronisation) before it walks. */
+ * count back (the host waits for the binning's scan, or for nothing when this
+ * frame's pairs are numbered already) before it walks; a query or a refused
+ * call waits for the stream. */
 apc_status apc_moments_pass_tiles(apc_ctx ctx, apc_mesh mesh, const apc_view* view, const apc_tf* tf, int32_t m,
                                   const int32_t* subdomains, int32_t n_sub, float* tiles, int32_t* pair_bin,
                                   int64_t max_pairs, int64_t* n_pairs, void* stream);

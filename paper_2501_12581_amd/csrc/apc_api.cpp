@@ -461,8 +461,11 @@ apc_status bin_faces(apc_ctx ctx, const apc_mesh_s* m, const FrameDev& f, const 
     HIPCHK(apc::launch_bin_fill(md, f, B.slots, max_faces, m->bface, B.offsets, B.cursors, B.records, B.rec_cap, s));
   if (!ctx->capturing) {
     HIPCHK(hipEventSynchronize(ctx->totals_done));
-    const int64_t total = int64_t(ctx->totals[0]);
-    if (total > (int64_t(1) << 31) - 1) return fail(APC_E_NUMERIC, "bin records overflow (%lld)", (long long)total);
+    const int64_t total = int64_t(ctx->totals[0]), most = (int64_t(1) << 31) - 1;
+    // a refused frame leaves nothing in flight: its fill pass has ended before another frame, on whatever stream,
+    // may use these buffers (the static workspace serves every context of the device)
+    if (total > most || (total > B.rec_cap && !B.grow)) HIPCHK(hipStreamSynchronize(s));
+    if (total > most) return fail(APC_E_NUMERIC, "bin records overflow (%lld)", (long long)total);
     if (total > B.rec_cap) {
       if (!B.grow)
         return fail(APC_E_NOMEM, "the frame bins %lld (face, tile) records; the static workspace holds %lld",
@@ -1121,6 +1124,8 @@ apc_status moments_tiles(apc_ctx ctx, apc_mesh m, const apc_view* view, const ap
   if ((st = build_bins(ctx, m, view, f, subs, n_sub, true, s, md)) != APC_OK) return st;
   const int64_t nb = int64_t(f.n_tiles) * n_sub, pairs = ctx->bin_pairs;
   *n_pairs = pairs;
+  // nothing is walked: the binning has ended when the call returns
+  if (pairs > max_pairs || (max_pairs == 0 && !tiles)) HIPCHK(hipStreamSynchronize(s));
   if (max_pairs == 0 && !tiles) return APC_OK;  // a query: the caller sizes its buffers from *n_pairs
   if (pairs > max_pairs)
     return fail(APC_E_NOMEM, "the frame has %lld (tile, subdomain) pairs; the buffers hold %lld (nothing written)",

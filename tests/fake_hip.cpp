@@ -1,0 +1,352 @@
+// A stand-in for the HIP runtime on the host: a program that defines the runtime's entry points itself and loads the
+// library, so that the launch sequence of its calls can be followed without a GPU.  "Device" memory is host memory,
+// no kernel runs; the scan of the bins reports the totals that a case asks for, and every launch, copy and wait is
+// noted, so that a case can say what is still in flight on a stream when a call returns, which allocations a call
+// made, and what a kernel was launched with.  Test infrastructure only.
+//
+// usage: fake_hip <libapc.so> <case>   exit status 0: the case holds
+#include <dlfcn.h>
+#include <stdint.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <hip/hip_runtime_api.h>
+
+#include <functional>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "../include/apc.h"
+
+namespace {
+
+struct Launch {
+  std::string name;
+  uint64_t grid, block;
+  std::vector<uint64_t> arg;  // the first 8 bytes of each argument a case looks at
+};
+std::vector<Launch> g_launches;
+std::map<const void*, std::string> g_kernels;
+std::map<void*, size_t> g_mem;
+size_t g_fail_above = SIZE_MAX;  // device allocations of more bytes are refused
+unsigned long long g_records = 0, g_pairs = 0;  // what the scan of the bins reports
+uint64_t g_issued = 0, g_done = 0;              // work handed to the device, and waited for (one stream at a time)
+struct Event {
+  uint64_t at = 0;
+};
+
+bool in_flight() { return g_done < g_issued; }
+size_t device_bytes() {
+  size_t n = 0;
+  for (auto& m : g_mem) n += m.second;
+  return n;
+}
+
+}  // namespace
+
+extern "C" {
+
+void** __hipRegisterFatBinary(const void*) {
+  static void* h = nullptr;
+  return &h;
+}
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* host, char* device, const char*, unsigned, void*, void*, void*, void*,
+                           int*) {
+  g_kernels[host] = device;
+}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+struct Config {
+  dim3 grid, block;
+  size_t lds;
+  hipStream_t s;
+};
+static thread_local Config g_config;
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t s) {
+  g_config = {grid, block, lds, s};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* s) {
+  *grid = g_config.grid;
+  *block = g_config.block;
+  *lds = g_config.lds;
+  *s = g_config.s;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
+  Launch l{g_kernels[f], uint64_t(grid.x) * grid.y * grid.z, uint64_t(block.x) * block.y * block.z, {}};
+  // the runtime takes fewer than 2^32 threads in each dimension
+  if (!l.grid || uint64_t(grid.x) * block.x >= (1ull << 32)) return hipErrorInvalidConfiguration;
+  auto is = [&](const char* k) { return l.name.find(k) != std::string::npos; };
+  if (is("k_bin_scan"))
+    for (int k = 0; k < 7; ++k) l.arg.push_back(*static_cast<uint64_t*>(args[k]));
+  if (is("k_pair_list"))
+    for (int k = 0; k < 5; ++k) l.arg.push_back(*static_cast<uint64_t*>(args[k]));
+  if (is("k_bin_scan") && l.arg[6]) {
+    unsigned long long* totals = reinterpret_cast<unsigned long long*>(l.arg[6]);
+    totals[0] = g_records;
+    totals[1] = g_pairs;
+  }
+  if (is("k_adjacency")) {  // every face on the hull
+    const int64_t n = *static_cast<int64_t*>(args[1]);
+    memset(*static_cast<int**>(args[4]), 0xff, size_t(4 * n) * sizeof(int));
+  }
+  if (is("k_fill") && *static_cast<int*>(args[1]) == 0) {
+    int* p = *static_cast<int**>(args[0]);
+    const int64_t n = *static_cast<int64_t*>(args[2]);
+    if (n < (1 << 20)) memset(p, 0, size_t(n) * sizeof(int));
+  }
+  g_launches.push_back(l);
+  ++g_issued;
+  return hipSuccess;
+}
+
+hipError_t hipMalloc(void** p, size_t n) {
+  if (n > g_fail_above) {
+    *p = nullptr;
+    return hipErrorOutOfMemory;
+  }
+  *p = malloc(n);
+  memset(*p, 0x5a, n < (1 << 20) ? n : (1 << 20));  // memory comes as somebody left it
+  g_mem[*p] = n;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  g_mem.erase(p);
+  free(p);
+  g_done = g_issued;  // waits for the device
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  *p = calloc(1, n);
+  return hipSuccess;
+}
+hipError_t hipHostFree(void* p) {
+  free(p);
+  return hipSuccess;
+}
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+  memcpy(d, s, n);
+  g_done = g_issued;
+  return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+  memcpy(d, s, n);
+  ++g_issued;
+  return hipSuccess;
+}
+hipError_t hipMemset(void* d, int v, size_t n) {
+  memset(d, v, n);
+  return hipSuccess;
+}
+hipError_t hipMemGetInfo(size_t* f, size_t* t) {
+  *f = *t = size_t(256) << 30;
+  return hipSuccess;
+}
+hipError_t hipGetSymbolAddress(void** p, const void*) {
+  static void* mem = calloc(1, size_t(64) << 20);
+  *p = mem;
+  return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) {
+  *v = 256;
+  return hipSuccess;
+}
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) {
+  *n = 4;
+  return hipSuccess;
+}
+hipError_t hipDeviceSynchronize() {
+  g_done = g_issued;
+  return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) {
+  g_done = g_issued;
+  return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t* e) {
+  *e = reinterpret_cast<hipEvent_t>(new Event);
+  return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) {
+  delete reinterpret_cast<Event*>(e);
+  return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
+  reinterpret_cast<Event*>(e)->at = g_issued;
+  return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t e) {
+  const uint64_t at = reinterpret_cast<Event*>(e)->at;
+  g_done = at > g_done ? at : g_done;
+  return hipSuccess;
+}
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
+  *ms = 0.0f;
+  return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) {
+  *d = 0;
+  return hipSuccess;
+}
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDeviceCount(int* n) {
+  *n = 1;
+  return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorString(hipError_t e) { return e == hipSuccess ? "no error" : "refused"; }
+
+}  // extern "C"
+
+// ------------------------------------------------------------------ cases
+
+namespace {
+
+void* g_lib;
+template <class F>
+F sym(const char* name) {
+  void* p = dlsym(g_lib, name);
+  if (!p) {
+    printf("no %s\n", name);
+    exit(3);
+  }
+  return reinterpret_cast<F>(p);
+}
+#define APC(fn) sym<decltype(&fn)>(#fn)
+
+#define CHECK(x)                                                              \
+  do {                                                                        \
+    if (!(x)) {                                                               \
+      printf("line %d: %s\n", __LINE__, #x);                                  \
+      return 1;                                                               \
+    }                                                                         \
+  } while (0)
+
+// `n_sub` subdomains of one tet each, seen from in front
+struct Scene {
+  apc_ctx ctx = nullptr;
+  apc_mesh mesh = nullptr;
+  std::vector<int32_t> subs;
+  apc_tf tf = {};
+  apc_mboit mb = {};
+  std::vector<float> table;
+  float *moments = reinterpret_cast<float*>(0x1000000), *rgba = reinterpret_cast<float*>(0x2000000);  // never read
+
+  explicit Scene(int n_sub) : table(8, 0.5f) {
+    if (APC(apc_create)(0, &ctx) != APC_OK) exit(4);
+    std::vector<float> xyz, scalar;
+    std::vector<int32_t> tets, of;
+    for (int k = 0; k < n_sub; ++k) {
+      const float p[4][3] = {{0, 0, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
+      for (int q = 0; q < 4; ++q) {
+        for (int c = 0; c < 3; ++c) xyz.push_back(p[q][c] + (c == 2 ? 2.0f * float(k) : 0.0f));
+        scalar.push_back(float(q));
+        tets.push_back(4 * k + q);
+      }
+      of.push_back(k);
+      subs.push_back(k);
+    }
+    apc_mesh_desc d = {};
+    d.n_vertices = int64_t(scalar.size());
+    d.n_tets = n_sub;
+    d.n_subdomains = n_sub;
+    d.xyz = xyz.data();
+    d.scalar = scalar.data();
+    d.tet_vertices = tets.data();
+    d.tet_subdomain = of.data();
+    if (APC(apc_load_mesh)(ctx, &d, &mesh, nullptr) != APC_OK) exit(5);
+    tf.n_entries = 2;
+    tf.rgba = table.data();
+    tf.s_max = 3.0f;
+    tf.kappa = 1.0f;
+    tf.absorbance_max = 10.0f;
+    mb.m = 8;
+    mb.renormalize = 1;
+    mb.alpha = 5e-5;
+    mb.eta = 0.3;
+    for (int j = 0; j < 8; ++j) mb.bias[j] = (j & 1) ? 1.0 / (j + 2) : 0.0;
+  }
+  apc_view view(int w, int h) const {
+    apc_view v = {};
+    v.width = w;
+    v.height = h;
+    v.projection = APC_ORTHOGRAPHIC;
+    v.eye[2] = -1.0;
+    v.dir[2] = 1.0;
+    v.right[0] = 1.0 / w;
+    v.down[1] = 1.0 / h;
+    v.step = 0.1;
+    return v;
+  }
+  apc_status moments_pass(const apc_view& v, uint32_t flags, int m = 8) {
+    return APC(apc_moments_pass)(ctx, mesh, &v, &tf, m, subs.data(), int(subs.size()), moments, flags, nullptr);
+  }
+  apc_status resolve(const apc_view& v, uint32_t flags) {
+    return APC(apc_resolve_pass)(ctx, mesh, &v, &tf, &mb, moments, subs.data(), int(subs.size()), rgba, flags,
+                                 nullptr);
+  }
+  apc_status tiles(const apc_view& v, float* tiles, int32_t* bins, int64_t cap, int64_t* n) {
+    return APC(apc_moments_pass_pairs)(ctx, mesh, &v, &tf, 8, subs.data(), int(subs.size()), tiles, bins, cap, n,
+                                       nullptr);
+  }
+};
+
+// A call that returns an error, or only a count, leaves nothing of its own in flight: the fill of the bins (which
+// starts before the host knows the totals) has ended, so its buffers -- the static workspace belongs to every
+// context and stream of the device -- may serve another frame at once.
+int refused_noalloc() {
+  Scene s(2);
+  g_records = uint64_t(64) << 20;  // more than the 64 MiB hold
+  const apc_view v = s.view(64, 64);
+  const apc_status st = APC(apc_resolve_pass_noalloc)(s.ctx, s.mesh, &v, &s.tf, &s.mb, s.moments, s.subs.data(), 2,
+                                                      s.rgba, 0, nullptr);
+  CHECK(st == APC_E_NOMEM);
+  CHECK(!in_flight());
+  return 0;
+}
+
+int refused_overflow() {
+  Scene s(2);
+  g_records = 10;
+  g_pairs = 4;
+  CHECK(s.moments_pass(s.view(64, 64), APC_MOMENTS_GLOBAL) == APC_OK);  // (the buffers exist now)
+  hipDeviceSynchronize();
+  g_records = uint64_t(1) << 31;
+  CHECK(s.moments_pass(s.view(64, 56), APC_MOMENTS_GLOBAL) == APC_E_NUMERIC);
+  CHECK(!in_flight());
+  return 0;
+}
+
+int counted_pairs() {
+  Scene s(2);
+  g_records = 10;
+  g_pairs = 4;
+  int64_t n = -1;
+  const apc_view v = s.view(64, 64);
+  CHECK(s.tiles(v, nullptr, nullptr, 0, &n) == APC_OK && n == 4);
+  CHECK(!in_flight());
+  CHECK(s.tiles(s.view(64, 56), s.moments, reinterpret_cast<int32_t*>(s.rgba), 3, &n) == APC_E_NOMEM && n == 4);
+  CHECK(!in_flight());
+  return 0;
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::map<std::string, std::function<int()>> cases = {
+      {"refused_noalloc", refused_noalloc},
+      {"refused_overflow", refused_overflow},
+      {"counted_pairs", counted_pairs},
+  };
+  if (argc != 3 || !cases.count(argv[2])) return 2;
+  g_lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);
+  if (!g_lib) {
+    printf("%s\n", dlerror());
+    return 2;
+  }
+  return cases.at(argv[2])();
+}

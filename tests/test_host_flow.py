@@ -1,0 +1,31 @@
+"""The launch sequence of the library's calls, followed on the host (CPU only): tests/fake_hip.cpp stands in for the
+HIP runtime, so a case can bring about totals, sizes and refused allocations that no frame here reaches, and look at
+what a call launched, allocated and left in flight."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    import paper_2501_12581_amd as P
+    P.lib()
+    out = str(tmp_path_factory.mktemp("flow") / "fake_hip")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-rdynamic",
+                           os.path.join(ROOT, "tests", "fake_hip.cpp"), "-ldl", "-o", out])
+    return out, P.LIB_PATH
+
+
+def _run(program, case):
+    res = subprocess.run([program[0], program[1], case], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, (case, res.returncode, res.stdout[-2000:], res.stderr[-2000:])
+
+
+@pytest.mark.parametrize("case", ["refused_noalloc", "refused_overflow", "counted_pairs"])
+def test_a_call_that_renders_nothing_leaves_nothing_in_flight(program, case):
+    """A refused frame and a count of pairs return after the bins' fill pass, which starts before the totals are
+    known, has ended: the next call may use the same buffers on any stream."""
+    _run(program, case)
