@@ -489,7 +489,10 @@ apc_status bin_faces(apc_ctx ctx, const apc_mesh_s* m, const FrameDev& f, const 
 apc_status build_bins(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const FrameDev& f, const int32_t* subs,
                       int32_t n_sub, bool pairs, hipStream_t s, MeshDev& md) {
   const int64_t nb = int64_t(f.n_tiles) * n_sub;
-  if (pairs) HIPCHK(ctx->pidx.ensure(sizeof(int) * nb));
+  if (pairs) {
+    if (ctx->pidx.bytes < sizeof(int) * nb) ctx->bin_pairs = -1;  // the numbers go with the buffer
+    HIPCHK(ctx->pidx.ensure(sizeof(int) * nb));
+  }
   if ((ctx->capturing ? ctx->captured_bins : ctx->bins_valid) && ctx->bin_mesh == m->uid && ctx->bin_tw == ctx->tw_log2 &&
       std::memcmp(&ctx->bin_view, v, sizeof(apc_view)) == 0 && ctx->bin_subs.size() == size_t(n_sub) &&
       std::equal(subs, subs + n_sub, ctx->bin_subs.begin())) {

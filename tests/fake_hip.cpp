@@ -334,6 +334,27 @@ int counted_pairs() {
   return 0;
 }
 
+// A frame whose pair numbers cannot be had must not leave an older frame's bins claiming numbers that are gone: the
+// older frame, asked for again, is numbered anew into the buffer that its pair list reads.
+int lost_numbers() {
+  Scene s(2);
+  g_records = 10;
+  g_pairs = 4;
+  const apc_view small = s.view(64, 64);
+  CHECK(s.resolve(small, APC_BY_PAIR) == APC_OK);
+  g_fail_above = 64 << 10;
+  CHECK(s.resolve(s.view(1024, 1024), APC_BY_PAIR) != APC_OK);  // 32768 bins: 128 KiB of numbers
+  g_fail_above = SIZE_MAX;
+  g_launches.clear();
+  CHECK(s.resolve(small, APC_BY_PAIR) == APC_OK);
+  uint64_t numbers = 0;
+  for (const Launch& l : g_launches) {
+    if (l.name.find("k_bin_scan") != std::string::npos) numbers = l.arg[5];
+    if (l.name.find("k_pair_list") != std::string::npos) CHECK(numbers && l.arg[2] == numbers);
+  }
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -341,6 +362,7 @@ int main(int argc, char** argv) {
       {"refused_noalloc", refused_noalloc},
       {"refused_overflow", refused_overflow},
       {"counted_pairs", counted_pairs},
+      {"lost_numbers", lost_numbers},
   };
   if (argc != 3 || !cases.count(argv[2])) return 2;
   g_lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);

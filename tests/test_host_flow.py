@@ -29,3 +29,9 @@ def test_a_call_that_renders_nothing_leaves_nothing_in_flight(program, case):
     """A refused frame and a count of pairs return after the bins' fill pass, which starts before the totals are
     known, has ended: the next call may use the same buffers on any stream."""
     _run(program, case)
+
+
+def test_pair_numbers_that_are_gone_are_made_again(program):
+    """A larger frame frees the pair numbers and cannot have its own: the smaller frame, repeated, does not trust
+    the new buffer's contents."""
+    _run(program, "lost_numbers")
