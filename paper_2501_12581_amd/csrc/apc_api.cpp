@@ -483,16 +483,19 @@ apc_status bin_faces(apc_ctx ctx, const apc_mesh_s* m, const FrameDev& f, const 
   return APC_OK;
 }
 
+// Room for the numbers of nb bins' pairs.  The numbers at hand go with a buffer that has to grow.
+hipError_t number_room(apc_ctx ctx, int64_t nb) {
+  if (ctx->pidx.bytes < sizeof(int) * nb) ctx->bin_pairs = -1;
+  return ctx->pidx.ensure(sizeof(int) * nb);
+}
+
 // bin_faces into the context's growable buffers, unless they already hold the bins of this mesh, view, tile
 // shape and subdomain list (stage two after stage one of the same frame); a captured frame bins once, in its
 // stage one.  With `pairs` the bins with faces are numbered in ctx->pidx, ctx->bin_pairs of them.
 apc_status build_bins(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const FrameDev& f, const int32_t* subs,
                       int32_t n_sub, bool pairs, hipStream_t s, MeshDev& md) {
   const int64_t nb = int64_t(f.n_tiles) * n_sub;
-  if (pairs) {
-    if (ctx->pidx.bytes < sizeof(int) * nb) ctx->bin_pairs = -1;  // the numbers go with the buffer
-    HIPCHK(ctx->pidx.ensure(sizeof(int) * nb));
-  }
+  if (pairs) HIPCHK(number_room(ctx, nb));
   if ((ctx->capturing ? ctx->captured_bins : ctx->bins_valid) && ctx->bin_mesh == m->uid && ctx->bin_tw == ctx->tw_log2 &&
       std::memcmp(&ctx->bin_view, v, sizeof(apc_view)) == 0 && ctx->bin_subs.size() == size_t(n_sub) &&
       std::equal(subs, subs + n_sub, ctx->bin_subs.begin())) {
@@ -1056,7 +1059,11 @@ apc_status apc_moments_pass(apc_ctx ctx, apc_mesh m, const apc_view* view, const
   if (ctx->host_only) return no_device("apc_moments_pass");
   hipStream_t s = static_cast<hipStream_t>(stream);
   MeshDev md;
-  const bool few = f.n_tiles <= STAGE_ONE_PAIR_TILES && ctx->dispatch == APC_DISPATCH_GRID && !(flags & APC_KEEP_PIECES);
+  bool few = f.n_tiles <= STAGE_ONE_PAIR_TILES && ctx->dispatch == APC_DISPATCH_GRID && !(flags & APC_KEEP_PIECES);
+  if (few && number_room(ctx, int64_t(f.n_tiles) * n_sub) != hipSuccess) {
+    (void)hipGetLastError();
+    few = false;
+  }
   if ((st = build_bins(ctx, m, view, f, subs, n_sub, few, s, md)) != APC_OK) return st;
   if (few && pairs_fit(ctx, mm, global)) {
     ctx->store_ready = false;

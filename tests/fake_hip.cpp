@@ -31,6 +31,7 @@ std::vector<Launch> g_launches;
 std::map<const void*, std::string> g_kernels;
 std::map<void*, size_t> g_mem;
 size_t g_fail_above = SIZE_MAX;  // device allocations of more bytes are refused
+size_t g_refuse_from = 1, g_refuse_to = 0;  // the next device allocation of a size between these is refused
 unsigned long long g_records = 0, g_pairs = 0;  // what the scan of the bins reports
 uint64_t g_issued = 0, g_done = 0;              // work handed to the device, and waited for (one stream at a time)
 struct Event {
@@ -104,7 +105,9 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
 }
 
 hipError_t hipMalloc(void** p, size_t n) {
-  if (n > g_fail_above) {
+  const bool refuse = n >= g_refuse_from && n <= g_refuse_to;
+  if (refuse) g_refuse_to = 0;
+  if (n > g_fail_above || refuse) {
     *p = nullptr;
     return hipErrorOutOfMemory;
   }
@@ -355,6 +358,27 @@ int lost_numbers() {
   return 0;
 }
 
+// The buffers that only walking by pairs needs (its numbers, list and moments, in this order) may be refused: the
+// frame is then walked per tile, in a launch of a workgroup per tile.
+int refused_pair_buffers() {
+  const size_t from[3] = {130 << 10, 78 << 10, 40 << 20}, to[3] = {170 << 10, 120 << 10, 90 << 20};
+  for (int which = 0; which < 3; ++which) {  // 32768 bins, 20000 pairs: 128 KiB, 80 KiB, 46 MiB and their slack
+    Scene s(2);
+    g_records = 10;
+    g_pairs = 20000;
+    g_refuse_from = from[which];
+    g_refuse_to = to[which];
+    g_launches.clear();
+    CHECK(s.moments_pass(s.view(1024, 1024), APC_MOMENTS_GLOBAL) == APC_OK);
+    CHECK(g_refuse_to == 0);
+    uint64_t walks = 0;
+    for (const Launch& l : g_launches)
+      if (l.name.find("k_moments") != std::string::npos) walks = l.grid;
+    CHECK(walks == 16384);
+  }
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -363,6 +387,7 @@ int main(int argc, char** argv) {
       {"refused_overflow", refused_overflow},
       {"counted_pairs", counted_pairs},
       {"lost_numbers", lost_numbers},
+      {"refused_pair_buffers", refused_pair_buffers},
   };
   if (argc != 3 || !cases.count(argv[2])) return 2;
   g_lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);

@@ -35,3 +35,8 @@ def test_pair_numbers_that_are_gone_are_made_again(program):
     """A larger frame frees the pair numbers and cannot have its own: the smaller frame, repeated, does not trust
     the new buffer's contents."""
     _run(program, "lost_numbers")
+
+
+def test_a_frame_without_room_for_its_pairs_goes_per_tile(program):
+    """No frame is refused for a buffer that only one of stage one's two forms needs."""
+    _run(program, "refused_pair_buffers")
