@@ -1005,10 +1005,12 @@ static constexpr int STAGE_ONE_PAIR_TILES = 16384;
 // m = 8 on 1.6M tets in 72 uneven subdomains, 1.39 ms against 1.51 per tile (about 100 MB).
 static constexpr size_t STAGE_ONE_PAIR_BYTES = size_t(256) << 20;
 
-// The buffers of stage one by pairs; false: too large, or not to be had (the per-tile form needs none of them).
+// The buffers of stage one by pairs; false: too large, or not to be had (the per-tile form needs none of them), or
+// more pairs than one launch holds wavefronts of (2^32 threads).
 static bool pairs_fit(apc_ctx ctx, int mm, bool global) {
   const size_t pairs = size_t(std::max<int64_t>(ctx->bin_pairs, 1)), bytes = sizeof(float) * 64 * (mm + 1) * pairs;
   if (global && bytes > STAGE_ONE_PAIR_BYTES) return false;
+  if (pairs >= size_t(1) << 26) return false;
   const bool ok = ctx->rpair.ensure(sizeof(int) * pairs) == hipSuccess &&
                   (!global || ctx->mtile.ensure(bytes) == hipSuccess);
   if (!ok) (void)hipGetLastError();

@@ -61,6 +61,9 @@ __device__ __forceinline__ int bit_select(int m, int a, int b) { return (m & b) 
 __device__ __forceinline__ unsigned long long ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 __device__ __forceinline__ bool lane_of(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
+// The block's number in a launch over wide_grid.
+__device__ __forceinline__ int64_t flat_block() { return int64_t(blockIdx.y) * gridDim.x + blockIdx.x; }
+
 // Blocks are dispatched round-robin over the 8 XCDs (block b runs on XCD
 // b % 8).  The tiles are handed out in runs of XCD_RUN consecutive tiles, so
 // neighbouring tiles (which read the same tets) share one XCD's L2, and
@@ -1657,7 +1660,7 @@ __global__ __launch_bounds__(WAVE * SUM_WPB) void k_sum_tiles(const float* __res
                                                               const int* __restrict__ pair_bin, int64_t n_pairs,
                                                               int n_slots, int W, int H, int tw_log2, int tiles_x,
                                                               int64_t n_tiles, float* __restrict__ out) {
-  const int64_t tile = int64_t(blockIdx.x) * SUM_WPB + __builtin_amdgcn_readfirstlane(int(threadIdx.x / WAVE));
+  const int64_t tile = flat_block() * SUM_WPB + __builtin_amdgcn_readfirstlane(int(threadIdx.x / WAVE));
   if (tile >= n_tiles) return;
   const int lane = threadIdx.x % WAVE;
   int64_t first, n;
@@ -1723,7 +1726,7 @@ __global__ __launch_bounds__(WAVE * SUM_WPB) void k_sum_color_tiles(const float*
                                                                     int tw_log2, int tiles_x, int64_t n_tiles,
                                                                     const float* __restrict__ b0, BoundParams bp,
                                                                     float4* __restrict__ out) {
-  const int64_t tile = int64_t(blockIdx.x) * SUM_WPB + __builtin_amdgcn_readfirstlane(int(threadIdx.x / WAVE));
+  const int64_t tile = flat_block() * SUM_WPB + __builtin_amdgcn_readfirstlane(int(threadIdx.x / WAVE));
   if (tile >= n_tiles) return;
   const int lane = threadIdx.x % WAVE;
   int64_t first, n;
@@ -1890,7 +1893,7 @@ __global__ void k_scan_add(int* __restrict__ out, int64_t n, const int* __restri
 }
 
 __global__ void k_fill(int* p, int v, int64_t n) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t i = flat_block() * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
 }
 
@@ -1951,6 +1954,12 @@ __global__ void k_adjacency(const int4* __restrict__ tv, int64_t n_tets, const i
 }
 
 inline unsigned grid1(int64_t n, int b) { return unsigned((n + b - 1) / b); }
+// At least n blocks of up to 1024 threads (flat_block; the last ones may have nothing to do) as rows, since a launch
+// takes fewer than 2^32 threads in each dimension.
+inline dim3 wide_grid(int64_t n) {
+  const int64_t x = n < (1 << 20) ? n : (1 << 20);
+  return dim3(unsigned(x), unsigned((n + x - 1) / x));
+}
 
 }  // namespace
 
@@ -2140,7 +2149,7 @@ hipError_t launch_sum_tiles(const float* tiles, const int* pair_bin, int64_t n_p
   const int tiles_x = int((int64_t(W) + tw - 1) / tw);
   const int64_t n_tiles = (int64_t(H) + th - 1) / th * tiles_x;
   if (n_tiles <= 0) return hipSuccess;
-  const dim3 grid(grid1(n_tiles, SUM_WPB)), block(WAVE * SUM_WPB);
+  const dim3 grid = wide_grid((n_tiles + SUM_WPB - 1) / SUM_WPB), block(WAVE * SUM_WPB);
   if (m1 == 5)
     hipLaunchKernelGGL((k_sum_tiles<5>), grid, block, 0, s, tiles, pair_bin, n_pairs, n_slots, W, H, tw_log2, tiles_x,
                        n_tiles, out);
@@ -2159,8 +2168,9 @@ hipError_t launch_sum_color_tiles(const float* part, const int* pair_bin, int64_
   const int tiles_x = int((int64_t(W) + tw - 1) / tw);
   const int64_t n_tiles = (int64_t(H) + th - 1) / th * tiles_x;
   if (n_tiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_sum_color_tiles, dim3(grid1(n_tiles, SUM_WPB)), dim3(WAVE * SUM_WPB), 0, s, part, pair_bin,
-                     n_pairs, n_slots, W, H, tw_log2, tiles_x, n_tiles, b0, bp, reinterpret_cast<float4*>(out));
+  hipLaunchKernelGGL(k_sum_color_tiles, wide_grid((n_tiles + SUM_WPB - 1) / SUM_WPB), dim3(WAVE * SUM_WPB), 0, s,
+                     part, pair_bin, n_pairs, n_slots, W, H, tw_log2, tiles_x, n_tiles, b0, bp,
+                     reinterpret_cast<float4*>(out));
   return hipGetLastError();
 }
 
@@ -2196,7 +2206,7 @@ hipError_t launch_exclusive_scan(const int* in, int* out, int64_t n, int* tmp, h
 
 hipError_t launch_fill_i32(int* p, int value, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill, dim3(grid1(n, 256)), dim3(256), 0, s, p, value, n);
+  hipLaunchKernelGGL(k_fill, wide_grid((n + 255) / 256), dim3(256), 0, s, p, value, n);
   return hipGetLastError();
 }
 

@@ -34,6 +34,7 @@ size_t g_fail_above = SIZE_MAX;  // device allocations of more bytes are refused
 size_t g_refuse_from = 1, g_refuse_to = 0;  // the next device allocation of a size between these is refused
 unsigned long long g_records = 0, g_pairs = 0;  // what the scan of the bins reports
 uint64_t g_issued = 0, g_done = 0;              // work handed to the device, and waited for (one stream at a time)
+hipError_t g_last = hipSuccess;
 struct Event {
   uint64_t at = 0;
 };
@@ -79,7 +80,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
   Launch l{g_kernels[f], uint64_t(grid.x) * grid.y * grid.z, uint64_t(block.x) * block.y * block.z, {}};
   // the runtime takes fewer than 2^32 threads in each dimension
-  if (!l.grid || uint64_t(grid.x) * block.x >= (1ull << 32)) return hipErrorInvalidConfiguration;
+  if (!l.grid || uint64_t(grid.x) * block.x >= (1ull << 32)) return g_last = hipErrorInvalidConfiguration;
   auto is = [&](const char* k) { return l.name.find(k) != std::string::npos; };
   if (is("k_bin_scan"))
     for (int k = 0; k < 7; ++k) l.arg.push_back(*static_cast<uint64_t*>(args[k]));
@@ -200,7 +201,11 @@ hipError_t hipGetDeviceCount(int* n) {
   *n = 1;
   return hipSuccess;
 }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() {
+  const hipError_t e = g_last;
+  g_last = hipSuccess;
+  return e;
+}
 const char* hipGetErrorString(hipError_t e) { return e == hipSuccess ? "no error" : "refused"; }
 
 }  // extern "C"
@@ -379,6 +384,40 @@ int refused_pair_buffers() {
   return 0;
 }
 
+// Launches stay below 2^32 threads in each dimension however large the output: per-subdomain images of 17 GB, more
+// pairs than such a launch holds, and sums of an image whose tiles are nearly empty.
+int large_images() {
+  Scene s(460);
+  g_records = 10;
+  g_pairs = 460;
+  CHECK(s.moments_pass(s.view(1024, 1024), 0) == APC_OK);  // 460 x 9 x 2^20 values
+  return 0;
+}
+
+int large_pair_lists() {
+  Scene s(4200);
+  g_records = 10;
+  g_pairs = 16384ull * 4200;
+  g_launches.clear();
+  CHECK(s.moments_pass(s.view(1024, 1024), 0, 4) == APC_OK);
+  uint64_t walks = 0;
+  for (const Launch& l : g_launches)
+    if (l.name.find("k_moments") != std::string::npos) walks = l.grid;
+  CHECK(walks == 16384);
+  return 0;
+}
+
+int thin_images() {
+  Scene s(1);
+  CHECK(APC(apc_sum_moment_tiles)(s.ctx, s.moments, reinterpret_cast<int32_t*>(s.rgba), 5, 1, 8, 1 << 27, 1, 64,
+                                  s.moments, nullptr) == APC_OK);
+  uint64_t blocks = 0;
+  for (const Launch& l : g_launches)
+    if (l.name.find("k_sum_tiles") != std::string::npos) blocks = l.grid * (l.block / 64);
+  CHECK(blocks >= 1u << 27);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -388,6 +427,9 @@ int main(int argc, char** argv) {
       {"counted_pairs", counted_pairs},
       {"lost_numbers", lost_numbers},
       {"refused_pair_buffers", refused_pair_buffers},
+      {"large_images", large_images},
+      {"large_pair_lists", large_pair_lists},
+      {"thin_images", thin_images},
   };
   if (argc != 3 || !cases.count(argv[2])) return 2;
   g_lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);

@@ -81,3 +81,25 @@ def test_stage_one_of_few_tiles_by_pairs_is_the_per_tile_pass(apc, ctx, W, H, n_
         ctx.set_dispatch(apc.APC_DISPATCH_GRID)
     for k, (a, b) in enumerate(zip(*got.values())):
         assert torch.equal(a, b), k
+
+
+def test_images_beyond_one_row_of_the_clearing_launch(apc, ctx):
+    """Per-subdomain images of more than 2^28 values (the clearing's grid then has rows): bit for bit the per-tile
+    pass's, zeros where no pair writes included."""
+    n_sub, W, H, m = 31, 1024, 1024, 8
+    sc = _scene(W, H, n_sub)
+    sc.view = synth.perspective_view((0.5, 2.3, 0.9), (0.5, 0.5, 0.5), W, H)
+    sc.m, sc.bias = m, synth.default_bias(m)
+    r = apc.Renderer(ctx, sc)
+    assert r.per_sub.numel() > 1 << 28
+    got = []
+    try:
+        for mode in (apc.APC_DISPATCH_QUEUE, apc.APC_DISPATCH_GRID):
+            ctx.set_dispatch(mode)
+            r.per_sub.fill_(-1.0)
+            ctx.moments_pass(r.mesh, r.view, r.tf, m, r.subs, r.per_sub)
+            torch.cuda.synchronize()
+            got.append(r.per_sub.clone())
+    finally:
+        ctx.set_dispatch(apc.APC_DISPATCH_GRID)
+    assert torch.equal(*got)

@@ -40,3 +40,9 @@ def test_pair_numbers_that_are_gone_are_made_again(program):
 def test_a_frame_without_room_for_its_pairs_goes_per_tile(program):
     """No frame is refused for a buffer that only one of stage one's two forms needs."""
     _run(program, "refused_pair_buffers")
+
+
+@pytest.mark.parametrize("case", ["large_images", "large_pair_lists", "thin_images"])
+def test_launches_fit_however_large_the_output(program, case):
+    """No launch of 2^32 threads in one dimension, which the runtime refuses."""
+    _run(program, case)
