@@ -1029,7 +1029,7 @@ static apc_status moments_by_pair(apc_ctx ctx, const apc_view* view, const apc_t
   if (global)
     ctx->ev_used[EV_SUM] = false;  // its time is the stage's
   else
-    HIPCHK(apc::launch_fill_i32(reinterpret_cast<int*>(out), 0, int64_t(n_sub) * (mm + 1) * HW, s));
+    HIPCHK(apc::launch_clear_unpaired(f, ctx->counts.as<int>(), mm + 1, out, s));
   HIPCHK(apc::launch_moments(mm, md, f, ctx->offsets.as<int>(), ctx->counts.as<int>(),
                              ctx->records.as<int>(), bin_cap(ctx), tf->rgba, global ? ctx->mtile.as<float>() : out,
                              nullptr, nullptr, ctx->segs.as<int>(), apc::PieceStore{},

@@ -151,6 +151,8 @@ hipError_t launch_exclusive_scan(const int* in, int* out, int64_t n, int* tmp, h
 // tmp: scan_tmp_elems(nb) ints, 8-byte aligned.
 hipError_t launch_bin_scan(const int* counts, int64_t nb, int* offsets, int* cursors, int* pidx, int* tmp,
                            unsigned long long* totals, hipStream_t s);
+// zeros in the per-subdomain images out [n_slots][m1][H][W] at the pixels of bins without records
+hipError_t launch_clear_unpaired(const FrameDev& f, const int* counts, int m1, float* out, hipStream_t s);
 // pair_bin[p] = the bin of pair p < n_pairs
 hipError_t launch_pair_list(const int* counts, int64_t nb, const int* pidx, int* pair_bin, int64_t n_pairs,
                             hipStream_t s);

@@ -1897,6 +1897,23 @@ __global__ void k_fill(int* p, int v, int64_t n) {
   if (i < n) p[i] = v;
 }
 
+// Per-subdomain images [n_slots][m1][H][W] that pairs write: zeros at the pixels of the tiles without a pair (the
+// pairs write the others), a thread per pixel of a slot.  Bound by its writes.
+constexpr int CLEAR_THREADS = 256;
+__global__ __launch_bounds__(CLEAR_THREADS) void k_clear_unpaired(const int* __restrict__ counts, int n_slots, int m1,
+                                                                  int W, int64_t HW, int tw_log2, int tiles_x,
+                                                                  int64_t chunks, float* __restrict__ out) {
+  const int64_t b = flat_block(), slot = b / chunks;
+  if (slot >= n_slots) return;
+  const int64_t pix = (b - slot * chunks) * CLEAR_THREADS + threadIdx.x;
+  if (pix >= HW) return;
+  const unsigned y = unsigned(pix) / unsigned(W), x = unsigned(pix) - y * unsigned(W);  // (HW <= 2^30)
+  const int64_t tile = int64_t(y >> (6 - tw_log2)) * tiles_x + (x >> tw_log2);
+  if (counts[tile * n_slots + slot] > 0) return;
+  float* o = out + slot * m1 * HW + pix;
+  for (int j = 0; j < m1; ++j, o += HW) *o = 0.0f;
+}
+
 // ------------------------------------------------------------------ mesh residency
 
 __global__ void k_inc_count(const int4* __restrict__ tv, int64_t n_tets, int* __restrict__ counts) {
@@ -2207,6 +2224,13 @@ hipError_t launch_exclusive_scan(const int* in, int* out, int64_t n, int* tmp, h
 hipError_t launch_fill_i32(int* p, int value, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_fill, wide_grid((n + 255) / 256), dim3(256), 0, s, p, value, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_clear_unpaired(const FrameDev& f, const int* counts, int m1, float* out, hipStream_t s) {
+  const int64_t HW = int64_t(f.W) * f.H, chunks = (HW + CLEAR_THREADS - 1) / CLEAR_THREADS;
+  hipLaunchKernelGGL(k_clear_unpaired, wide_grid(chunks * f.n_slots), dim3(CLEAR_THREADS), 0, s, counts, f.n_slots, m1,
+                     f.W, HW, f.tw_log2, f.tiles_x, chunks, out);
   return hipGetLastError();
 }
 
