@@ -208,10 +208,11 @@ typedef struct apc_mboit {
  *     for the second walk; results equal the plain form's to rounding.
  * Without APC_KEEP_PIECES nothing per piece is stored (the paper's method: the
  * per-pixel state is the m + 1 moments).
- * A frame of at most 16384 tiles (1024^2 at 8 x 8) without APC_KEEP_PIECES
- * under APC_DISPATCH_GRID is walked pair by pair, as apc_moments_pass_pairs
- * does, with the same results bit for bit; with APC_MOMENTS_GLOBAL the pairs'
- * moments take a context buffer of up to 256 MiB (larger frames go per tile). */
+ * A frame of few tiles (at most 9216, 768^2 at 8 x 8, or up to 16384 when
+ * its subdomains are many) without APC_KEEP_PIECES under APC_DISPATCH_GRID is
+ * walked pair by pair, as apc_moments_pass_pairs does, with the same results
+ * bit for bit; with APC_MOMENTS_GLOBAL the pairs' moments take a context
+ * buffer of up to 256 MiB (frames that need more go per tile). */
 apc_status apc_moments_pass(apc_ctx ctx, apc_mesh mesh, const apc_view* view, const apc_tf* tf, int32_t m,
                             const int32_t* subdomains, int32_t n_sub, float* moments_per_sub, uint32_t flags,
                             void* stream);

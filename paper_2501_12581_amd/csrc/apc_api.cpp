@@ -996,11 +996,24 @@ static bool grow_piece_store(apc_ctx ctx, size_t slots) {
 
 // Stage one of frames of few tiles runs by pairs: a workgroup per (tile, subdomain) pair with binned faces, since
 // a workgroup per tile walks every subdomain on its rays in turn and the device waits for the longest chains.
-// The same moments bit for bit (each pair is the same walk, the sum takes the slots in the same order).  Measured,
-// per tile and by pairs, ms: 256^2 on 1.6M tets in 16 subdomains 0.93, 0.30; 512^2 0.85, 0.42; 768^2 0.93, 0.67; 1024^2
-// (16384 tiles) 1.12, 1.03; 1280^2 1.52, 1.47: beyond it is the larger buffers for little.  Pieces are kept in one
-// order per pixel, so not with APC_KEEP_PIECES; a work queue is of tiles.
-static constexpr int STAGE_ONE_PAIR_TILES = 16384;
+// The same moments bit for bit (each pair is the same walk, the sum takes the slots in the same order).  Pieces are
+// kept in one order per pixel, so not with APC_KEEP_PIECES; a work queue is of tiles.  The pair list, the sum and the
+// clearing cost per tile and pixel, the chains per subdomain, so the line depends on the subdomains.  Measured, ms of
+// a whole call (binning included) per tile and by pairs, m = 4, on 24.6k tets / 1.6M tets:
+//   2 subdomains   256^2 0.23, 0.18 / 0.90, 0.68   768^2 0.292, 0.286 / 0.86, 0.83   1024^2 0.37, 0.39 / 1.09, 1.10
+//   4 subdomains   256^2 0.27, 0.17 / 1.01, 0.57   768^2 0.325, 0.302 / 0.95, 0.77   1024^2 0.404, 0.418 / 1.18, 1.12
+//   16 subdomains  256^2 0.31, 0.15 / 1.10, 0.44   768^2 0.36, 0.30 / 1.01, 0.84     1024^2 0.454, 0.448 / 1.27, 1.24
+// With one subdomain there is no chain to split, but only tiles with faces get a workgroup, which spreads a middling
+// frame better: 256^2 0.162, 0.170 / 0.564, 0.565   512^2 0.204, 0.192 / 0.64, 0.53   1024^2 0.358, 0.373 / 1.05, 1.06.
+// The per-subdomain images take the same line: their clearing writes only what no pair does.
+static constexpr int STAGE_ONE_PAIR_TILES = 16384;  // 1024^2: the most for any frame
+static bool walk_by_pairs(const apc_mesh_s* m, const FrameDev& f) {
+  if (f.n_tiles > STAGE_ONE_PAIR_TILES) return false;
+  const bool middling = f.n_tiles <= 9216;  // 768^2
+  if (f.n_slots == 1) return f.n_tiles > 2304 && middling;  // 384^2
+  // beyond: chains enough, or long ones (1024^2 and 4 subdomains above: the smaller mesh has 1.5 tets per tile)
+  return middling || f.n_slots >= 8 || (f.n_slots >= 4 && m->T >= 4 * int64_t(f.n_tiles));
+}
 // ... and while the pairs' moments (the sum's input; per-subdomain images need none) stay below this: 1024^2 at
 // m = 8 on 1.6M tets in 72 uneven subdomains, 1.39 ms against 1.51 per tile (about 100 MB).
 static constexpr size_t STAGE_ONE_PAIR_BYTES = size_t(256) << 20;
@@ -1061,7 +1074,7 @@ apc_status apc_moments_pass(apc_ctx ctx, apc_mesh m, const apc_view* view, const
   if (ctx->host_only) return no_device("apc_moments_pass");
   hipStream_t s = static_cast<hipStream_t>(stream);
   MeshDev md;
-  bool few = f.n_tiles <= STAGE_ONE_PAIR_TILES && ctx->dispatch == APC_DISPATCH_GRID && !(flags & APC_KEEP_PIECES);
+  bool few = ctx->dispatch == APC_DISPATCH_GRID && !(flags & APC_KEEP_PIECES) && walk_by_pairs(m, f);
   if (few && number_room(ctx, int64_t(f.n_tiles) * n_sub) != hipSuccess) {
     (void)hipGetLastError();
     few = false;

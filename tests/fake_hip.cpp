@@ -4,7 +4,7 @@
 // noted, so that a case can say what is still in flight on a stream when a call returns, which allocations a call
 // made, and what a kernel was launched with.  Test infrastructure only.
 //
-// usage: fake_hip <libapc.so> <case>   exit status 0: the case holds
+// usage: fake_hip <libapc.so> <case> [arguments]   exit status 0: the case holds
 #include <dlfcn.h>
 #include <stdint.h>
 #include <stdio.h>
@@ -234,7 +234,7 @@ F sym(const char* name) {
     }                                                                         \
   } while (0)
 
-// `n_sub` subdomains of one tet each, seen from in front
+// `n_sub` subdomains of `tets_each` tets, seen from in front
 struct Scene {
   apc_ctx ctx = nullptr;
   apc_mesh mesh = nullptr;
@@ -244,23 +244,23 @@ struct Scene {
   std::vector<float> table;
   float *moments = reinterpret_cast<float*>(0x1000000), *rgba = reinterpret_cast<float*>(0x2000000);  // never read
 
-  explicit Scene(int n_sub) : table(8, 0.5f) {
+  explicit Scene(int n_sub, int tets_each = 1) : table(8, 0.5f) {
     if (APC(apc_create)(0, &ctx) != APC_OK) exit(4);
     std::vector<float> xyz, scalar;
     std::vector<int32_t> tets, of;
-    for (int k = 0; k < n_sub; ++k) {
+    for (int k = 0; k < n_sub * tets_each; ++k) {
       const float p[4][3] = {{0, 0, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
       for (int q = 0; q < 4; ++q) {
         for (int c = 0; c < 3; ++c) xyz.push_back(p[q][c] + (c == 2 ? 2.0f * float(k) : 0.0f));
         scalar.push_back(float(q));
         tets.push_back(4 * k + q);
       }
-      of.push_back(k);
-      subs.push_back(k);
+      of.push_back(k / tets_each);
     }
+    for (int k = 0; k < n_sub; ++k) subs.push_back(k);
     apc_mesh_desc d = {};
     d.n_vertices = int64_t(scalar.size());
-    d.n_tets = n_sub;
+    d.n_tets = n_sub * tets_each;
     d.n_subdomains = n_sub;
     d.xyz = xyz.data();
     d.scalar = scalar.data();
@@ -366,20 +366,20 @@ int lost_numbers() {
 // The buffers that only walking by pairs needs (its numbers, list and moments, in this order) may be refused: the
 // frame is then walked per tile, in a launch of a workgroup per tile.
 int refused_pair_buffers() {
-  const size_t from[3] = {130 << 10, 78 << 10, 40 << 20}, to[3] = {170 << 10, 120 << 10, 90 << 20};
-  for (int which = 0; which < 3; ++which) {  // 32768 bins, 20000 pairs: 128 KiB, 80 KiB, 46 MiB and their slack
-    Scene s(2);
+  const size_t from[3] = {280 << 10, 78 << 10, 40 << 20}, to[3] = {370 << 10, 120 << 10, 100 << 20};
+  for (int which = 0; which < 3; ++which) {  // 73728 bins, 20000 pairs: 288 KiB, 80 KiB, 44 MiB and their slack
+    Scene s(8);
     g_records = 10;
     g_pairs = 20000;
     g_refuse_from = from[which];
     g_refuse_to = to[which];
     g_launches.clear();
-    CHECK(s.moments_pass(s.view(1024, 1024), APC_MOMENTS_GLOBAL) == APC_OK);
+    CHECK(s.moments_pass(s.view(768, 768), APC_MOMENTS_GLOBAL) == APC_OK);
     CHECK(g_refuse_to == 0);
     uint64_t walks = 0;
     for (const Launch& l : g_launches)
       if (l.name.find("k_moments") != std::string::npos) walks = l.grid;
-    CHECK(walks == 16384);
+    CHECK(walks == 9216);
   }
   return 0;
 }
@@ -418,6 +418,20 @@ int thin_images() {
   return 0;
 }
 
+// Which form stage one takes: <width> <height> <subdomains> <tets of each>.
+int route(int w, int h, int n_sub, int tets_each) {
+  Scene s(n_sub, tets_each);
+  g_records = 100;
+  g_pairs = 7;
+  for (uint32_t flags : {APC_MOMENTS_GLOBAL, 0u}) {
+    g_launches.clear();
+    CHECK(s.moments_pass(s.view(w, h), flags) == APC_OK);
+    for (const Launch& l : g_launches)
+      if (l.name.find("k_moments") != std::string::npos) printf("%s ", l.grid == 7 ? "pairs" : "tiles");
+  }
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -431,11 +445,12 @@ int main(int argc, char** argv) {
       {"large_pair_lists", large_pair_lists},
       {"thin_images", thin_images},
   };
-  if (argc != 3 || !cases.count(argv[2])) return 2;
+  const bool routes = argc == 7 && std::string(argv[2]) == "route";
+  if (!routes && (argc != 3 || !cases.count(argv[2]))) return 2;
   g_lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);
   if (!g_lib) {
     printf("%s\n", dlerror());
     return 2;
   }
-  return cases.at(argv[2])();
+  return routes ? route(atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6])) : cases.at(argv[2])();
 }

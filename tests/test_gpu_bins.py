@@ -103,3 +103,35 @@ def test_images_beyond_one_row_of_the_clearing_launch(apc, ctx):
     finally:
         ctx.set_dispatch(apc.APC_DISPATCH_GRID)
     assert torch.equal(*got)
+
+
+@pytest.mark.parametrize("W,H,n_sub,pairs", [
+    (512, 288, 1, False), (392, 384, 1, True), (768, 768, 1, True), (776, 768, 1, False),
+    (8, 8, 2, True), (768, 768, 3, True), (776, 768, 3, False), (1000, 1000, 8, True), (1032, 1024, 8, False),
+])
+def test_both_forms_of_stage_one_on_both_sides_of_the_line(apc, W, H, n_sub, pairs):
+    """Frames on both sides of the lines between the forms: the expected form ran (the per-tile one of a global sum
+    needs its FP64 partials, which a context that went by pairs gets only for the work queue's frame after it), and
+    moments, images per subdomain and segment counts are the queue's bit for bit."""
+    sc = _scene(W, H, n_sub)
+    sc.view = synth.perspective_view((0.5, 2.3, 0.9), (0.5, 0.5, 0.5), W, H)
+    sc.m, sc.bias = 4, synth.default_bias(4)
+    own = apc.Context(0)
+    try:
+        r = apc.Renderer(own, sc)
+        got = []
+        for mode in (apc.APC_DISPATCH_GRID, apc.APC_DISPATCH_QUEUE):
+            own.set_dispatch(mode)
+            before = own.workspace_bytes()
+            r.moments.fill_(-1.0)
+            own.moments_pass(r.mesh, r.view, r.tf, sc.m, r.subs, r.moments, global_sum=True)
+            grown = own.workspace_bytes() - before
+            seg = own.segment_counts(H, W)
+            r.per_sub.fill_(-1.0)
+            own.moments_pass(r.mesh, r.view, r.tf, sc.m, r.subs, r.per_sub)
+            got.append([r.moments.clone(), seg, r.per_sub.clone(), own.segment_counts(H, W)])
+        assert (grown >= 8 * 5 * W * H) == pairs
+        for a, b in zip(*got):
+            assert torch.equal(a, b)
+    finally:
+        own.close()

@@ -19,9 +19,11 @@ def program(tmp_path_factory):
     return out, P.LIB_PATH
 
 
-def _run(program, case):
-    res = subprocess.run([program[0], program[1], case], capture_output=True, text=True, timeout=120)
-    assert res.returncode == 0, (case, res.returncode, res.stdout[-2000:], res.stderr[-2000:])
+def _run(program, case, *args):
+    res = subprocess.run([program[0], program[1], case] + [str(a) for a in args], capture_output=True, text=True,
+                         timeout=120)
+    assert res.returncode == 0, (case, args, res.returncode, res.stdout[-2000:], res.stderr[-2000:])
+    return res.stdout
 
 
 @pytest.mark.parametrize("case", ["refused_noalloc", "refused_overflow", "counted_pairs"])
@@ -46,3 +48,14 @@ def test_a_frame_without_room_for_its_pairs_goes_per_tile(program):
 def test_launches_fit_however_large_the_output(program, case):
     """No launch of 2^32 threads in one dimension, which the runtime refuses."""
     _run(program, case)
+
+
+@pytest.mark.parametrize("w,h,n_sub,tets_each,form", [
+    (384, 384, 1, 1, "tiles"), (392, 384, 1, 1, "pairs"), (768, 768, 1, 1, "pairs"), (776, 768, 1, 1, "tiles"),
+    (8, 8, 1, 1, "tiles"), (8, 8, 2, 1, "pairs"), (768, 768, 2, 1, "pairs"), (776, 768, 3, 9000, "tiles"),
+    (776, 768, 4, 1, "tiles"), (776, 768, 4, 9311, "tiles"), (776, 768, 4, 9312, "pairs"),
+    (776, 768, 8, 1, "pairs"), (1024, 1024, 8, 1, "pairs"), (1032, 1024, 8, 9000, "tiles"),
+])
+def test_stage_one_takes_pairs_where_the_rule_says(program, w, h, n_sub, tets_each, form):
+    """The form on both sides of every line of the rule, for the global sum and for per-subdomain images."""
+    assert _run(program, "route", w, h, n_sub, tets_each).split() == [form, form]
