@@ -40,6 +40,7 @@
 // would round differently.
 #pragma clang fp contract(on)
 
+#include "apc_cut.h"
 #include "apc_internal.h"
 #include "apc_mboit.h"
 
@@ -270,43 +271,6 @@ struct LaneCount {
   unsigned long long* ctr;
   __device__ void rare(int which, unsigned n = 1u) {
     if (n) atomicAdd(ctr + which, (unsigned long long)n);
-  }
-};
-
-// Cuts the chords of one ray at the sampling lattice t_near + k*step.  The
-// chords of a segment meet end to start, so only a chord's end is handed over
-// (to) and the next lattice point carries on from chord to chord.  The cut
-// points and mid depths are FP64 (depths are absolute positions along the
-// ray); lengths and scalars are FP32.
-struct Cutter {
-  double u = 0.0, t1 = 0.0, nxt = 0.0;  // cut so far, chord end, the next lattice point
-  float s1 = 0.0f, slope = 0.0f;        // scalar at the chord's end and along it
-
-  __device__ __forceinline__ bool cutting() const { return u < t1; }
-  // a segment begins at depth t with scalar s
-  __device__ __forceinline__ void start(const FrameDev& f, double t, float s) {
-    u = t1 = t;
-    s1 = s;
-    nxt = fma(floor((t - f.t_near) * f.inv_step) + 1.0, f.step, f.t_near);
-    if (!(nxt > t)) nxt += f.step;  // the rounded floor can fall one short
-  }
-  // the next chord ends at depth t with scalar s
-  __device__ __forceinline__ void to(const FrameDev& f, double t, float s) {
-    const double len = t - t1;
-    slope = (s - s1) * __builtin_amdgcn_rcpf(float(len));
-    t1 = t;
-    s1 = s;
-    if (f.long_chords && !(len <= f.max_chord)) nxt = HUGE_VAL;  // never that many pieces: the chord is one
-  }
-  // the next piece of the chord: its mid depth from the eye (over the range's geometric mean), length and scalar
-  __device__ __forceinline__ void piece(const FrameDev& f, float& wt, float& len, float& s) {
-    const bool lat = nxt <= t1;
-    const double v = lat ? nxt : t1, sum = u + v;
-    wt = float(fma(sum, f.w_scale, f.w_off));
-    len = float(v - u);
-    s = fmaf(slope, float(fma(0.5, sum, -t1)), s1);
-    nxt = lat ? nxt + f.step : nxt;
-    u = v;
   }
 };
 
