@@ -2,6 +2,7 @@
 import ctypes as C
 import os
 import subprocess
+from fractions import Fraction
 
 import numpy as np
 import pytest
@@ -38,3 +39,20 @@ def test_a_chord_too_long_to_cut_is_one_piece_and_the_others_are_cut(cut):
     want = inside[1:] - inside[:-1] + 1  # (no end is a lattice point)
     want[[1, 4]] = 1
     assert pieces.tolist() == want.tolist()
+
+
+@pytest.mark.parametrize("step", [1e-3, 1.0 / 3.0 * 1e-6, 0.7e-7])
+def test_cut_points_are_lattice_points_to_the_last(cut, step):
+    """The last of up to 7 million cut points of a segment of 5000 chords is its lattice point t_near + k * step
+    rounded once, as the first is: a unit in the last place at most."""
+    t_near = -0.85
+    at = np.concatenate([[-0.513], -0.5 + 0.49 * np.cumsum(np.linspace(1.0, 3.0, 5000)) / 10000.0])
+    pieces, ends = cut(t_near, step, 1e9, at, keep=9)
+    assert pieces.sum() > 0.48 / step
+    n = int(pieces.sum())
+    for e in (ends[i % 9] for i in range(n - 8, n)):
+        if e in at:
+            continue  # a chord's end
+        k = round((Fraction(float(e)) - Fraction(t_near)) / Fraction(step))
+        point = Fraction(t_near) + k * Fraction(step)
+        assert abs(Fraction(float(e)) - point) <= Fraction(float(np.spacing(abs(e))))
