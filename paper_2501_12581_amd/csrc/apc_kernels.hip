@@ -282,6 +282,13 @@ __device__ __forceinline__ void tf_coord(const FrameDev& f, float s, int& i0, fl
   fr = __builtin_amdgcn_fractf(u);
 }
 
+// Kappa times a table entry's alpha, within what the differences of two and their products with a fraction can
+// hold: an infinite product caps every piece all the same, and infinity times no alpha is none.
+__device__ __forceinline__ float kappa_alpha(const FrameDev& f, float alpha) {
+  const float k = f.kappa * alpha;
+  return k == k ? __builtin_amdgcn_fmed3f(k, -0.25f * FLT_MAX, 0.25f * FLT_MAX) : 0.0f;
+}
+
 // Optical depth of a piece (Alg. 2: absorbance capped) from kappa times the
 // transfer function's alpha at its scalar and its length, and its warped depth
 // (log depth rescaled to [-1, 1], clamped to the range) from its mid depth
@@ -761,7 +768,7 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(WALK_WAVES
   __shared__ int ent_c[E_MAX * WAVE];
   const int lane = threadIdx.x;
   for (int i = lane; i < f.n_tf; i += WAVE) {
-    const float a0 = f.kappa * tf_rgba[4 * i + 3], a1 = f.kappa * tf_rgba[4 * min(i + 1, f.n_tf - 1) + 3];
+    const float a0 = kappa_alpha(f, tf_rgba[4 * i + 3]), a1 = kappa_alpha(f, tf_rgba[4 * min(i + 1, f.n_tf - 1) + 3]);
     tfa[i] = make_float2(a0, a1 - a0);
   }
   __shared__ unsigned long long blk_base;
@@ -1258,7 +1265,7 @@ __global__ __launch_bounds__(2 * WAVE) __attribute__((amdgpu_waves_per_eu(PairSh
   __shared__ int next_tile;
   for (int i = threadIdx.x; i <= f.n_tf; i += 2 * WAVE) {  // (the last entry twice: the end of an interpolation)
     const float* e = tf_rgba + 4 * min(i, f.n_tf - 1);
-    tf[i] = make_float4(e[0], e[1], e[2], f.kappa * e[3]);
+    tf[i] = make_float4(e[0], e[1], e[2], kappa_alpha(f, e[3]));
   }
   // PAIRS (a launch over pair_list): this workgroup walks the one (tile, subdomain) pair `pair` and writes
   // its colour sums, unfinalised, to part[pair]; else every subdomain of its tile, into the image
