@@ -1772,9 +1772,29 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_bin_sums(const int* __restrict
   }
 }
 
-// offsets and cursors, pidx, totals (records, pairs): each may be null
+// supers[i]: records of the workgroups from i * SCAN_TILE on << 24 | their pairs (at most SCAN_TILE^2)
+__global__ __launch_bounds__(SCAN_THREADS) void k_bin_supers(const unsigned long long* __restrict__ sums, int64_t n,
+                                                             unsigned long long* __restrict__ supers) {
+  __shared__ unsigned long long part[SCAN_THREADS / WAVE];
+  unsigned long long t = 0;
+  for (int k = threadIdx.x; k < SCAN_TILE; k += SCAN_THREADS) {
+    const int64_t at = int64_t(blockIdx.x) * SCAN_TILE + k;
+    const unsigned long long v = at < n ? sums[at] : 0;
+    t += ((v >> 12) << 24) + (v & 0xfffu);
+  }
+  t = wave_sum64(t);
+  if (threadIdx.x % WAVE == 0) part[threadIdx.x / WAVE] = t;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < SCAN_THREADS / WAVE; ++w) t += part[w];
+    supers[blockIdx.x] = t;
+  }
+}
+
+// supers, offsets and cursors, pidx, totals (records, pairs): each may be null
 __global__ __launch_bounds__(SCAN_THREADS) void k_bin_scan(const int* __restrict__ counts, int64_t nb,
                                                            const unsigned long long* __restrict__ sums,
+                                                           const unsigned long long* __restrict__ supers,
                                                            int* __restrict__ offsets, int* __restrict__ cursors,
                                                            int* __restrict__ pidx,
                                                            unsigned long long* __restrict__ totals) {
@@ -1785,7 +1805,12 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_bin_scan(const int* __restrict
   int v[SCAN_ITEMS];
   load_bins(counts, at, nb, v);
   unsigned long long rec = 0, pairs = 0;  // before this workgroup's bins
-  for (unsigned w = threadIdx.x; w < blockIdx.x; w += SCAN_THREADS) {
+  const unsigned whole = supers ? blockIdx.x / SCAN_TILE : 0u;
+  for (unsigned w = threadIdx.x; w < whole; w += SCAN_THREADS) {
+    rec += supers[w] >> 24;
+    pairs += supers[w] & 0xffffffu;
+  }
+  for (unsigned w = whole * SCAN_TILE + threadIdx.x; w < blockIdx.x; w += SCAN_THREADS) {
     rec += sums[w] >> 12;
     pairs += sums[w] & 0xfffu;
   }
@@ -2120,7 +2145,12 @@ hipError_t launch_bin_scan(const int* counts, int64_t nb, int* offsets, int* cur
   unsigned long long* sums = reinterpret_cast<unsigned long long*>(tmp);
   const dim3 grid(grid1(nb, SCAN_TILE)), block(SCAN_THREADS);
   hipLaunchKernelGGL(k_bin_sums, grid, block, 0, s, counts, nb, sums);
-  hipLaunchKernelGGL(k_bin_scan, grid, block, 0, s, counts, nb, sums, offsets, cursors, pidx, totals);
+  unsigned long long* supers = nullptr;
+  if (grid.x > SCAN_TILE) {
+    supers = sums + grid.x;
+    hipLaunchKernelGGL(k_bin_supers, dim3(grid1(grid.x, SCAN_TILE)), block, 0, s, sums, int64_t(grid.x), supers);
+  }
+  hipLaunchKernelGGL(k_bin_scan, grid, block, 0, s, counts, nb, sums, supers, offsets, cursors, pidx, totals);
   return hipGetLastError();
 }
 

@@ -83,11 +83,13 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
   if (!l.grid || uint64_t(grid.x) * block.x >= (1ull << 32)) return g_last = hipErrorInvalidConfiguration;
   auto is = [&](const char* k) { return l.name.find(k) != std::string::npos; };
   if (is("k_bin_scan"))
-    for (int k = 0; k < 7; ++k) l.arg.push_back(*static_cast<uint64_t*>(args[k]));
+    for (int k = 0; k < 8; ++k) l.arg.push_back(*static_cast<uint64_t*>(args[k]));
+  if (is("k_bin_supers"))
+    for (int k = 0; k < 3; ++k) l.arg.push_back(*static_cast<uint64_t*>(args[k]));
   if (is("k_pair_list"))
     for (int k = 0; k < 5; ++k) l.arg.push_back(*static_cast<uint64_t*>(args[k]));
-  if (is("k_bin_scan") && l.arg[6]) {
-    unsigned long long* totals = reinterpret_cast<unsigned long long*>(l.arg[6]);
+  if (is("k_bin_scan") && l.arg[7]) {
+    unsigned long long* totals = reinterpret_cast<unsigned long long*>(l.arg[7]);
     totals[0] = g_records;
     totals[1] = g_pairs;
   }
@@ -357,7 +359,7 @@ int lost_numbers() {
   CHECK(s.resolve(small, APC_BY_PAIR) == APC_OK);
   uint64_t numbers = 0;
   for (const Launch& l : g_launches) {
-    if (l.name.find("k_bin_scan") != std::string::npos) numbers = l.arg[5];
+    if (l.name.find("k_bin_scan") != std::string::npos) numbers = l.arg[6];
     if (l.name.find("k_pair_list") != std::string::npos) CHECK(numbers && l.arg[2] == numbers);
   }
   return 0;
@@ -418,6 +420,25 @@ int thin_images() {
   return 0;
 }
 
+// The scan of very many bins adds up the sums of its workgroups in two levels, within its scratch memory.
+int many_bins() {
+  Scene s(72);
+  g_records = 10;
+  g_pairs = 4;
+  CHECK(s.resolve(s.view(8192, 8192), 0) == APC_OK);  // 75.5M bins, 36864 workgroups
+  bool two = false;
+  for (const Launch& l : g_launches)
+    if (l.name.find("k_bin_supers") != std::string::npos) {
+      two = true;
+      CHECK(l.arg[1] == 36864 && l.grid == 18);
+      const auto buf = g_mem.find(reinterpret_cast<void*>(l.arg[0]));
+      CHECK(buf != g_mem.end());
+      CHECK(l.arg[2] >= l.arg[0] + 8 * 36864 && l.arg[2] + 8 * 18 <= l.arg[0] + buf->second);
+    }
+  CHECK(two);
+  return 0;
+}
+
 // Which form stage one takes: <width> <height> <subdomains> <tets of each>.
 int route(int w, int h, int n_sub, int tets_each) {
   Scene s(n_sub, tets_each);
@@ -444,6 +465,7 @@ int main(int argc, char** argv) {
       {"large_images", large_images},
       {"large_pair_lists", large_pair_lists},
       {"thin_images", thin_images},
+      {"many_bins", many_bins},
   };
   const bool routes = argc == 7 && std::string(argv[2]) == "route";
   if (!routes && (argc != 3 || !cases.count(argv[2]))) return 2;

@@ -135,3 +135,36 @@ def test_both_forms_of_stage_one_on_both_sides_of_the_line(apc, W, H, n_sub, pai
             assert torch.equal(a, b)
     finally:
         own.close()
+
+
+@pytest.mark.parametrize("size,n_sub", [(1024, 36), (2048, 72), (2896, 64)])
+def test_numbers_and_offsets_of_millions_of_bins(apc, ctx, size, n_sub):
+    """589,824, 4.7 and 8.4 million bins (more workgroups of the scan than one has threads, and the sums in two
+    levels): the list of the pairs is exactly that of the subdomains binned one at a time, and the tiles' sum is bit
+    for bit the per-tile pass's."""
+    sc = _scene(size, size, n_sub)
+    sc.view = synth.perspective_view((0.5, 2.3, 0.9), (0.5, 0.5, 0.5), size, size)
+    sc.m, sc.bias = 4, synth.default_bias(4)
+    r = apc.Renderer(ctx, sc)
+    want = []
+    for k in range(n_sub):
+        one = r.subs[k:k + 1]
+        n = ctx.moments_pass_tiles(r.mesh, r.view, r.tf, 4, one, None, None, by_pair=True)
+        tiles = torch.empty((n, 5, 64), device="cuda")
+        bins = torch.empty(n, dtype=torch.int32, device="cuda")
+        assert ctx.moments_pass_tiles(r.mesh, r.view, r.tf, 4, one, tiles, bins, by_pair=True) == n
+        want.append(bins.long() * n_sub + k)
+    want = torch.cat(want).sort().values
+    tiles = torch.empty((len(want), 5, 64), device="cuda")
+    bins = torch.empty(len(want), dtype=torch.int32, device="cuda")
+    assert ctx.moments_pass_tiles(r.mesh, r.view, r.tf, 4, r.subs, tiles, bins, by_pair=True) == len(want)
+    assert torch.equal(bins.long(), want)
+    ctx.sum_moment_tiles(tiles, bins, len(want), n_sub, 4, size, size, r.moments)
+    by_pair = r.moments.clone()
+    try:
+        ctx.set_dispatch(apc.APC_DISPATCH_QUEUE)
+        ctx.moments_pass(r.mesh, r.view, r.tf, 4, r.subs, r.moments, global_sum=True)
+        torch.cuda.synchronize()
+    finally:
+        ctx.set_dispatch(apc.APC_DISPATCH_GRID)
+    assert torch.equal(by_pair, r.moments)

@@ -59,3 +59,8 @@ def test_launches_fit_however_large_the_output(program, case):
 def test_stage_one_takes_pairs_where_the_rule_says(program, w, h, n_sub, tets_each, form):
     """The form on both sides of every line of the rule, for the global sum and for per-subdomain images."""
     assert _run(program, "route", w, h, n_sub, tets_each).split() == [form, form]
+
+
+def test_the_scan_of_very_many_bins_has_two_levels(program):
+    """The work of the bins' scan grows with the bins, not with their square."""
+    _run(program, "many_bins")
