@@ -1020,12 +1020,18 @@ static constexpr size_t STAGE_ONE_PAIR_BYTES = size_t(256) << 20;
 
 // The buffers of stage one by pairs; false: too large, or not to be had (the per-tile form needs none of them), or
 // more pairs than one launch holds wavefronts of (2^32 threads).
-static bool pairs_fit(apc_ctx ctx, int mm, bool global) {
+static bool pairs_fit(apc_ctx ctx, int mm, int64_t bins, bool global) {
   const size_t pairs = size_t(std::max<int64_t>(ctx->bin_pairs, 1)), bytes = sizeof(float) * 64 * (mm + 1) * pairs;
   if (global && bytes > STAGE_ONE_PAIR_BYTES) return false;
   if (pairs >= size_t(1) << 26) return false;
-  const bool ok = ctx->rpair.ensure(sizeof(int) * pairs) == hipSuccess &&
-                  (!global || ctx->mtile.ensure(bytes) == hipSuccess);
+  bool ok = ctx->rpair.ensure(sizeof(int) * pairs) == hipSuccess;
+  if (ok && global && bytes > ctx->mtile.bytes) {
+    // room for views with more pairs, twice this one's within the bound and what the frame's bins can hold: to grow
+    // is a release and an allocation, which wait for the device
+    const size_t all = sizeof(float) * 64 * (mm + 1) * size_t(bins);
+    ok = ctx->mtile.ensure(std::min(std::min(2 * bytes, all), STAGE_ONE_PAIR_BYTES), false) == hipSuccess ||
+         ctx->mtile.ensure(bytes, false) == hipSuccess;
+  }
   if (!ok) (void)hipGetLastError();
   return ok;
 }
@@ -1080,7 +1086,7 @@ apc_status apc_moments_pass(apc_ctx ctx, apc_mesh m, const apc_view* view, const
     few = false;
   }
   if ((st = build_bins(ctx, m, view, f, subs, n_sub, few, s, md)) != APC_OK) return st;
-  if (few && pairs_fit(ctx, mm, global)) {
+  if (few && pairs_fit(ctx, mm, int64_t(f.n_tiles) * n_sub, global)) {
     ctx->store_ready = false;
     if ((st = moments_by_pair(ctx, view, tf, mm, md, f, n_sub, out, global, s)) != APC_OK) return st;
     set_piece_key(ctx, m, view, subs, n_sub);

@@ -31,7 +31,8 @@ std::vector<Launch> g_launches;
 std::map<const void*, std::string> g_kernels;
 std::map<void*, size_t> g_mem;
 size_t g_fail_above = SIZE_MAX;  // device allocations of more bytes are refused
-size_t g_refuse_from = 1, g_refuse_to = 0;  // the next device allocation of a size between these is refused
+size_t g_refuse_from = 1, g_refuse_to = 0;  // the next so many device allocations of sizes between these are refused
+int g_refusals = 0;
 unsigned long long g_records = 0, g_pairs = 0;  // what the scan of the bins reports
 uint64_t g_issued = 0, g_done = 0;              // work handed to the device, and waited for (one stream at a time)
 hipError_t g_last = hipSuccess;
@@ -108,8 +109,8 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
 }
 
 hipError_t hipMalloc(void** p, size_t n) {
-  const bool refuse = n >= g_refuse_from && n <= g_refuse_to;
-  if (refuse) g_refuse_to = 0;
+  const bool refuse = g_refusals > 0 && n >= g_refuse_from && n <= g_refuse_to;
+  if (refuse) --g_refusals;
   if (n > g_fail_above || refuse) {
     *p = nullptr;
     return hipErrorOutOfMemory;
@@ -375,9 +376,10 @@ int refused_pair_buffers() {
     g_pairs = 20000;
     g_refuse_from = from[which];
     g_refuse_to = to[which];
+    g_refusals = which == 2 ? 2 : 1;  // (the moments are asked for twice: with room and without)
     g_launches.clear();
     CHECK(s.moments_pass(s.view(768, 768), APC_MOMENTS_GLOBAL) == APC_OK);
-    CHECK(g_refuse_to == 0);
+    CHECK(g_refusals == 0);
     uint64_t walks = 0;
     for (const Launch& l : g_launches)
       if (l.name.find("k_moments") != std::string::npos) walks = l.grid;
@@ -417,6 +419,37 @@ int thin_images() {
   for (const Launch& l : g_launches)
     if (l.name.find("k_sum_tiles") != std::string::npos) blocks = l.grid * (l.block / 64);
   CHECK(blocks >= 1u << 27);
+  return 0;
+}
+
+// The buffer of the pairs' moments: at most 256 MiB, twice what the first frame needs, never more than the bins of
+// the frame can fill, and in place for a view with more pairs.
+int moments_buffer() {
+  auto largest = [] {
+    size_t n = 0;
+    for (auto& m : g_mem) n = m.second > n ? m.second : n;
+    return n;
+  };
+  const size_t tile = 64 * 9 * sizeof(float);
+  {
+    Scene s(8);
+    g_records = 10;
+    g_pairs = (size_t(255) << 20) / tile;
+    CHECK(s.moments_pass(s.view(1000, 1000), APC_MOMENTS_GLOBAL) == APC_OK);
+    CHECK(largest() == size_t(256) << 20);
+    APC(apc_destroy)(s.ctx);
+  }
+  Scene s(8);
+  g_pairs = 4000;
+  CHECK(s.moments_pass(s.view(512, 512), APC_MOMENTS_GLOBAL) == APC_OK);
+  CHECK(largest() == 8000 * tile);
+  g_pairs = 7900;
+  const size_t held = device_bytes();
+  CHECK(s.moments_pass(s.view(512, 504), APC_MOMENTS_GLOBAL) == APC_OK);
+  CHECK(largest() == 8000 * tile && device_bytes() - held < (64 << 10));  // (the pairs' list)
+  g_pairs = 512 * 504 / 64 * 8;  // every bin
+  CHECK(s.moments_pass(s.view(504, 512), APC_MOMENTS_GLOBAL) == APC_OK);
+  CHECK(largest() == g_pairs * tile);
   return 0;
 }
 
@@ -466,6 +499,7 @@ int main(int argc, char** argv) {
       {"large_pair_lists", large_pair_lists},
       {"thin_images", thin_images},
       {"many_bins", many_bins},
+      {"moments_buffer", moments_buffer},
   };
   const bool routes = argc == 7 && std::string(argv[2]) == "route";
   if (!routes && (argc != 3 || !cases.count(argv[2]))) return 2;

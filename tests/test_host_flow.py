@@ -64,3 +64,8 @@ def test_stage_one_takes_pairs_where_the_rule_says(program, w, h, n_sub, tets_ea
 def test_the_scan_of_very_many_bins_has_two_levels(program):
     """The work of the bins' scan grows with the bins, not with their square."""
     _run(program, "many_bins")
+
+
+def test_the_buffer_of_the_pairs_moments_is_bounded(program):
+    """256 MiB at most, slack included, and room for a view with more pairs."""
+    _run(program, "moments_buffer")
