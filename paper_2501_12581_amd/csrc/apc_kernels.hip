@@ -1736,7 +1736,7 @@ __global__ void k_sum_images(const float4* __restrict__ in, int n_slots, const i
 
 // ------------------------------------------------------------------ scan / fill
 
-constexpr int SCAN_THREADS = 256, SCAN_ITEMS = 8, SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
+constexpr int SCAN_THREADS = 256, SCAN_ITEMS = 8, SCAN_TILE = SCAN_THREADS * SCAN_ITEMS, SCAN_DIRECT = 8192;
 
 // The bins' scan: where each bin's records start (the exclusive sums of the counts) and the numbers of the bins
 // that have any (the pairs), with the fill pass's cursors cleared on the way.  Two launches: the sums of each
@@ -2146,7 +2146,7 @@ hipError_t launch_bin_scan(const int* counts, int64_t nb, int* offsets, int* cur
   const dim3 grid(grid1(nb, SCAN_TILE)), block(SCAN_THREADS);
   hipLaunchKernelGGL(k_bin_sums, grid, block, 0, s, counts, nb, sums);
   unsigned long long* supers = nullptr;
-  if (grid.x > SCAN_TILE) {
+  if (grid.x > SCAN_DIRECT) {
     supers = sums + grid.x;
     hipLaunchKernelGGL(k_bin_supers, dim3(grid1(grid.x, SCAN_TILE)), block, 0, s, sums, int64_t(grid.x), supers);
   }

@@ -137,11 +137,11 @@ def test_both_forms_of_stage_one_on_both_sides_of_the_line(apc, W, H, n_sub, pai
         own.close()
 
 
-@pytest.mark.parametrize("size,n_sub", [(1024, 36), (2048, 72), (2896, 64)])
+@pytest.mark.parametrize("size,n_sub", [(1024, 36), (4096, 64), (4096, 72)])
 def test_numbers_and_offsets_of_millions_of_bins(apc, ctx, size, n_sub):
-    """589,824, 4.7 and 8.4 million bins (more workgroups of the scan than one has threads, and the sums in two
-    levels): the list of the pairs is exactly that of the subdomains binned one at a time, and the tiles' sum is bit
-    for bit the per-tile pass's."""
+    """589,824, 16.8 and 18.9 million bins (more workgroups of the scan than one has threads; the last with its sums
+    in two levels): the list of the pairs is exactly that of the subdomains binned one at a time, and the tiles' sum is
+    bit for bit the per-tile pass's."""
     sc = _scene(size, size, n_sub)
     sc.view = synth.perspective_view((0.5, 2.3, 0.9), (0.5, 0.5, 0.5), size, size)
     sc.m, sc.bias = 4, synth.default_bias(4)
