@@ -14,8 +14,8 @@ moments_pair_max_tiles tiles and stage two of one of at most pair_max_tiles tile
 pairs in parallel (such a frame has too few tiles to fill the device one workgroup per tile; a larger one
 is faster per tile):
 stage one into buffers the slot sized when it was warmed, whose ordered sum gives the same global moments
-(a frame with more pairs than the buffers hold takes the per-tile form instead, counted, never an
-allocation), and stage two (APC_BY_PAIR) into the library's pair buffers, the image to FP32 rounding.  Every step of a frame runs in the library's
+(a frame with more pairs than the buffers hold takes the per-tile form instead, counted, in buffers
+sized then too), and stage two (APC_BY_PAIR) into the library's pair buffers, the image to FP32 rounding.  Every step of a frame runs in the library's
 kernels; this module only schedules, allocates buffers and times.
 """
 from __future__ import annotations
@@ -138,6 +138,11 @@ class Server:
                 self.render(k, req)
                 for size in sizes:  # the largest frames by pairs of each pass size their buffers
                     self.render(k, {**req, "size": size})
+            if self.pair_bufs[k] is not None:  # the form of a frame with more pairs than these buffers hold
+                view, tfd, _ = self._frame_args({**req, "size": ps})
+                mom = self.bufs[k][0][: (self.max_m + 1) * ps * ps].view(self.max_m + 1, ps, ps)
+                self._moments_per_tile(k, view, tfd, self.max_m, mom, self.slots[k][1].cuda_stream)
+                self.slots[k][1].synchronize()
         self.slot_ws = [c.workspace_bytes() + (0 if b is None else b[0].numel() * 4 + b[1].numel() * 4)
                         for (c, _), b in zip(self.slots, self.pair_bufs)]
 
@@ -204,6 +209,18 @@ class Server:
         ctx.sum_moment_tiles(tiles, bins, n, len(self.subs), m, view.height, view.width, mom, s)
         return True
 
+    def _moments_per_tile(self, slot, view, tf, m, mom, s):
+        """Stage one per tile: a work queue is of tiles, where the grid of a small frame may be of pairs, into buffers
+        that the library then sizes for the frame's pairs."""
+        from . import APC_DISPATCH_QUEUE
+        ctx, _ = self.slots[slot]
+        mode = ctx.dispatch()
+        ctx.set_dispatch(APC_DISPATCH_QUEUE)
+        try:
+            ctx.moments_pass(self.mesh, view, tf, m, self.subs, mom, s, global_sum=True)
+        finally:
+            ctx.set_dispatch(mode)
+
     def render(self, slot: int, req) -> "object":
         """One frame for `req` on slot `slot` (stage one, moment sum, resolve); returns the RGBA image (a view
         of the slot's buffer, valid until the slot's next request) after the slot's stream has finished it."""
@@ -223,10 +240,11 @@ class Server:
         tiles = self._pair_tiles(slot, W)
         pairs = self.by_pair and not self.keep
         one_by_pair = pairs and self.pair_bufs[slot] is not None and tiles <= self.moments_pair_max_tiles
-        if not (one_by_pair and self._moments_by_pair(slot, view, tf, m, mom, s)):
-            if one_by_pair:
-                self.pair_overflow[slot] += 1
+        if not one_by_pair:
             ctx.moments_pass(self.mesh, view, tf, m, self.subs, mom, s, global_sum=True, keep=self.keep)
+        elif not self._moments_by_pair(slot, view, tf, m, mom, s):
+            self.pair_overflow[slot] += 1
+            self._moments_per_tile(slot, view, tf, m, mom, s)
         ctx.resolve_pass(self.mesh, view, tf, mb, mom, self.subs, rgba, finalize=True, stream=s,
                          by_pair=pairs and tiles <= self.pair_max_tiles)
         ev1.record(stream)

@@ -221,3 +221,32 @@ def test_a_request_over_the_budget_waits():
         assert st["device_overlap_frac"] > 0
     finally:
         srv.close()
+
+
+def test_a_frame_with_more_pairs_than_the_buffers_allocates_nothing():
+    """A slot warmed with a distant view, whose few pairs size its buffers: a near view overflows them and runs in the
+    buffers that the slot has (its bins are sized beforehand here): its workspace and footprint stay, the dispatch
+    mode too, and the image is that of a slot whose pairs fit."""
+    from paper_2501_12581_amd.serve import Server
+    sc = synth.scene_medium(size=128)
+    m = sc.mesh
+    args = ((m.xyz, m.scalar, m.tets, m.tet_sub, m.n_sub), sc.step, [synth.make_tf(13)], (sc.s_min, sc.s_max))
+    kw = dict(slots=1, workspace_limit=1 << 30, hbm_budget=1 << 30, max_size=768, by_pair=True)
+    far, near = Server(*args, **kw), Server(*args, **kw)
+    try:
+        far.warm(eye=(30.0, 13.5, 10.5))
+        near.warm()
+        ctx, stream = far.slots[0]
+        for mm in (8, 4):
+            req = {"id": 0, "arrival": 0.0, "size": 768, "eye": (2.0, 0.9, 0.7), "m": mm, "tf": 0}
+            view, tf, _ = far._frame_args(req)
+            ctx.moments_pass_tiles(far.mesh, view, tf, mm, far.subs, stream=stream.cuda_stream, by_pair=True)
+            held, counted, over = ctx.workspace_bytes(), far.footprint(req), far.pair_overflow[0]
+            got = far.render(0, req).clone()
+            assert far.pair_overflow[0] == over + 1
+            assert ctx.workspace_bytes() == held and far.footprint(req) == counted
+            assert ctx.dispatch() == 0  # one workgroup per tile or pair
+            assert torch.equal(got, near.render(0, req)) and near.pair_overflow[0] == 0
+    finally:
+        far.close()
+        near.close()
