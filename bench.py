@@ -422,10 +422,12 @@ def passes_by_size(ctx, r, seed, sizes=(256, 512, 1024, 2048, 2560)):
     """Both passes of orbit camera 0 at several image sizes on the renderer's mesh: one workgroup per tile
     against one per (tile, subdomain) pair plus the ordered sum of the pairs, each the best of 3 by the
     library's HIP events; stage one's global moments compared bit for bit, stage two's images by their
-    largest difference."""
+    largest difference.  Stage one of a small frame goes by pairs either way: "by_tile" is then the call that
+    sums in the library, "by_pair" the one into the caller's tiles (stage_one_by_tile_is says which it was)."""
     import torch
     import paper_2501_12581_amd as apc
     import synth
+    from paper_2501_12581_amd.serve import LIBRARY_PAIR_TILES
     m, S, out = r.scene.m, len(r.subs), {}
     dev = r.moments.device
     for size in sizes:
@@ -450,6 +452,7 @@ def passes_by_size(ctx, r, seed, sizes=(256, 512, 1024, 2048, 2560)):
                 t = tk["moments_ms"] + (tk["sum_ms"] if form == "by_pair" else 0.0)
                 best = t if best is None else min(best, t)
             res[form + "_ms"] = round(best, 3)
+        res["stage_one_by_tile_is"] = "by pairs" if res["tiles"] <= LIBRARY_PAIR_TILES else "by tiles"
         res["global_moments_bitwise_equal"] = bool(torch.equal(glob, mom))
         rgba2 = torch.empty_like(rgba)
         for form in ("by_tile", "by_pair"):
@@ -558,7 +561,8 @@ def batching_leg(bsc, steps=5):
 def serve_leg(n_requests, n_requests_30, sc):
     """p50/p99 frame latency of a served request stream on the batching configuration's mesh: batched
     (continuous batching over slots) against one request at a time, both in the plain form with both passes by
-    (tile, subdomain) pairs; at 30 requests/s also with both passes by tiles."""
+    (tile, subdomain) pairs; at 30 requests/s also asked for by tiles (stage one of small frames goes by pairs
+    inside the library then, too: each run's "stage_one")."""
     import synth
     from paper_2501_12581_amd.serve import Server
     t0 = time.time()

@@ -255,7 +255,9 @@ class Server:
 
     def run(self, requests, mode="batched", keep_images=False) -> dict:
         """Serve `requests` (dicts with arrival [s], size, eye, m, tf) open loop: request k is released at
-        its arrival time after the start.  Returns per-request records and latency statistics."""
+        its arrival time after the start.  Returns per-request records and latency statistics; "passes" says how
+        the server asks for its frames, "stage_one" how their first pass is walked then (a frame that is asked for
+        by tiles and is small goes by pairs inside the library)."""
         if mode not in ("batched", "fifo"):
             raise ValueError(mode)
         n_slots = len(self.slots) if mode == "batched" else 1
@@ -278,6 +280,9 @@ class Server:
         st["device_overlap_frac"] = device_overlap(st["records"])
         st["passes"] = ("by (tile, subdomain) pairs up to %d (stage one) and %d (stage two) tiles per frame, else "
                         "by tiles" % (self.moments_pair_max_tiles, self.pair_max_tiles) if self.by_pair else "by tiles")
+        most = self.moments_pair_max_tiles if self.by_pair else 0
+        st["stage_one"] = "by tiles" if self.keep else (
+            "by (tile, subdomain) pairs up to %d tiles per frame, else by tiles" % max(most, LIBRARY_PAIR_TILES))
         if self.by_pair:
             st["pair_buffer_overflows"] = int(sum(self.pair_overflow))
         self.t_ref = None

@@ -250,3 +250,21 @@ def test_a_frame_with_more_pairs_than_the_buffers_allocates_nothing():
     finally:
         far.close()
         near.close()
+
+
+def test_a_run_says_how_stage_one_was_walked(server):
+    """Frames asked for by tiles go by pairs inside the library where they are small: the record says so; only a
+    server that keeps pieces walks tiles throughout."""
+    from paper_2501_12581_amd.serve import Server
+    srv, sc, tfs = server
+    req = [{"id": 0, "arrival": 0.0, "size": 96, "eye": (2.2, 0.4, 1.1), "m": 4, "tf": 0}]
+    st = srv.run(req, "fifo")
+    assert st["passes"] == "by tiles" and st["stage_one"].startswith("by (tile, subdomain) pairs up to 16384 tiles")
+    m = sc.mesh
+    keep = Server((m.xyz, m.scalar, m.tets, m.tet_sub, m.n_sub), sc.step, tfs, (sc.s_min, sc.s_max), slots=1,
+                  workspace_limit=1 << 28, max_size=96, keep=True)
+    try:
+        st = keep.run(req, "fifo")
+        assert st["passes"] == st["stage_one"] == "by tiles"
+    finally:
+        keep.close()
