@@ -141,7 +141,7 @@ struct apc_ctx_s {
   DevBuf gacc;  // FP64 [m+1][H][W] partial sums of APC_MOMENTS_GLOBAL
   int seg_h = 0, seg_w = 0;
   // the pieces per pixel in `pcount` belong to this (mesh, view, subdomain list)
-  const void* pc_mesh = nullptr;
+  uint64_t pc_mesh = 0;
   apc_view pc_view;
   int pc_tw_log2 = -1;
   std::vector<int> pc_subs;
@@ -536,7 +536,7 @@ apc_status build_bins(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const
 }
 
 void set_piece_key(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const int32_t* subs, int32_t n_sub) {
-  ctx->pc_mesh = m;
+  ctx->pc_mesh = m->uid;
   ctx->pc_view = *v;
   ctx->pc_tw_log2 = ctx->tw_log2;
   ctx->pc_subs.assign(subs, subs + n_sub);
@@ -546,7 +546,7 @@ void set_piece_key(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const in
 // Do the pieces per pixel in the context belong to this mesh, camera, lattice
 // and subdomain list?  (They do not depend on the transfer function or m.)
 bool piece_key_matches(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const int32_t* subs, int32_t n_sub) {
-  return ctx->pc_valid && ctx->pc_mesh == m && ctx->pc_tw_log2 == ctx->tw_log2 &&
+  return ctx->pc_valid && ctx->pc_mesh == m->uid && ctx->pc_tw_log2 == ctx->tw_log2 &&
          std::memcmp(&ctx->pc_view, v, sizeof(apc_view)) == 0 &&
          ctx->pc_subs.size() == size_t(n_sub) && std::equal(ctx->pc_subs.begin(), ctx->pc_subs.end(), subs);
 }

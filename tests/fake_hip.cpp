@@ -241,7 +241,8 @@ F sym(const char* name) {
 struct Scene {
   apc_ctx ctx = nullptr;
   apc_mesh mesh = nullptr;
-  std::vector<int32_t> subs;
+  std::vector<float> xyz, scalar;
+  std::vector<int32_t> tet, of, subs;
   apc_tf tf = {};
   apc_mboit mb = {};
   std::vector<float> table;
@@ -249,27 +250,17 @@ struct Scene {
 
   explicit Scene(int n_sub, int tets_each = 1) : table(8, 0.5f) {
     if (APC(apc_create)(0, &ctx) != APC_OK) exit(4);
-    std::vector<float> xyz, scalar;
-    std::vector<int32_t> tets, of;
     for (int k = 0; k < n_sub * tets_each; ++k) {
       const float p[4][3] = {{0, 0, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
       for (int q = 0; q < 4; ++q) {
         for (int c = 0; c < 3; ++c) xyz.push_back(p[q][c] + (c == 2 ? 2.0f * float(k) : 0.0f));
         scalar.push_back(float(q));
-        tets.push_back(4 * k + q);
+        tet.push_back(4 * k + q);
       }
       of.push_back(k / tets_each);
     }
     for (int k = 0; k < n_sub; ++k) subs.push_back(k);
-    apc_mesh_desc d = {};
-    d.n_vertices = int64_t(scalar.size());
-    d.n_tets = n_sub * tets_each;
-    d.n_subdomains = n_sub;
-    d.xyz = xyz.data();
-    d.scalar = scalar.data();
-    d.tet_vertices = tets.data();
-    d.tet_subdomain = of.data();
-    if (APC(apc_load_mesh)(ctx, &d, &mesh, nullptr) != APC_OK) exit(5);
+    load();
     tf.n_entries = 2;
     tf.rgba = table.data();
     tf.s_max = 3.0f;
@@ -280,6 +271,17 @@ struct Scene {
     mb.alpha = 5e-5;
     mb.eta = 0.3;
     for (int j = 0; j < 8; ++j) mb.bias[j] = (j & 1) ? 1.0 / (j + 2) : 0.0;
+  }
+  void load() {
+    apc_mesh_desc d = {};
+    d.n_vertices = int64_t(scalar.size());
+    d.n_tets = int64_t(of.size());
+    d.n_subdomains = int(subs.size());
+    d.xyz = xyz.data();
+    d.scalar = scalar.data();
+    d.tet_vertices = tet.data();
+    d.tet_subdomain = of.data();
+    if (APC(apc_load_mesh)(ctx, &d, &mesh, nullptr) != APC_OK) exit(5);
   }
   apc_view view(int w, int h) const {
     apc_view v = {};
@@ -453,6 +455,26 @@ int moments_buffer() {
   return 0;
 }
 
+// Kept pieces belong to the mesh they were made from, not to the next one at its address.
+int kept_mesh() {
+  Scene s(2);
+  g_records = 10;
+  g_pairs = 4;
+  const apc_view v = s.view(64, 64);
+  for (int attempt = 0; attempt < 64; ++attempt) {
+    CHECK(s.moments_pass(v, APC_KEEP_PIECES) == APC_OK);
+    const apc_mesh old = s.mesh;
+    APC(apc_free_mesh)(s.ctx, s.mesh);
+    s.load();
+    g_launches.clear();
+    CHECK(s.resolve(v, 0) == APC_OK);
+    for (const Launch& l : g_launches) CHECK(l.name.find("k_eval") == std::string::npos);
+    if (s.mesh == old) return 0;
+  }
+  printf("no address was used again\n");
+  return 1;
+}
+
 // The scan of very many bins adds up the sums of its workgroups in two levels, within its scratch memory.
 int many_bins() {
   Scene s(72);
@@ -498,6 +520,7 @@ int main(int argc, char** argv) {
       {"large_images", large_images},
       {"large_pair_lists", large_pair_lists},
       {"thin_images", thin_images},
+      {"kept_mesh", kept_mesh},
       {"many_bins", many_bins},
       {"moments_buffer", moments_buffer},
   };

@@ -69,3 +69,8 @@ def test_the_scan_of_very_many_bins_has_two_levels(program):
 def test_the_buffer_of_the_pairs_moments_is_bounded(program):
     """256 MiB at most, slack included, and room for a view with more pairs."""
     _run(program, "moments_buffer")
+
+
+def test_kept_pieces_are_not_taken_for_another_mesh_at_the_same_address(program):
+    """A mesh freed and another loaded where it was: stage two walks the new one."""
+    _run(program, "kept_mesh")
