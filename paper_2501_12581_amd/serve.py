@@ -138,10 +138,12 @@ class Server:
                 self.render(k, req)
                 for size in sizes:  # the largest frames by pairs of each pass size their buffers
                     self.render(k, {**req, "size": size})
-            if self.pair_bufs[k] is not None:  # the form of a frame with more pairs than these buffers hold
+            if self.pair_bufs[k] is not None:
+                # the form of a frame with more pairs than these buffers hold: its own buffers depend on the image
+                # alone, so one subdomain sizes them
                 view, tfd, _ = self._frame_args({**req, "size": ps})
                 mom = self.bufs[k][0][: (self.max_m + 1) * ps * ps].view(self.max_m + 1, ps, ps)
-                self._moments_per_tile(k, view, tfd, self.max_m, mom, self.slots[k][1].cuda_stream)
+                self._moments_per_tile(k, view, tfd, self.max_m, mom, self.slots[k][1].cuda_stream, self.subs[:1])
                 self.slots[k][1].synchronize()
         self.slot_ws = [c.workspace_bytes() + (0 if b is None else b[0].numel() * 4 + b[1].numel() * 4)
                         for (c, _), b in zip(self.slots, self.pair_bufs)]
@@ -209,7 +211,7 @@ class Server:
         ctx.sum_moment_tiles(tiles, bins, n, len(self.subs), m, view.height, view.width, mom, s)
         return True
 
-    def _moments_per_tile(self, slot, view, tf, m, mom, s):
+    def _moments_per_tile(self, slot, view, tf, m, mom, s, subs=None):
         """Stage one per tile: a work queue is of tiles, where the grid of a small frame may be of pairs, into buffers
         that the library then sizes for the frame's pairs."""
         from . import APC_DISPATCH_QUEUE
@@ -217,7 +219,7 @@ class Server:
         mode = ctx.dispatch()
         ctx.set_dispatch(APC_DISPATCH_QUEUE)
         try:
-            ctx.moments_pass(self.mesh, view, tf, m, self.subs, mom, s, global_sum=True)
+            ctx.moments_pass(self.mesh, view, tf, m, self.subs if subs is None else subs, mom, s, global_sum=True)
         finally:
             ctx.set_dispatch(mode)
 
