@@ -433,8 +433,6 @@ apc_status bin_faces(apc_ctx ctx, const apc_mesh_s* m, const FrameDev& f, const 
   int max_faces = 0;
   for (int k = 0; k < n_sub; ++k) {
     int id = subs[k];
-    sl[k].tet_begin = m->sub_begin[id];
-    sl[k].tet_end = m->sub_begin[id + 1];
     sl[k].face_begin = m->face_begin[id];
     sl[k].face_end = m->face_begin[id + 1];
     max_faces = std::max(max_faces, sl[k].face_end - sl[k].face_begin);
@@ -449,8 +447,6 @@ apc_status bin_faces(apc_ctx ctx, const apc_mesh_s* m, const FrameDev& f, const 
   md.vert = m->vert;
   md.tet = m->tet;
   md.wrec = m->wrec;
-  md.n_vertices = m->V;
-  md.n_tets = m->T;
   HIPCHK(ev_mark(ctx, EV_BIN, 0, s));
   HIPCHK(apc::launch_fill_i32(B.counts, 0, nb, s));
   HIPCHK(apc::launch_bin_count(md, f, B.slots, max_faces, m->bface, B.counts, s));
@@ -502,8 +498,6 @@ apc_status build_bins(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const
     md.vert = m->vert;
     md.tet = m->tet;
     md.wrec = m->wrec;
-    md.n_vertices = m->V;
-    md.n_tets = m->T;
     if (pairs && ctx->bin_pairs < 0 && !ctx->capturing) {  // binned without them
       HIPCHK(apc::launch_bin_scan(ctx->counts.as<int>(), nb, nullptr, nullptr, ctx->pidx.as<int>(),
                                   ctx->scan_tmp.as<int>(), ctx->totals, s));

@@ -17,13 +17,10 @@ struct MeshDev {
   // [8T]: the walk's records of tet t, one 128-byte line: for each face the
   // tet may be entered through, 32 bytes (k_walk_records)
   const int4* wrec;
-  int64_t n_vertices;
-  int64_t n_tets;
 };
 
 // One subdomain taking part in a call.
 struct SlotDev {
-  int tet_begin, tet_end;    // tet range of the subdomain
   int face_begin, face_end;  // range in the boundary-face array
 };
 
@@ -112,8 +109,8 @@ hipError_t launch_moments(int mm, const MeshDev& m, const FrameDev& f, const int
                           int64_t n_pairs, hipStream_t s);
 // pair_idx (tiles form, gacc null): per bin with faces its pair number; out is then [pairs][m+1][64]
 // (lane-minor), every lane of every pair written.  pair_list (may be null; gacc must be null): the bin of each of
-// the n_pairs pairs; a workgroup per pair then walks that pair alone (pcount must be null; segs and, without
-// pair_idx, out must hold zeros: what no pair covers stays, and a pixel's segments are added up)
+// the n_pairs pairs; a workgroup per pair then walks that pair alone (pcount must be null; segs must hold zeros, a
+// pixel's segments are added up; without pair_idx, out must hold zeros where no pair is, launch_clear_unpaired)
 // queue (both passes): null for one workgroup per tile; else QUEUE_INTS device ints that the launch
 // resets and a persistent launch (as many workgroups as the device holds) takes the tiles from
 constexpr int QUEUE_INTS = 8;
