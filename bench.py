@@ -422,8 +422,9 @@ def passes_by_size(ctx, r, seed, sizes=(256, 512, 1024, 2048, 2560)):
     """Both passes of orbit camera 0 at several image sizes on the renderer's mesh: one workgroup per tile
     against one per (tile, subdomain) pair plus the ordered sum of the pairs, each the best of 3 by the
     library's HIP events; stage one's global moments compared bit for bit, stage two's images by their
-    largest difference.  Stage one of a small frame goes by pairs either way: "by_tile" is then the call that
-    sums in the library, "by_pair" the one into the caller's tiles (stage_one_by_tile_is says which it was)."""
+    largest difference.  Unless the context takes its tiles from a work queue, stage one of a small frame goes by
+    pairs either way: "by_tile" is then the call that sums in the library, "by_pair" the one into the caller's
+    tiles (stage_one_by_tile_is says which it was)."""
     import torch
     import paper_2501_12581_amd as apc
     import synth
@@ -452,7 +453,8 @@ def passes_by_size(ctx, r, seed, sizes=(256, 512, 1024, 2048, 2560)):
                 t = tk["moments_ms"] + (tk["sum_ms"] if form == "by_pair" else 0.0)
                 best = t if best is None else min(best, t)
             res[form + "_ms"] = round(best, 3)
-        res["stage_one_by_tile_is"] = "by pairs" if res["tiles"] <= LIBRARY_PAIR_TILES else "by tiles"
+        res["stage_one_by_tile_is"] = ("by pairs" if res["tiles"] <= LIBRARY_PAIR_TILES and
+                                       ctx.dispatch() == apc.APC_DISPATCH_GRID else "by tiles")
         res["global_moments_bitwise_equal"] = bool(torch.equal(glob, mom))
         rgba2 = torch.empty_like(rgba)
         for form in ("by_tile", "by_pair"):

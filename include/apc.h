@@ -496,8 +496,8 @@ typedef struct apc_counters {
   int64_t table_samples;    /* samples (m >= 6) whose moment bound needed roots, found by Newton from those of
                                the ray's previous sample */
   int64_t table_fallback;   /* of those, samples without a carried start: with kept pieces the ones that took
-                               the closed-form roots (0.1 to 0.5 %: a start that did not converge), in the
-                               re-walk every first sample of a ray in a new gap of the bound (a few percent) */
+                               the closed-form roots (0.05 to 0.4 %: a start that did not converge), in the
+                               re-walk every first sample of a ray in a new gap of the bound (1 to 2 %) */
   int64_t segments;         /* maximal ray intervals inside one subdomain with at least one piece, every walk */
 } apc_counters;
 

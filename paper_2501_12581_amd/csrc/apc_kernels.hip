@@ -537,7 +537,7 @@ __device__ __forceinline__ void start_walk(const MeshDev& M, const Ray& r, int c
 // lanes on average.  The record of the next tet is asked for before the
 // rounds and used after them.  Bound by vector instructions issued (FP64
 // among them at the same rate).  Measured, m = 8, 2560^2 on 12.6M tets: 17.4 ms
-// with a loop per chord and 64-byte records, 12.0 ms now (56 lanes
+// with a loop per chord and 64-byte records, 12.2 ms now (56 lanes
 // the same); 1024^2 on 1.6M tets 1.72 -> 1.18 ms at m = 6.
 constexpr int ROUND_LANES = 48;
 template <class Sink>
@@ -967,14 +967,15 @@ __device__ __forceinline__ float pixel_bound(const void* moments, const BoundPar
 // Moment bound for every kept piece of a tile and the per-pixel colour sums
 // (Alg. 1 second loop, Alg. 3).  A lane takes its pixel's pieces in walk order,
 // each with the roots the previous one left (apcm::Bound::frac_continued, n >= 3).
-// Bound by FP64
-// arithmetic at n >= 3, whose few wavefronts re-read their lanes' lines from L2;
-// at n = 2 the lanes of all wavefronts hold more lines than L2 does, so a lane
-// reads four pieces at once (1024^2, m = 4: 2.9 ms one at a time, 1.1 now).  The form before took a pixel's pieces 64 at a time, one per lane,
-// each from a table of its gaps' roots that the 64 lanes filled with closed
+// Bound by FP64 arithmetic at n >= 3, whose few wavefronts re-read their lanes'
+// lines from L2; at n = 2 the lanes of all wavefronts hold more lines than L2
+// does, so a lane reads four pieces at once (1024^2, m = 4: 2.9 ms one at a
+// time, 1.1 now).  The form before took a pixel's pieces 64 at a time, one per
+// lane, each from a table of its gaps' roots that the 64 lanes filled with closed
 // forms first: a third of the time, and four Newton steps a piece.  Measured,
-// 1024^2 on 1.6M tets, before and now: m = 8 3.67 and 1.75 ms, m = 6 2.61 and 1.60,
-// m = 4 1.14 and 1.09.
+// 1024^2 on 1.6M tets in 16 subdomains, three views, before and now: m = 8 3.8 to
+// 4.1 and 1.9 to 2.3 ms, m = 6 2.7 to 2.9 and 1.7 to 1.9, m = 4 1.16 to 1.27 and
+// 1.08 to 1.21.
 constexpr int EVAL_WPB = 4;  // wavefronts (tiles) per workgroup: they share the transfer function in LDS
 
 template <int N, class R>
@@ -1141,7 +1142,7 @@ __global__ __launch_bounds__(WAVE * EVAL_WPB) __attribute__((amdgpu_waves_per_eu
 // The pair's shape for n = N roots: wavefronts per SIMD the kernel is compiled for (register budget 512 / n),
 // slots of the ring (one bit each in half a word) and evaluation rounds (one piece per lane) per phase at most.
 // Four wavefronts per SIMD need 128 registers and 20 KB of LDS per workgroup: the bound's state fits for n <= 3
-// with a ring of 8, and a phase there takes about what half the ring holds.  At n = 4 the state does not fit
+// (but for 3 registers at n = 3 by tiles) with a ring of 8, and a phase there takes about what half the ring holds.  At n = 4 the state does not fit
 // (spills in the loop: 83 ms), and a ring of 16 lets the walker run further ahead.  Measured, re-walk ms of the
 // 2560^2 frame of a 12.6M-tet mesh at m = 8: 3 wavefronts, ring 16: 33.2 with 12 rounds, 33.4 with 8; ring 8:
 // 34.1 with 5; of the 1024^2 frame of a 1.6M-tet mesh at m = 6 and m = 4: 4 wavefronts, ring 8, 5 rounds: 2.56
