@@ -212,7 +212,11 @@ typedef struct apc_mboit {
  * its subdomains are many) without APC_KEEP_PIECES under APC_DISPATCH_GRID is
  * walked pair by pair, as apc_moments_pass_pairs does, with the same results
  * bit for bit; with APC_MOMENTS_GLOBAL the pairs' moments take a context
- * buffer of up to 256 MiB (frames that need more go per tile). */
+ * buffer of up to 256 MiB (frames that need more go per tile).
+ * A frame's first pass bins its boundary faces and reads their number back;
+ * the next pass of the same mesh, camera, tile shape and subdomain list finds
+ * the bins at hand.  On a stream that the caller captures (in a graph of its
+ * own) a pass that has to bin is refused (APC_E_DEVICE, nothing launched). */
 apc_status apc_moments_pass(apc_ctx ctx, apc_mesh mesh, const apc_view* view, const apc_tf* tf, int32_t m,
                             const int32_t* subdomains, int32_t n_sub, float* moments_per_sub, uint32_t flags,
                             void* stream);
@@ -280,7 +284,8 @@ apc_status apc_pack_moments_f16(apc_ctx ctx, const float* moments_global, int32_
  * (another grouping of the colour sums, and each pair's root solver starts
  * afresh).  Reads the pair count back (the host waits for the binning's scan,
  * or for nothing when this frame's pairs are numbered already); not with
- * APC_MOMENTS_F16 or in a captured frame (APC_E_ARG).
+ * APC_MOMENTS_F16, in a captured frame or on a stream that the caller
+ * captures (APC_E_ARG).
  * flags: APC_FINALIZE, APC_MOMENTS_F16, APC_BY_PAIR. */
 apc_status apc_resolve_pass(apc_ctx ctx, apc_mesh mesh, const apc_view* view, const apc_tf* tf,
                             const apc_mboit* mboit, const void* moments_global, const int32_t* subdomains,

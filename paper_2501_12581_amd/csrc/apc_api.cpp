@@ -405,6 +405,18 @@ apc_status check_subdomains(const apc_mesh_s* m, const int32_t* subs, int32_t n_
 int* tile_queue(apc_ctx ctx) { return ctx->dispatch == APC_DISPATCH_QUEUE ? ctx->queue.as<int>() : nullptr; }
 long long bin_cap(apc_ctx ctx) { return (long long)(ctx->records.bytes / sizeof(int)); }
 
+// A stream that the caller captures in a graph of its own: nothing can be read back on it, and an event recorded on
+// it says nothing about work that is done.
+bool being_captured(apc_ctx ctx, hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (ctx->capturing) return false;  // (this library's own graph: its frame needs no read-back)
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
 // Where a frame's binning state lives: the context's growable buffers, or
 // fixed slices of the static workspace (apc_resolve_pass_noalloc).
 struct BinSpace {
@@ -423,6 +435,8 @@ struct BinSpace {
 // it has, and runs again where that turns out too small.
 apc_status bin_faces(apc_ctx ctx, const apc_mesh_s* m, const FrameDev& f, const int32_t* subs, int32_t n_sub,
                      BinSpace& B, hipStream_t s, MeshDev& md) {
+  if (being_captured(ctx, s))
+    return fail(APC_E_DEVICE, "the frame's binning reads its totals back: not on a stream under capture");
   SlotDev sl_fixed[64];
   std::vector<SlotDev> sl_big;
   SlotDev* sl = sl_fixed;
@@ -479,6 +493,13 @@ apc_status bin_faces(apc_ctx ctx, const apc_mesh_s* m, const FrameDev& f, const 
   return APC_OK;
 }
 
+// Do the context's bins belong to this mesh, view, tile shape and subdomain list?
+bool bins_at_hand(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const int32_t* subs, int32_t n_sub) {
+  return (ctx->capturing ? ctx->captured_bins : ctx->bins_valid) && ctx->bin_mesh == m->uid &&
+         ctx->bin_tw == ctx->tw_log2 && std::memcmp(&ctx->bin_view, v, sizeof(apc_view)) == 0 &&
+         ctx->bin_subs.size() == size_t(n_sub) && std::equal(subs, subs + n_sub, ctx->bin_subs.begin());
+}
+
 // Room for the numbers of nb bins' pairs.  The numbers at hand go with a buffer that has to grow.
 hipError_t number_room(apc_ctx ctx, int64_t nb) {
   if (ctx->pidx.bytes < sizeof(int) * nb) ctx->bin_pairs = -1;
@@ -492,13 +513,13 @@ apc_status build_bins(apc_ctx ctx, const apc_mesh_s* m, const apc_view* v, const
                       int32_t n_sub, bool pairs, hipStream_t s, MeshDev& md) {
   const int64_t nb = int64_t(f.n_tiles) * n_sub;
   if (pairs) HIPCHK(number_room(ctx, nb));
-  if ((ctx->capturing ? ctx->captured_bins : ctx->bins_valid) && ctx->bin_mesh == m->uid && ctx->bin_tw == ctx->tw_log2 &&
-      std::memcmp(&ctx->bin_view, v, sizeof(apc_view)) == 0 && ctx->bin_subs.size() == size_t(n_sub) &&
-      std::equal(subs, subs + n_sub, ctx->bin_subs.begin())) {
+  if (bins_at_hand(ctx, m, v, subs, n_sub)) {
     md.vert = m->vert;
     md.tet = m->tet;
     md.wrec = m->wrec;
     if (pairs && ctx->bin_pairs < 0 && !ctx->capturing) {  // binned without them
+      if (being_captured(ctx, s))
+        return fail(APC_E_DEVICE, "the pair count is read back: not on a stream under capture");
       HIPCHK(apc::launch_bin_scan(ctx->counts.as<int>(), nb, nullptr, nullptr, ctx->pidx.as<int>(),
                                   ctx->scan_tmp.as<int>(), ctx->totals, s));
       HIPCHK(hipEventRecord(ctx->totals_done, s));
@@ -1075,6 +1096,8 @@ apc_status apc_moments_pass(apc_ctx ctx, apc_mesh m, const apc_view* view, const
   hipStream_t s = static_cast<hipStream_t>(stream);
   MeshDev md;
   bool few = ctx->dispatch == APC_DISPATCH_GRID && !(flags & APC_KEEP_PIECES) && walk_by_pairs(m, f);
+  // bins at hand without numbers, on a stream under capture: the per-tile form needs none
+  if (few && bins_at_hand(ctx, m, view, subs, n_sub) && ctx->bin_pairs < 0 && being_captured(ctx, s)) few = false;
   if (few && number_room(ctx, int64_t(f.n_tiles) * n_sub) != hipSuccess) {
     (void)hipGetLastError();
     few = false;
@@ -1144,6 +1167,8 @@ apc_status moments_tiles(apc_ctx ctx, apc_mesh m, const apc_view* view, const ap
   if ((st = make_frame(m, view, tf, n_sub, max_tets_of(m, subs, n_sub), ctx->tw_log2, f)) != APC_OK) return st;
   if (ctx->host_only) return no_device(name);
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (being_captured(ctx, s))
+    return fail(APC_E_DEVICE, "%s reads its pair count back: not on a stream under capture", name);
   MeshDev md;
   // the pairs: the (tile, slot) bins that have faces, numbered
   if ((st = build_bins(ctx, m, view, f, subs, n_sub, true, s, md)) != APC_OK) return st;
@@ -1307,6 +1332,8 @@ static apc_status resolve_frame(apc_ctx ctx, apc_mesh m, const apc_view* view, c
   if ((flags & APC_BY_PAIR) && ctx->capturing)
     return fail(APC_E_ARG, "stage two by pairs reads its pair count back: not in a captured frame");
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if ((flags & APC_BY_PAIR) && being_captured(ctx, s))
+    return fail(APC_E_ARG, "stage two by pairs reads its pair count back: not on a stream under capture");
   const int nt = f.n_tiles;
   unsigned long long* ctr = ctx->counters.as<unsigned long long>();
   ctx->ev_used[EV_STG] = false;

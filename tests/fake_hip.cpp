@@ -35,6 +35,7 @@ size_t g_refuse_from = 1, g_refuse_to = 0;  // the next so many device allocatio
 int g_refusals = 0;
 unsigned long long g_records = 0, g_pairs = 0;  // what the scan of the bins reports
 uint64_t g_issued = 0, g_done = 0;              // work handed to the device, and waited for (one stream at a time)
+bool g_captured = false;                        // the caller captures the stream
 hipError_t g_last = hipSuccess;
 struct Event {
   uint64_t at = 0;
@@ -171,6 +172,10 @@ hipError_t hipDeviceSynchronize() {
 }
 hipError_t hipStreamSynchronize(hipStream_t) {
   g_done = g_issued;
+  return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) {
+  *st = g_captured ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
   return hipSuccess;
 }
 hipError_t hipEventCreate(hipEvent_t* e) {
@@ -475,6 +480,44 @@ int kept_mesh() {
   return 1;
 }
 
+// On a stream that the caller captures: what has to read totals back is refused before anything is launched; bins at
+// hand serve stage one (per tile where their pairs have no numbers) and stage two.
+int users_capture() {
+  Scene s(8);
+  g_records = 10;
+  g_pairs = 4;
+  const apc_view v = s.view(512, 512), w = s.view(512, 504);
+  auto walks = [] {
+    uint64_t n = 0;
+    for (const Launch& l : g_launches)
+      if (l.name.find("k_moments") != std::string::npos) n = l.grid;
+    return n;
+  };
+  int64_t n = 0;
+  g_captured = true;
+  g_launches.clear();
+  CHECK(s.moments_pass(v, APC_MOMENTS_GLOBAL) == APC_E_DEVICE);
+  CHECK(s.resolve(v, 0) == APC_E_DEVICE);
+  CHECK(APC(apc_resolve_pass_noalloc)(s.ctx, s.mesh, &v, &s.tf, &s.mb, s.moments, s.subs.data(), 8, s.rgba, 0,
+                                      nullptr) == APC_E_DEVICE);
+  CHECK(g_launches.empty());
+  g_captured = false;
+  CHECK(s.moments_pass(v, APC_MOMENTS_GLOBAL) == APC_OK);
+  g_captured = true;
+  g_launches.clear();
+  CHECK(s.resolve(v, APC_BY_PAIR) == APC_E_ARG);
+  CHECK(s.tiles(v, nullptr, nullptr, 0, &n) == APC_E_DEVICE);
+  CHECK(g_launches.empty());
+  CHECK(s.moments_pass(v, APC_MOMENTS_GLOBAL) == APC_OK && walks() == 4);
+  CHECK(s.resolve(v, 0) == APC_OK);
+  g_captured = false;
+  CHECK(s.resolve(w, 0) == APC_OK);  // binned without numbers
+  g_captured = true;
+  CHECK(s.moments_pass(w, APC_MOMENTS_GLOBAL) == APC_OK && walks() == 64 * 63);
+  CHECK(s.resolve(w, 0) == APC_OK);
+  return 0;
+}
+
 // The scan of very many bins adds up the sums of its workgroups in two levels, within its scratch memory.
 int many_bins() {
   Scene s(72);
@@ -521,6 +564,7 @@ int main(int argc, char** argv) {
       {"large_pair_lists", large_pair_lists},
       {"thin_images", thin_images},
       {"kept_mesh", kept_mesh},
+      {"users_capture", users_capture},
       {"many_bins", many_bins},
       {"moments_buffer", moments_buffer},
   };

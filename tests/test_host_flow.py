@@ -74,3 +74,8 @@ def test_the_buffer_of_the_pairs_moments_is_bounded(program):
 def test_kept_pieces_are_not_taken_for_another_mesh_at_the_same_address(program):
     """A mesh freed and another loaded where it was: stage two walks the new one."""
     _run(program, "kept_mesh")
+
+
+def test_a_stream_under_the_callers_capture_reads_nothing_back(program):
+    """Refused where totals are needed, and kernels only where the bins are at hand."""
+    _run(program, "users_capture")
